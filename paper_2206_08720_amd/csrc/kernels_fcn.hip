@@ -14,13 +14,16 @@
 #include <type_traits>
 
 #include "gemm_core.hpp"
+#include "gram_small.hpp"
 #include "launch.hpp"
+#include "pair_core.hpp"
 
 namespace ntk {
 
 using CfgBig = TileCfg<128, 128, 32, 64, 64>;   // 4 waves, 64x64 per wave
 using CfgBig8 = TileCfg<128, 128, 32, 32, 64>;  // 8 waves, 32x64 per wave
 using CfgSK = CfgBig8;                          // stream-K contraction
+using CfgSKPair = TileCfg<128, 128, 32, 64, 64>;   // the same on pair rows: 4 waves, 64x64 per wave
 // The stream-K contraction keeps two workgroups per compute unit (two LDS stages each, so
 // both fit the 160 KB of LDS): one workgroup's barrier waits are covered by the other's MFMAs.
 constexpr int kSkPerCu = 2, kSkStages = 2;
@@ -683,6 +686,10 @@ hipError_t launch_transpose_batch(hipStream_t s, const TransposeBatch& b) {
 }
 
 // ------------------------------------------------------------------------------ Grams
+// An entry of a Gram weights a whole O x O block of theta, so its rounding does not average out
+// there, and the layer inputs' products are mostly of one sign: the sum is formed in chunks of
+// kGramFlush k, whose sums are then added, which rounds less than one chain over all of K.
+constexpr int kGramFlush = 512;
 template <class Cfg, bool VEC, bool DMA>
 __global__ void __launch_bounds__(Cfg::THREADS)
 k_gram(GramBatch g, int N1, int N2, int tiles_n) {
@@ -691,18 +698,27 @@ k_gram(GramBatch g, int N1, int N2, int tiles_n) {
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
   const int K = g.K[z];
-  f32x16 acc[Cfg::FM][Cfg::FN];
-  zero_acc<Cfg>(acc);
-  if (DMA) {
-    gemm_mainloop_dma<Cfg, kGramStages>(g.h1[z], K, N1, g.h2[z], K, N2, m0, n0, 0, K, smem, acc);
-  } else {
-    LoadKInnerT<VEC> la{g.h1[z], N1, K, K};
-    LoadKInnerT<VEC> lb{g.h2[z], N2, K, K};
-    gemm_mainloop<Cfg>(la, lb, m0, n0, 0, K, smem, acc);
+  f32x16 tot[Cfg::FM][Cfg::FN];
+  zero_acc<Cfg>(tot);
+  for (int k0 = 0; k0 < K; k0 += kGramFlush) {
+    const int k1 = min(K, k0 + kGramFlush);
+    f32x16 acc[Cfg::FM][Cfg::FN];
+    zero_acc<Cfg>(acc);
+    if (DMA) {
+      gemm_mainloop_dma<Cfg, kGramStages>(g.h1[z], K, N1, g.h2[z], K, N2, m0, n0, k0, k1, smem, acc);
+    } else {
+      LoadKInnerT<VEC> la{g.h1[z], N1, K, K};
+      LoadKInnerT<VEC> lb{g.h2[z], N2, K, K};
+      gemm_mainloop<Cfg>(la, lb, m0, n0, k0, k1, smem, acc);
+    }
+#pragma unroll
+    for (int fm = 0; fm < Cfg::FM; ++fm)
+#pragma unroll
+      for (int fn = 0; fn < Cfg::FN; ++fn) tot[fm][fn] += acc[fm][fn];
   }
   float* out = g.out[z];
   const float beta = g.beta[z];
-  for_each_acc<Cfg>(acc, m0, n0, [&](int r, int c, float v) {
+  for_each_acc<Cfg>(tot, m0, n0, [&](int r, int c, float v) {
     if (r < N1 && c < N2) out[(long long)r * N2 + c] = v + beta;
   });
 }
@@ -768,74 +784,9 @@ hipError_t launch_gram_strided(hipStream_t s, const float* a1, const float* a2, 
   return v ? go(TrueT{}, FalseT{}) : go(FalseT{}, FalseT{});
 }
 
-// Small batches: the 64 x 64 tiles of k_gram would leave most compute units idle, so workgroup
-// (block, z) computes one 16 x 16 block of layer z's Gram with the 16x16x4 fp32 MFMA, its four
-// waves taking every fourth 16-column slice of K; the waves' partial blocks are then added in
-// wave order through LDS.  The MFMA takes A[i][k] from lane i + 16 k and B[k][j] from lane
-// j + 16 k, and returns D[4 (l / 16) + v][l % 16] in register v of lane l.  Lane l loads the four
-// columns k0 + 4 (l / 16) + q (q = 0..3) of row l % 16 of both operands, and MFMA q contracts
-// element q of both, so the four MFMAs cover the 16 columns of the slice (in a permuted order,
-// the same for both operands).
-template <bool VEC>
-__device__ __forceinline__ void gram_small_block(const GramBatch& g, int N1, int N2, int tiles_n, int bx, int z,
-                                                 float (*red)[256]) {
-  const int m0 = (bx / tiles_n) * 16, n0 = (bx % tiles_n) * 16;
-  const int K = g.K[z];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i = lane & 15, kq = 4 * (lane >> 4);
-  const bool va = m0 + i < N1, vb = n0 + i < N2;
-  const float* __restrict__ pa = g.h1[z] + (long long)min(m0 + i, N1 - 1) * K;
-  const float* __restrict__ pb = g.h2[z] + (long long)min(n0 + i, N2 - 1) * K;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  // batches of U slices: every load of a batch is issued before its MFMAs, from addresses
-  // clamped into the rows (a column past K reads a valid element and is zeroed), so that the
-  // loop body has no branch
-  constexpr int U = 4;
-  for (int kb = 16 * wave; kb < K; kb += 64 * U) {
-    f32x4 a[U], b[U];
-    bool in[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = kb + 64 * u + kq;
-      if (VEC) {   // K % 4 == 0 and 16-byte aligned rows: the 4 columns are all in or all out
-        in[u] = k < K;
-        const int kc = min(k, K - 4);
-        a[u] = *reinterpret_cast<const f32x4*>(pa + kc);
-        b[u] = *reinterpret_cast<const f32x4*>(pb + kc);
-      } else {
-        in[u] = true;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int kc = min(k + q, K - 1);
-          const float x = pa[kc], y = pb[kc];
-          a[u][q] = k + q < K ? x : 0.f;
-          b[u][q] = k + q < K ? y : 0.f;
-        }
-      }
-    }
-    // keep the loads of the batch ahead of its MFMAs
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool use_a = va && in[u], use_b = vb && in[u];
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(use_a ? a[u][q] : 0.f, use_b ? b[u][q] : 0.f, acc, 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int v = 0; v < 4; ++v) red[wave][(4 * (lane >> 4) + v) * 16 + i] = acc[v];
-  __syncthreads();
-  const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
-  if (m0 + r < N1 && n0 + c < N2) {
-    const float v = ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
-    g.out[z][(long long)(m0 + r) * N2 + n0 + c] = v + g.beta[z];
-  }
-}
-
 template <bool VEC>
 __global__ void __launch_bounds__(256) k_gram_small(GramBatch g, int N1, int N2, int tiles_n) {
-  __shared__ float red[4][256];
+  __shared__ double red[4][256];
   gram_small_block<VEC>(g, N1, N2, tiles_n, blockIdx.x, blockIdx.y, red);
 }
 
@@ -873,18 +824,8 @@ k_dense_bwd_ko_gram(const float* __restrict__ G, const float* __restrict__ W, in
     dense_bwd_ko_tile<Cfg>(G, W, R, N, K, epi, tiles_n, blockIdx.x, smem);
   } else {
     const int b = blockIdx.x - nbwd;
-    gram_small_block<GVEC>(g, N1, N2, gtiles_n, b % gblocks, b / gblocks, reinterpret_cast<float (*)[256]>(smem));
+    gram_small_block<GVEC>(g, N1, N2, gtiles_n, b % gblocks, b / gblocks, reinterpret_cast<double (*)[256]>(smem));
   }
-}
-
-static bool gram_small_fits(const GramBatch& g, int N1, int N2, int num_cu) {
-  return g.count > 0 && (long long)cdiv(N1, 64) * cdiv(N2, 64) * g.count < num_cu;
-}
-
-static bool gram_batch_vec(const GramBatch& g) {
-  bool v = true;
-  for (int z = 0; z < g.count; ++z) v = v && vec_ok(g.h1[z], g.K[z], g.K[z]) && vec_ok(g.h2[z], g.K[z], g.K[z]);
-  return v;
 }
 
 hipError_t launch_dense_bwd_w_gram(hipStream_t s, const float* G, const float* W, const float* dphi, int R, int N,
@@ -901,7 +842,7 @@ hipError_t launch_dense_bwd_w_gram(hipStream_t s, const float* G, const float* W
   const int gtn = cdiv(N2, 16), gblocks = cdiv(N1, 16) * gtn;
   const long long blocks = (long long)tm * tn + (long long)gblocks * g.count;
   constexpr int bytes = gemm_dma_smem_bytes<Cfg, 2>();
-  static_assert(bytes >= 4 * 256 * 4, "the Gram blocks' partials fit the LDS of the tiles");
+  static_assert(bytes >= 4 * 256 * 8, "the Gram blocks' partials fit the LDS of the tiles");
   auto go = [&](auto kern) -> hipError_t {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e != hipSuccess) return e;
@@ -933,6 +874,74 @@ __device__ __forceinline__ void stage_gram(const float* __restrict__ gram, int N
   __syncthreads();
 }
 
+// Pair rows: the exponents of the tile's rows of batch 1 (staged in LDS as integers) and of this
+// lane's columns of batch 2 (per fragment column, from memory).  tot += gram * 2^(e1 + e2) acc.
+template <class Cfg>
+__device__ __forceinline__ void pair_weighted_add(const float* sg, const int* se, const int* __restrict__ e2, int R1,
+                                                  int R2, FastDiv fO, int n1lo, int n2lo, int S2, int m0, int n0,
+                                                  int wm0, int wn0, int lane, const f32x16 (&acc)[Cfg::FM][Cfg::FN],
+                                                  f32x16 (&tot)[Cfg::FM][Cfg::FN]) {
+#pragma unroll
+  for (int fn = 0; fn < Cfg::FN; ++fn) {
+    const int s = min(n0 + wn0 + fn * 32 + (lane & 31), R2 - 1);
+    const int b = (int)fO.div(s) - n2lo, es = e2[s];
+#pragma unroll
+    for (int fm = 0; fm < Cfg::FM; ++fm) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int i = wm0 + fm * 32 + frag_row(v, lane);
+        const int r = min(m0 + i, R1 - 1);
+        const int a = (int)fO.div(r) - n1lo;
+        tot[fm][fn][v] += sg[a * S2 + b] * ldexpf(acc[fm][fn][v], se[i] + es);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+// LDS of the contraction on pair rows: NSTAGE stages, then the tile's Gram block, then the
+// exponents of its rows
+template <class Cfg, int NSTAGE>
+constexpr int pair_gram_offset() {
+  return NSTAGE * (Cfg::BM + Cfg::BN) * 32;
+}
+// a tile of BM rows (n, o) touches at most (BM - 1) / O + 2 samples
+template <class Cfg>
+__host__ __device__ inline int gram_block_floats(int O) {
+  return (((Cfg::BM - 1) / O + 2) * ((Cfg::BN - 1) / O + 2) + 3) / 4 * 4;
+}
+template <class Cfg, int NSTAGE>
+__host__ inline int pair_smem_bytes(int O) {
+  return (pair_gram_offset<Cfg, NSTAGE>() + gram_block_floats<Cfg>(O) + Cfg::BM) * 4;
+}
+// The sum over a layer's k is flushed into the tile's total every FLUSH k: shorter chains of
+// roundings than one over all of K (the fp32 accumulator is rounded three times per 16 k).
+// Error of theta against 64 bits, fp32 MFMA / pair rows in one chain / flushed: 9.9e-8 / 1.2e-7 /
+// 1.0e-7 (512) on widths 1001, 750, 301; 2.6e-7 / 1.9e-7 / 1.4e-7 (512) at depth 8, width 2048,
+// where each flush of the large tiles costs 2 % of the contraction.
+constexpr int kPairFlushSmall = 256, kPairFlushBig = 1024;
+template <class Cfg, int NSTAGE, int FLUSH>
+__device__ __forceinline__ void fcn_pair_layer(const FcnContraction& c, int l, int N2, int R1, int R2, FastDiv fO,
+                                               int m0, int n0, float* smem, f32x16 (&tot)[Cfg::FM][Cfg::FN]) {
+  const int lane_id = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm0 = (wave / Cfg::WAVES_N) * Cfg::WM, wn0 = (wave % Cfg::WAVES_N) * Cfg::WN;
+  float* sg = smem + pair_gram_offset<Cfg, NSTAGE>();
+  int* se = reinterpret_cast<int*>(sg + gram_block_floats<Cfg>((int)fO.d));
+  for (int i = threadIdx.x; i < Cfg::BM; i += Cfg::THREADS) se[i] = c.exps[l * c.exps_ld + min(m0 + i, R1 - 1)];
+  int n1lo, n2lo, S2;
+  stage_gram<Cfg>(c.gram[l], N2, R1, R2, fO, m0, n0, sg, n1lo, n2lo, S2);
+  for (int k0 = 0; k0 < c.K[l]; k0 += FLUSH) {
+    f32x16 acc[Cfg::FM][Cfg::FN];
+    zero_acc<Cfg>(acc);
+    pair_mainloop<Cfg, NSTAGE>(c.G1[l], c.K[l], R1, c.G2[l], c.K[l], R2, m0, n0, k0, min(FLUSH, c.K[l] - k0), smem,
+                               acc);
+    // an opaque copy of the lane index keeps the addresses below out of the main loop's registers
+    int lane = lane_id;
+    asm volatile("" : "+v"(lane));
+    pair_weighted_add<Cfg>(sg, se, c.exps + l * c.exps_ld + c.exps_off, R1, R2, fO, n1lo, n2lo, S2, m0, n0, wm0, wn0, lane, acc, tot);
+  }
+  __syncthreads();
+}
+
 // tot += gram_l[n1, n2] * (G1_l G2_l^T) over the tile at (m0, n0) (the scalar x1.x2 of Eq.
 // mixed_product_example weights the cotangent product); the tile's Gram block is staged in the
 // LDS tile area, free after the main loop.  Ends with a barrier.
@@ -946,11 +955,11 @@ __device__ __forceinline__ void fcn_layer_term(const FcnContraction& c, int l, i
   LoadKInnerT<VEC> lb{c.G2[l], R2, K, K};
   f32x16 acc[Cfg::FM][Cfg::FN];
   zero_acc<Cfg>(acc);
+  int n1lo, n2lo, S2;
   if (DMA)
     gemm_mainloop_dma<Cfg, kSplitStages>(c.G1[l], K, R1, c.G2[l], K, R2, m0, n0, 0, K, smem, acc);
   else
     gemm_mainloop<Cfg>(la, lb, m0, n0, 0, K, smem, acc);
-  int n1lo, n2lo, S2;
   stage_gram<Cfg>(c.gram[l], N2, R1, R2, fO, m0, n0, smem, n1lo, n2lo, S2);
 #pragma unroll
   for (int fn = 0; fn < Cfg::FN; ++fn) {
@@ -1107,7 +1116,7 @@ __device__ __forceinline__ void fcn_tile_reduce(const float* __restrict__ gram_r
   }
 }
 
-template <class Cfg, bool VEC, bool DMA>
+template <class Cfg, bool VEC, bool DMA, bool PAIR = false>
 __global__ void __launch_bounds__(Cfg::THREADS)
 k_ntk_fcn_lpart(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, int tiles_n, int T, int NG,
                 float* __restrict__ part) {
@@ -1125,7 +1134,12 @@ k_ntk_fcn_lpart(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, int
   const int l0 = (int)((long long)g * c.L / NG), l1 = (int)((long long)(g + 1) * c.L / NG);
   f32x16 tot[Cfg::FM][Cfg::FN];
   zero_acc<Cfg>(tot);
-  for (int l = l0; l < l1; ++l) fcn_layer_term<Cfg, VEC, DMA>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
+  for (int l = l0; l < l1; ++l) {
+    if constexpr (PAIR)
+      fcn_pair_layer<Cfg, kSplitStages, kPairFlushSmall>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
+    else
+      fcn_layer_term<Cfg, VEC, DMA>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
+  }
   float* P = part + ((long long)g * T + t) * (Cfg::BM * Cfg::BN);
   for_each_acc<Cfg>(tot, 0, 0, [&](int r, int s, float v) { P[r * Cfg::BN + s] = v; });
 }
@@ -1226,7 +1240,7 @@ __device__ __forceinline__ void fcn_tile_layers(const FcnContraction& c, int l0,
 
 // kSkPerCu workgroups per compute unit must be resident together: the register budget is that
 // of kSkPerCu * THREADS / 256 waves per SIMD
-template <class Cfg, bool VEC, bool DMA>
+template <class Cfg, bool VEC, bool DMA, bool PAIR = false>
 __global__ void __launch_bounds__(Cfg::THREADS, kSkPerCu * Cfg::THREADS / 256)
 k_ntk_fcn_sk(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, float* __restrict__ theta,
              int tiles_m, int tiles_n, int T, int P, float* __restrict__ part) {
@@ -1260,7 +1274,11 @@ k_ntk_fcn_sk(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, float*
     const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
     f32x16 tot[Cfg::FM][Cfg::FN];
     zero_acc<Cfg>(tot);
-    fcn_tile_layers<Cfg, VEC, DMA>(c, l0, l1, N2, fO, R1, R2, m0, n0, smem, tot);
+    if constexpr (PAIR) {
+      for (int l = l0; l < l1; ++l) fcn_pair_layer<Cfg, kSkStages, kPairFlushBig>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
+    } else {
+      fcn_tile_layers<Cfg, VEC, DMA>(c, l0, l1, N2, fO, R1, R2, m0, n0, smem, tot);
+    }
     if (l0 == 0 && l1 == L) {
       fcn_tile_out<Cfg>(tot, c.gram_readout, c.readout_scale, N1, N2, fO, R1, R2, m0, n0, symmetric && tm != tn, smem,
                         theta);
@@ -1350,17 +1368,25 @@ static bool fcn_uses_stream_k(int L, long long big_tiles, int num_cu, bool part)
 
 // Few output tiles: the number of layer groups of the layer-split contraction (>= 2), or 0 when
 // that form does not apply.
-static int fcn_split_groups(long long R1, long long R2, int L, int symmetric, int num_cu, bool part) {
+// Pair rows have no other form below the stream-K size: one group and any number of tiles there.
+static int fcn_split_groups(long long R1, long long R2, int L, int symmetric, int num_cu, bool part, bool pair) {
   const long long big_tiles = (long long)cdiv(R1, 128) * cdiv(R2, 128);
-  if (!part || L < 2 || fcn_uses_stream_k(L, big_tiles, num_cu, part) || big_tiles >= 512) return 0;
+  if (!part || fcn_uses_stream_k(L, big_tiles, num_cu, part)) return 0;
+  if (!pair && (L < 2 || big_tiles >= 512)) return 0;
   // fewer 64 x 64 tiles than two per compute unit: about four workgroups per compute unit in
   // all, as far as the partial tiles fit the buffer
   const long long ts_m = cdiv(R1, 64), ts_n = cdiv(R2, 64);
   const long long Ts = symmetric ? ts_n * (ts_n + 1) / 2 : ts_m * ts_n;
-  if (Ts >= 2LL * num_cu) return 0;
+  if (!pair && Ts >= 2LL * num_cu) return 0;
   long long NG = std::min<long long>(L, (4LL * num_cu + Ts - 1) / Ts);
   NG = std::min<long long>(NG, ntk_fcn_part_floats(num_cu) / (Ts * 4096));
-  return NG >= 2 ? (int)NG : 0;
+  return NG >= (pair ? 1 : 2) ? (int)NG : 0;
+}
+
+bool ntk_fcn_pair_ok(long long R1, long long R2, int L, int symmetric, int num_cu, bool part) {
+  const long long big_tiles = (long long)cdiv(R1, 128) * cdiv(R2, 128);
+  return L >= 1 && (fcn_uses_stream_k(L, big_tiles, num_cu, part) ||
+                    fcn_split_groups(R1, R2, L, symmetric, num_cu, part, true) >= 1);
 }
 
 hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2, int O,
@@ -1385,10 +1411,13 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
   };
   bool dma = v;
   for (int l = 0; l < c.L; ++l) dma = dma && c.K[l] % 32 == 0 && dma_span_ok(c.K[l], c.K[l], 256);
-  auto go_sk = [&](auto vec_tag, auto dma_tag) -> hipError_t {
-    using Cfg = CfgSK;
+  const bool pair = c.L > 0 && c.exps;
+  if (pair && !dma) return hipErrorInvalidValue;   // pair rows are aligned and padded to 32 k
+  auto go_sk = [&](auto vec_tag, auto dma_tag, auto pair_tag) -> hipError_t {
     constexpr bool VEC = decltype(vec_tag)::value;
     constexpr bool DMA = decltype(dma_tag)::value;
+    constexpr bool PAIR = decltype(pair_tag)::value;
+    using Cfg = std::conditional_t<PAIR, CfgSKPair, CfgSK>;
     using L = LoadKInnerT<VEC>;
     const int tm = cdiv(R1, Cfg::BM), tn = cdiv(R2, Cfg::BN);
     const int T = symmetric ? tn * (tn + 1) / 2 : tm * tn;
@@ -1396,13 +1425,14 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
     // LDS: the main loop's stages, or the Gram block of a tile if larger
     constexpr int loop_bytes = DMA ? gemm_dma_smem_bytes<Cfg, kSkStages>() : gemm_smem_bytes<Cfg, L, L>();
     constexpr int gram_bytes = (Cfg::BM + 1) * (Cfg::BN + 1) * 4;
-    constexpr int bytes = loop_bytes > gram_bytes ? loop_bytes : gram_bytes;
-    static_assert(kSkPerCu * bytes <= 160 * 1024, "the workgroups of one CU must fit its LDS");
-    hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_sk<Cfg, VEC, DMA>,
+    constexpr int max_bytes = loop_bytes > gram_bytes ? loop_bytes : gram_bytes;
+    static_assert(kSkPerCu * max_bytes <= 160 * 1024, "the workgroups of one CU must fit its LDS");
+    const int bytes = PAIR ? pair_smem_bytes<Cfg, kSkStages>(O) : max_bytes;
+    hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_sk<Cfg, VEC, DMA, PAIR>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e != hipSuccess) return e;
     const FastDiv fO((uint32_t)O);
-    k_ntk_fcn_sk<Cfg, VEC, DMA><<<dim3(P), dim3(Cfg::THREADS), bytes, s>>>(
+    k_ntk_fcn_sk<Cfg, VEC, DMA, PAIR><<<dim3(P), dim3(Cfg::THREADS), bytes, s>>>(
         c, N1, N2, fO, symmetric, theta, tm, tn, T, P, part);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1411,24 +1441,29 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
     return hipGetLastError();
   };
   const long long big_tiles = (long long)cdiv(R1, 128) * cdiv(R2, 128);
-  if (fcn_uses_stream_k(c.L, big_tiles, num_cu, part != nullptr))
-    return dma ? go_sk(TrueT{}, TrueT{}) : (v ? go_sk(TrueT{}, FalseT{}) : go_sk(FalseT{}, FalseT{}));
-  if (big_tiles >= 512) return v ? go(CfgBig8{}, TrueT{}) : go(CfgBig8{}, FalseT{});
-  const int NG = fcn_split_groups(R1, R2, c.L, symmetric, num_cu, part != nullptr);
-  auto go_split = [&](auto vec_tag, auto dma_tag) -> hipError_t {
+  if (fcn_uses_stream_k(c.L, big_tiles, num_cu, part != nullptr)) {
+    if (pair) return go_sk(TrueT{}, TrueT{}, TrueT{});
+    return dma ? go_sk(TrueT{}, TrueT{}, FalseT{})
+               : (v ? go_sk(TrueT{}, FalseT{}, FalseT{}) : go_sk(FalseT{}, FalseT{}, FalseT{}));
+  }
+  if (!pair && big_tiles >= 512) return v ? go(CfgBig8{}, TrueT{}) : go(CfgBig8{}, FalseT{});
+  const int NG = fcn_split_groups(R1, R2, c.L, symmetric, num_cu, part != nullptr, pair);
+  auto go_split = [&](auto vec_tag, auto dma_tag, auto pair_tag) -> hipError_t {
     using Cfg = CfgSmall;
     constexpr bool VEC = decltype(vec_tag)::value;
     constexpr bool DMA = decltype(dma_tag)::value;
+    constexpr bool PAIR = decltype(pair_tag)::value;
     using L = LoadKInnerT<VEC>;
-    constexpr int bytes = DMA ? gemm_dma_smem_bytes<Cfg, kSplitStages>() : gemm_smem_bytes<Cfg, L, L>();
-    static_assert(64 * 64 <= bytes / 4, "Gram block must fit the LDS tile area");
+    constexpr int max_bytes = DMA ? gemm_dma_smem_bytes<Cfg, kSplitStages>() : gemm_smem_bytes<Cfg, L, L>();
+    static_assert(64 * 64 <= max_bytes / 4, "Gram block must fit the LDS tile area");
+    const int bytes = PAIR ? pair_smem_bytes<Cfg, kSplitStages>(O) : max_bytes;
     const int tm = cdiv(R1, 64), tn = cdiv(R2, 64);
     const int T = symmetric ? tn * (tn + 1) / 2 : tm * tn;
     const FastDiv fO((uint32_t)O);
-    hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_lpart<Cfg, VEC, DMA>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_lpart<Cfg, VEC, DMA, PAIR>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e != hipSuccess) return e;
-    k_ntk_fcn_lpart<Cfg, VEC, DMA><<<dim3(8 * cdiv((long long)T * NG, 8)), dim3(Cfg::THREADS), bytes, s>>>(
+    k_ntk_fcn_lpart<Cfg, VEC, DMA, PAIR><<<dim3(8 * cdiv((long long)T * NG, 8)), dim3(Cfg::THREADS), bytes, s>>>(
         c, N1, N2, fO, symmetric, tn, T, NG, part);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1436,7 +1471,11 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
                                                     NG, part, theta);
     return hipGetLastError();
   };
-  if (NG >= 2) return dma ? go_split(TrueT{}, TrueT{}) : (v ? go_split(TrueT{}, FalseT{}) : go_split(FalseT{}, FalseT{}));
+  if (NG >= 1 && pair) return go_split(TrueT{}, TrueT{}, TrueT{});
+  if (pair) return hipErrorInvalidValue;
+  if (NG >= 2)
+    return dma ? go_split(TrueT{}, TrueT{}, FalseT{})
+               : (v ? go_split(TrueT{}, FalseT{}, FalseT{}) : go_split(FalseT{}, FalseT{}, FalseT{}));
   return v ? go(CfgSmall{}, TrueT{}) : go(CfgSmall{}, FalseT{});
 }
 

@@ -4,6 +4,8 @@
 
 #include <algorithm>
 
+#include "index_math.hpp"
+
 namespace ntk {
 
 constexpr int kMaxLayers = 64;  // parametrised layers a model may have
@@ -83,17 +85,68 @@ struct TransposeBatch {
 };
 hipError_t launch_transpose_batch(hipStream_t s, const TransposeBatch& b);
 
-struct GramBatch {
-  const float* h1[kMaxLayers + 1];
-  const float* h2[kMaxLayers + 1];
-  float* out[kMaxLayers + 1];
-  int K[kMaxLayers + 1];
-  float beta[kMaxLayers + 1];
+// ---- fp32 products on the f16 matrix cores (pair rows, pair_core.hpp) ----------------------
+// The transposed weights of all layers as pair rows: out[z] holds N[z] rows of pair_stride(K[z])
+// floats for W[z] [K, N]; exps[z][n] the row exponents; l1[z][i] the largest sum_k |W[k, n]| of
+// the i-th strip of kPairStrip columns (cdiv(N, kPairStrip) strips).
+constexpr int kPairStrip = 64;
+template <int ML>
+struct PairWeightsT {
+  const float* W[ML];
+  float* out[ML];
+  int* exps[ML];
+  float* l1[ML];
+  float* stats[ML];   // scratch, pair_stats_floats(K, N)
+  int K[ML], N[ML];
   int count;
 };
+using PairWeights = PairWeightsT<kMaxLayers>;
+long long pair_stats_floats(long long K, long long N);
+hipError_t launch_pair_weights(hipStream_t s, const PairWeights& b);
+// Pair rows of Wr[o, c] dphi[n, c], r = (n, o) < R, c < K; exponents and the rows' largest scaled
+// elements.
+hipError_t launch_pair_seed(hipStream_t s, const float* Wr, const float* dphi, int R, int O, int K, float* out,
+                            int* exps, float* rmax);
+// One layer of the cotangent backward, out[r, n] = (sum_k G[r, k] W[k, n]) * dphi[r / O, n].
+struct PairBwd {
+  const float* G;         // pair rows [R, Kp]
+  const int* exps_in;     // [R]
+  const float* rmax_in;   // rmax_parts x [rmax_ld]: maxima of scaled |G| over parts of a row
+  int rmax_parts;
+  long long rmax_ld;
+  const float* W;         // pair rows of the transposed weights [N, Kp]
+  const int* wexps;       // [N]
+  const float* l1;        // l1_parts column-sum maxima
+  int l1_parts;
+  int act_exp;            // |dphi| <= 2^act_exp
+  const float* dphi;      // [R / O, N]
+  int R, N, Kp;
+  FastDiv fO;
+  float* out;             // pair rows [R, pair_stride(N)], or null
+  float* out32;           // fp32 rows [R, N], or null
+  int* exps_out;          // [R]
+  float* rmax_out;        // pair_bwd_parts x [rmax_ld]
+  int vec;                // set by the launcher
+};
+int pair_bwd_parts(int R, int N, int num_cu);
+hipError_t launch_pair_bwd(hipStream_t s, PairBwd p, int num_cu);
+
+template <int ML>
+struct GramBatchT {
+  const float* h1[ML];
+  const float* h2[ML];
+  float* out[ML];
+  int K[ML];
+  float beta[ML];
+  int count;
+};
+using GramBatch = GramBatchT<kMaxLayers + 1>;
 // out_l[n1, n2] = h1_l[n1] . h2_l[n2] + beta_l for every l (rows of h have stride K_l).
 // Batches whose 64 x 64 tiles would not fill num_cu compute units run in 16 x 16 blocks.
 hipError_t launch_gram(hipStream_t s, const GramBatch& g, int N1, int N2, int num_cu);
+// launch_pair_weights, launch_pair_seed and launch_gram, in one launch for small problems.
+hipError_t launch_pair_prep(hipStream_t s, const PairWeights& b, const float* Wr, const float* dphi, int R, int O, int K,
+                            float* out, int* exps, float* rmax, const GramBatch& g, int N1, int N2, int num_cu);
 // launch_dense_bwd_w and launch_gram together, in one launch where the layer's tiles leave
 // compute units idle and the Grams take 16 x 16 blocks.
 hipError_t launch_dense_bwd_w_gram(hipStream_t s, const float* G, const float* W, const float* dphi, int R, int N,
@@ -107,6 +160,10 @@ struct FcnContraction {
   const float* G1[kMaxLayers];    // cotangents of batch 1, [N1*O, K_l]
   const float* G2[kMaxLayers];    // cotangents of batch 2, [N2*O, K_l]
   const float* gram[kMaxLayers];  // [N1, N2] input Gram (+ bias term) of layer l
+  // pair rows (pair_core.hpp): the exponents of the rows of G1_l at exps + l exps_ld, those of G2_l
+  // exps_off further on, K the padded row length; exps null: fp32 rows
+  const int* exps;
+  long long exps_ld, exps_off;
   int K[kMaxLayers];
   int L;                          // number of hidden layers (summands with a cotangent Gram)
   const float* gram_readout;      // [N1, N2], multiplies delta_{o1 o2}
@@ -118,6 +175,8 @@ struct FcnContraction {
 // Large problems use a stream-K schedule over num_cu persistent workgroups with a partial
 // buffer `part` of ntk_fcn_part_floats(num_cu) floats (part may be null: no stream-K).
 long long ntk_fcn_part_floats(int num_cu);
+// whether the contraction of R1 x R2 cotangent rows has a form on pair rows
+bool ntk_fcn_pair_ok(long long R1, long long R2, int L, int symmetric, int num_cu, bool part);
 hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2, int O,
                           int symmetric, float* theta, int num_cu, float* part);
 

@@ -18,6 +18,7 @@
 #include "../../include/ntk.h"
 #include "launch.hpp"
 #include "launch_conv.hpp"
+#include "pair_core.hpp"
 #include "launch_struct.hpp"
 
 namespace ntk {
@@ -138,6 +139,15 @@ struct ntk_handle {
   std::vector<size_t> off_Wt;     // Wt_l,   l = 1..L-1    [d_l, d_{l+1}]
   std::vector<size_t> off_gram;   // gram_l, l = 0..L      [max_n1*max_n2]
   std::vector<int> param_index;   // first parameter slot of dense layer l
+  // pair rows (fp32 products on the f16 matrix cores, pair_core.hpp); false: no buffers for them
+  bool pair = false;
+  size_t off_ge = 0;              // exponents of the rows of G_l                  [L, Mmax*O]
+  std::vector<size_t> off_we;     // exponents of the rows of Wt_l, l = 1..L-1     [d_l]
+  std::vector<size_t> off_l1;     // column-sum maxima of W_l                      [strips of d_l]
+  std::vector<size_t> off_ws;     // column statistics of W_l by row chunks
+  size_t off_rmax[2] = {0, 0};    // row maxima of two neighbouring layers         [parts, Mmax*O]
+  size_t off_gp[2] = {0, 0};      // pair rows of two neighbouring layers for the variants, whose
+                                  // contractions read fp32 rows                   [Mmax*O, padded]
   int num_cu = 0;                 // compute units of the device (stream-K workgroup count)
   size_t off_skpart = 0;          // stream-K partial tiles of the contraction
   size_t off_fpart = 0;           // fp64 split-K partials of the small-batch forward
@@ -349,6 +359,18 @@ static int check_index_range(const ntk_handle& t, long long n1, long long n2) {
                   "in sample blocks instead)");
 }
 
+// Whether the padded pair rows of a fully-connected net keep to the index range as well.
+static bool pair_in_range(const ntk_handle& t) {
+  const long long MO = smul((long long)t.max_n1 + t.max_n2, t.out_dim);
+  for (size_t l = 0; l + 1 < t.layers.size(); ++l) {
+    const long long in = t.layers[l].in, out = t.layers[l].out;
+    if (smul(MO, pair_stride(out)) > kMaxElems || smul(in, pair_stride(out)) > kMaxElems ||
+        smul(MO, (out + 63) / 64) > kMaxElems || !dma_span_ok(pair_stride(out), pair_stride(out), 256))
+      return false;
+  }
+  return true;
+}
+
 static size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
 // ------------------------------------------------------------------------------ planning
@@ -374,8 +396,27 @@ static void plan_fcn(ntk_handle* h) {
   h->off_gram.assign(L + 1, 0);
   for (int l = 0; l <= L; ++l) h->off_h[l] = take(Mmax * h->dims[l]);
   for (int l = 0; l < L; ++l) h->off_dphi[l] = take(Mmax * h->dims[l + 1]);
-  for (int l = 0; l < L; ++l) h->off_G[l] = take(Mmax * O * h->dims[l + 1]);
-  for (int l = 1; l < L; ++l) h->off_Wt[l] = take((size_t)h->dims[l] * h->dims[l + 1]);
+  // G_l and Wt_l hold fp32 rows or pair rows (the latter padded)
+  auto row = [&](int d) { return h->pair ? (size_t)pair_stride(d) : (size_t)d; };
+  for (int l = 0; l < L; ++l) h->off_G[l] = take(Mmax * O * row(h->dims[l + 1]));
+  for (int l = 1; l < L; ++l) h->off_Wt[l] = take((size_t)h->dims[l] * row(h->dims[l + 1]));
+  if (h->pair) {
+    h->off_we.assign(std::max(L, 1), 0);
+    h->off_l1.assign(std::max(L, 1), 0);
+    h->off_ws.assign(std::max(L, 1), 0);
+    h->off_ge = take((size_t)L * Mmax * O);
+    size_t parts = 1, widest = 0;
+    for (int l = 0; l < L; ++l) {
+      parts = std::max(parts, (size_t)(h->dims[l + 1] + 63) / 64);
+      widest = std::max(widest, row(h->dims[l + 1]));
+      if (l == 0) continue;
+      h->off_we[l] = take(h->dims[l]);
+      h->off_l1[l] = take((h->dims[l] + kPairStrip - 1) / kPairStrip);
+      h->off_ws[l] = take((size_t)pair_stats_floats(h->dims[l + 1], h->dims[l]));
+    }
+    for (int i = 0; i < 2 && L >= 1; ++i) h->off_rmax[i] = take(parts * Mmax * O);
+    for (int i = 0; i < 2 && L >= 2; ++i) h->off_gp[i] = take(Mmax * O * widest);
+  }
   for (int l = 0; l <= L; ++l) h->off_gram[l] = take((size_t)h->max_n1 * h->max_n2);
   if (h->lean) {   // the full theta only: no stream-K, no split forward, no one-output variants
     h->off_skpart = h->off_fpart = h->off_vpart = 0;
@@ -554,11 +595,19 @@ extern "C" int ntk_init(const ntk_model_desc* model, int max_n1, int max_n2, voi
     delete h;
     return hip_fail(nullptr, e, "hipDeviceGetAttribute");
   }
-  if (h->cnn)
+  if (h->cnn) {
     plan_cnn(h);
-  else
+  } else {
+    h->pair = pair_in_range(*h);
     plan_fcn(h);
+  }
   e = hipMalloc((void**)&h->ws, h->ws_bytes);
+  if (e != hipSuccess && h->pair) {   // without the pair rows' buffers
+    (void)hipGetLastError();
+    h->pair = false;
+    plan_fcn(h);
+    e = hipMalloc((void**)&h->ws, h->ws_bytes);
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     size_t bytes = h->ws_bytes;
@@ -734,6 +783,26 @@ static int fcn_forward(ntk_handle* h, const float* const* params, const float* X
   return fcn_forward_rows(h, params, *h0, 0, sym ? n1 : n1 + n2, h->stream, true, seedW, seedO, seedG);
 }
 
+// Whether the backward (and the contraction of `pairs` input pairs) of a fully-connected net runs
+// on pair rows.  It costs one more launch (the weights' and the seed's pair rows), so small
+// problems keep the fp32 kernels: equal at 3.7 GFLOP on widths that take the direct-to-LDS fp32
+// kernels (64 + 64 samples, width 512, depth 4: 85.2 against 83.8 us; 1.4 GFLOP, width 128:
+// 55.0 against 57.3), below 1 GFLOP on widths that do not (width 250, depth 4: 122 against
+// 90 us).  Layers narrower than 128 keep fp32: sums that short are no more exact on pairs.
+constexpr double kPairMinFlops = 3e9, kPairMinFlopsRagged = 5e8;
+static bool fcn_pair_pays(const ntk_handle* h, int M, int Oe, double pairs) {
+  double flops = 0;
+  bool ragged = false;
+  for (int l = 0; l < h->L; ++l) {
+    const double d = h->dims[l + 1];
+    if (d < 128) return false;
+    ragged = ragged || h->dims[l + 1] % 32 != 0;
+    if (l >= 1) flops += 2.0 * M * Oe * d * h->dims[l];
+    flops += 2.0 * pairs * Oe * Oe * d;
+  }
+  return flops >= (ragged ? kPairMinFlopsRagged : kPairMinFlops);
+}
+
 // forward FLOPs from which the FCN path puts independent steps on the second stream
 constexpr double kAuxStreamMinFlops = 4e9;
 
@@ -765,7 +834,41 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
   // that no transposed copies are made; with one stream, the Grams in the launch of the first
   // backward layer
   bool bwd_w = false, gram_in_bwd = false;
+  // The backward and the full contraction on pair rows; the variants' contractions read fp32 rows,
+  // which the backward then writes beside them.
+  const bool full = !logit && !trace && !diag;
+  const bool pair = h->pair && !jc && L >= 1 && fcn_pair_pays(h, M, Oe, full ? (sym ? 0.5 : 1.0) * n1 * n2 : 0.0) &&
+                    (full ? ntk_fcn_pair_ok((long long)n1 * O, (long long)n2 * O, L, sym ? 1 : 0, h->num_cu, true)
+                          : L >= 2);
+  auto I = [&](size_t off) { return reinterpret_cast<int*>(h->ws + off); };
+  auto Gp = [&](int l) { return full ? F(h->off_G[l]) : F(h->off_gp[l & 1]); };
+  const size_t ge_ld = ((size_t)h->max_n1 + h->max_n2) * O;
+  auto Ge = [&](int l) { return I(h->off_ge) + l * ge_ld; };
+  int gparts[2] = {1, 1};   // parts of the row maxima of the layer above, per half
+  auto pair_weights = [&]() {
+    PairWeights pw{};
+    pw.count = std::max(0, L - 1);
+    for (int l = 1; l < L; ++l) {
+      pw.W[l - 1] = params[h->param_index[l]];
+      pw.out[l - 1] = F(h->off_Wt[l]);
+      pw.exps[l - 1] = I(h->off_we[l]);
+      pw.l1[l - 1] = F(h->off_l1[l]);
+      pw.stats[l - 1] = F(h->off_ws[l]);
+      pw.K[l - 1] = h->dims[l + 1];
+      pw.N[l - 1] = h->dims[l];
+    }
+    return pw;
+  };
+  // without a second stream the pair rows of the weights and the seed and the Grams share a launch
+  const bool prep = pair && !aux && !diag;
   auto transposes = [&](hipStream_t st) -> int {
+    if (pair) {
+      if (prep) return NTK_OK;
+      prof_begin(P, st, KC_TRANSPOSE);
+      hipError_t err = launch_pair_weights(st, pair_weights());
+      prof_end(P, st, KC_TRANSPOSE);
+      return err == hipSuccess ? NTK_OK : hip_fail(h, err, "weight pair rows");
+    }
     if (L < 2 || bwd_w) return NTK_OK;
     TransposeBatch tb{};
     tb.count = L - 1;
@@ -823,9 +926,42 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
   // alone in NTK_OUTPUT_LOGIT: the cotangent rows are then (n) instead of (n, o)): written by the
   // epilogue of the last forward layer, G[n, o, c] = WL[o, c] act'(z[n, c])
   const float* WL = params[h->param_index[L]] + (logit ? (size_t)h->opt_logit * h->dims[L] : 0);
+  // the readout cotangents of the samples [r0, r1) as pair rows
+  auto seed_pairs = [&](hipStream_t st, int r0, int r1) -> hipError_t {
+    const int l = L - 1, K = h->dims[L];
+    gparts[r0 ? 1 : 0] = 1;
+    return launch_pair_seed(st, WL, F(h->off_dphi[l]) + (size_t)r0 * K, (r1 - r0) * Oe, Oe, K,
+                            Gp(l) + (size_t)r0 * Oe * pair_stride(K), Ge(l) + (size_t)r0 * Oe,
+                            F(h->off_rmax[l & 1]) + (size_t)r0 * Oe);
+  };
   // one layer of the cotangent backward for the samples [r0, r1)
   auto bwd_layer = [&](hipStream_t st, int l, int r0, int r1) -> hipError_t {
     const size_t K = h->dims[l + 1], N = h->dims[l];
+    if (pair) {
+      const size_t row0 = (size_t)r0 * Oe;
+      PairBwd b{};
+      b.Kp = (int)pair_stride(K);
+      b.G = Gp(l) + row0 * b.Kp;
+      b.exps_in = Ge(l) + row0;
+      b.rmax_in = F(h->off_rmax[l & 1]) + row0;
+      b.rmax_parts = gparts[r0 ? 1 : 0];
+      b.rmax_ld = (long long)M * Oe;
+      b.W = F(h->off_Wt[l]);
+      b.wexps = I(h->off_we[l]);
+      b.l1 = F(h->off_l1[l]);
+      b.l1_parts = (int)(N + kPairStrip - 1) / kPairStrip;
+      b.act_exp = h->layers[l - 1].act == NTK_ACT_ERF ? 1 : 0;   // |erf'| <= 2 / sqrt(pi)
+      b.dphi = F(h->off_dphi[l - 1]) + (size_t)r0 * N;
+      b.R = (r1 - r0) * Oe;
+      b.N = (int)N;
+      b.fO = FastDiv((uint32_t)Oe);
+      b.out = full || l > 1 ? Gp(l - 1) + row0 * pair_stride(N) : nullptr;
+      b.out32 = full ? nullptr : F(h->off_G[l - 1]) + row0 * N;
+      b.exps_out = Ge(l - 1) + row0;
+      b.rmax_out = F(h->off_rmax[(l - 1) & 1]) + row0;
+      gparts[r0 ? 1 : 0] = pair_bwd_parts(b.R, b.N, h->num_cu);
+      return launch_pair_bwd(st, b, h->num_cu);
+    }
     if (bwd_w && gram_in_bwd && l == L - 1)
       return launch_dense_bwd_w_gram(st, F(h->off_G[l]) + (size_t)r0 * Oe * K, params[h->param_index[l]],
                                      F(h->off_dphi[l - 1]) + (size_t)r0 * N, (r1 - r0) * Oe, N, K, Oe,
@@ -856,8 +992,8 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
     min_tiles = min_tiles < 0 ? t : std::min(min_tiles, t);
   }
   const bool split = aux && L >= 2 && M >= 2 && min_tiles >= 2LL * h->num_cu;
-  bwd_w = L >= 2;
-  for (int l = 1; l < L; ++l)
+  bwd_w = L >= 2 && !pair;
+  for (int l = 1; l < L && !pair; ++l)
     bwd_w = bwd_w && dense_bwd_w_ok(F(h->off_G[l]), params[h->param_index[l]], (long long)M * Oe, h->dims[l],
                                       h->dims[l + 1]);
   gram_in_bwd = bwd_w && !aux && !jc && !diag;
@@ -880,7 +1016,7 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
         const float* in = (l == 0 ? h0 : F(h->off_h[l])) + (size_t)r0 * h->dims[l];
         const long long cap = h->fpart_capacity / 2;
         double* part = h->fpart_capacity ? reinterpret_cast<double*>(h->ws + h->off_fpart) + half * cap : nullptr;
-        const bool last = l == L - 1;
+        const bool last = l == L - 1 && !(pair && full);
         e = launch_dense_fwd(half ? aux : s, in, W, b, r1 - r0, h->dims[l + 1], h->dims[l], h->layers[l].act,
                              F(h->off_h[l + 1]) + (size_t)r0 * h->dims[l + 1],
                              F(h->off_dphi[l]) + (size_t)r0 * h->dims[l + 1], part, part ? cap : 0,
@@ -890,6 +1026,11 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
     }
     if ((e = hipEventRecord(h->ev_fwd, aux)) != hipSuccess) return hip_fail(h, e, "stream event");
     if ((e = hipStreamWaitEvent(s, h->ev_tr, 0)) != hipSuccess) return hip_fail(h, e, "stream join");
+    if (pair) {
+      e = seed_pairs(s, 0, MA);
+      if (e == hipSuccess) e = seed_pairs(aux, MA, M);
+      if (e != hipSuccess) return hip_fail(h, e, "readout cotangents");
+    }
     for (int l = L - 1; l >= 1; --l) {
       e = bwd_layer(s, l, 0, MA);
       if (e == hipSuccess) e = bwd_layer(aux, l, MA, M);
@@ -909,12 +1050,12 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
     if (aux && (e = hipEventRecord(h->ev_tr, sa)) != hipSuccess) return hip_fail(h, e, "stream event");
     // 1. forward pass keeping the layer inputs, and the readout cotangents in the last layer's
     //    epilogue
-    if ((rc = L >= 1 ? fcn_forward(h, params, X1, n1, X2, n2, sym, &h0, WL, Oe, F(h->off_G[L - 1]))
+    if ((rc = L >= 1 && !(pair && full) ? fcn_forward(h, params, X1, n1, X2, n2, sym, &h0, WL, Oe, F(h->off_G[L - 1]))
                      : fcn_forward(h, params, X1, n1, X2, n2, sym, &h0)) != NTK_OK)
       return rc;
     // 2. the Grams, on the second stream while the backward runs (or in the first backward
     //    layer's launch)
-    if (!jc && !gram_in_bwd) {
+    if (!jc && !gram_in_bwd && !prep) {
       if (aux && (rc = fork(h->ev_fwd, s, sa)) != NTK_OK) return rc;
       if ((rc = grams(sa)) != NTK_OK) return rc;
       if (aux && (e = hipEventRecord(h->ev_gram, sa)) != hipSuccess) return hip_fail(h, e, "stream event");
@@ -922,6 +1063,16 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
     // 3. the cotangents of every hidden pre-activation
     if (aux && (e = hipStreamWaitEvent(s, h->ev_tr, 0)) != hipSuccess) return hip_fail(h, e, "stream join");
     if (L >= 1) {
+      if (pair) {
+        prof_begin(P, s, KC_BWD_SEED);
+        if (prep)
+          e = launch_pair_prep(s, pair_weights(), WL, F(h->off_dphi[L - 1]), M * Oe, Oe, h->dims[L], Gp(L - 1),
+                               Ge(L - 1), F(h->off_rmax[(L - 1) & 1]), gram_batch(), n1, n2, h->num_cu);
+        else
+          e = seed_pairs(s, 0, M);
+        prof_end(P, s, KC_BWD_SEED);
+        if (e != hipSuccess) return hip_fail(h, e, "readout cotangents");
+      }
       if (split && (rc = fork(h->ev_seed, s, aux)) != NTK_OK) return rc;
       prof_begin(P, s, KC_DENSE_BWD);
       for (int l = L - 1; l >= 1; --l) {
@@ -1010,6 +1161,15 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
     c.G2[l] = G2(l);
     c.gram[l] = F(h->off_gram[l]);
     c.K[l] = h->dims[l + 1];
+    if (pair) {
+      c.K[l] = (int)pair_stride(h->dims[l + 1]);
+      c.G2[l] = sym ? c.G1[l] : c.G1[l] + (size_t)n1 * O * c.K[l];
+    }
+  }
+  if (pair) {
+    c.exps = Ge(0);
+    c.exps_ld = (long long)ge_ld;
+    c.exps_off = sym ? 0 : (long long)n1 * O;
   }
   c.gram_readout = F(h->off_gram[L]);
   c.readout_scale = 1.f;
