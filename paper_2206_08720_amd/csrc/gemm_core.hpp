@@ -399,11 +399,16 @@ __device__ __forceinline__ int frag_row(int v, int lane) { return 8 * (v >> 2) +
 // images of each image (null dphi: the identity).  A fragment that lies inside R and inside
 // one cotangent image (no multiple of D in (r0, r0 + 31]) maps to 32 consecutive rows of dphi,
 // so its row arithmetic is done once and an element costs an offset, a load, a multiply and a
-// store (32-bit byte offsets: N < 2^25); other fragments take the per-element form.
+// store (32-bit byte offsets: N < 2^25); other fragments take the per-element form.  With gmax,
+// gmax[r / D] (the cotangent image) also takes the largest magnitude stored, by integer maxima of
+// the bits (order-free, so deterministic).
+__device__ __forceinline__ void gmax_update(float* gmax, float m) {
+  atomicMax(reinterpret_cast<unsigned*>(gmax), __float_as_uint(m));
+}
 template <class Cfg>
 __device__ __forceinline__ void store_pixel_rows(f32x16 (&acc)[Cfg::FM][Cfg::FN], int m0, int n0,
                                                  const float* __restrict__ dphi, float* __restrict__ out, int R,
-                                                 int N, FastDiv fOD, FastDiv fD) {
+                                                 int N, FastDiv fOD, FastDiv fD, float* __restrict__ gmax) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm0 = (wave / Cfg::WAVES_N) * Cfg::WM;
@@ -418,6 +423,7 @@ __device__ __forceinline__ void store_pixel_rows(f32x16 (&acc)[Cfg::FM][Cfg::FN]
       const int img = (int)fOD.div(r0);
       float* ob = out + (long long)r0 * N;
       const float* db = dphi ? dphi + ((long long)img * D + (r0 - t0 * D)) * N : nullptr;
+      float mx = 0.f;
 #pragma unroll
       for (int fn = 0; fn < Cfg::FN; ++fn) {
         const int c = n0 + wn0 + fn * 32 + (lane & 31);
@@ -427,25 +433,48 @@ __device__ __forceinline__ void store_pixel_rows(f32x16 (&acc)[Cfg::FM][Cfg::FN]
 #pragma unroll
           for (int v = 0; v < 16; ++v) d[v] = at_bytes(db, (uint32_t)(frag_row(v, lane) * N + c) * 4u);
 #pragma unroll
-          for (int v = 0; v < 16; ++v) at_bytes(ob, (uint32_t)(frag_row(v, lane) * N + c) * 4u) = acc[fm][fn][v] * d[v];
+          for (int v = 0; v < 16; ++v) {
+            const float x = acc[fm][fn][v] * d[v];
+            at_bytes(ob, (uint32_t)(frag_row(v, lane) * N + c) * 4u) = x;
+            mx = fmaxf(mx, fabsf(x));
+          }
         } else {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) at_bytes(ob, (uint32_t)(frag_row(v, lane) * N + c) * 4u) = acc[fm][fn][v];
+          for (int v = 0; v < 16; ++v) {
+            at_bytes(ob, (uint32_t)(frag_row(v, lane) * N + c) * 4u) = acc[fm][fn][v];
+            mx = fmaxf(mx, fabsf(acc[fm][fn][v]));
+          }
         }
+      }
+      if (gmax) {
+#pragma unroll
+        for (int q = 32; q; q >>= 1) mx = fmaxf(mx, __shfl_xor(mx, q));
+        if (lane == 0) gmax_update(gmax + t0, mx);
       }
     } else {
 #pragma unroll
-      for (int fn = 0; fn < Cfg::FN; ++fn)
+      for (int v = 0; v < 16; ++v) {
+        const int r = r0 + frag_row(v, lane);
+        const int rc = min(r, R - 1);
+        const int img = (int)fOD.div(rc), t = (int)fD.div(rc);
+        const int p = rc - t * D;
+        float mx = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int r = r0 + frag_row(v, lane), c = n0 + wn0 + fn * 32 + (lane & 31);
+        for (int fn = 0; fn < Cfg::FN; ++fn) {
+          const int c = n0 + wn0 + fn * 32 + (lane & 31);
           if (r < R && c < N) {
-            const int img = (int)fOD.div(r);
-            const int p = r - (int)fD.div(r) * D;
             const float d = dphi ? dphi[((long long)img * D + p) * N + c] : 1.f;
-            out[(long long)r * N + c] = acc[fm][fn][v] * d;
+            const float x = acc[fm][fn][v] * d;
+            out[(long long)r * N + c] = x;
+            mx = fmaxf(mx, fabsf(x));
           }
         }
+        if (gmax) {   // the 32 lanes of a half-wave hold one row
+#pragma unroll
+          for (int q = 16; q; q >>= 1) mx = fmaxf(mx, __shfl_xor(mx, q));
+          if ((lane & 31) == 0 && r < R) gmax_update(gmax + t, mx);
+        }
+      }
     }
   }
 }

@@ -20,6 +20,7 @@
 
 #include "gemm_core.hpp"
 #include "launch_conv.hpp"
+#include "pair_core.hpp"
 
 namespace ntk {
 
@@ -34,6 +35,13 @@ using CfgConvBwd = TileCfg<256, 64, 32, 32, 64>;
 using CfgConvWg = CfgConv;
 using CfgConvWgSmall = TileCfg<64, 64, 32, 32, 32>;   // one-output rows (O C <= 64): 4 waves
 constexpr int kConvBwdStages = 2, kConvWgStages = 2;
+// the same on pairs (three f16 MFMAs): 64-wide wave tiles, so that a fragment is split into pairs
+// and read from LDS for at least two of the other operand
+using CfgConvBwdPair = TileCfg<256, 64, 32, 64, 64>;       // 4 waves
+using CfgConvBwdPairSmall = TileCfg<128, 64, 32, 32, 64>;  // 4 waves
+using CfgConvWgPair = TileCfg<128, 128, 32, 64, 64>;       // 4 waves
+using CfgConvWgPairN = TileCfg<128, 64, 32, 64, 32>;
+using CfgConvWgPairM = TileCfg<64, 64, 32, 32, 32>;
 // Small images (few output rows): below kConvFewTiles tiles of the shapes above, the backward
 // takes 128x64 tiles (8 waves of 32x32) and the fp64 forward 32x32 tiles (4 waves of 16x16), so
 // that the launch still spreads over the compute units.
@@ -889,6 +897,119 @@ hipError_t launch_conv_flip_batch(hipStream_t s, const FlipBatch& b) {
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------------------------ pair preparation
+// One wave per row of a flipped kernel (pair rows), then workgroups that zero the maxima, one
+// workgroup per output o for the seed's bound, and one for the factors of the block-diagonal
+// layers.
+__global__ void __launch_bounds__(256) k_conv_prep(ConvPrep p, ConvFactors f, int nrow_blocks, int nzero_blocks) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int bx = blockIdx.x;
+  if (bx < nrow_blocks) {
+    int row = bx * 4 + wave, z = 0;
+    while (z < p.count && row >= p.N[z]) row -= p.N[z++];
+    if (z >= p.count) return;   // the whole wave
+    const int K = p.K[z], Kp = (int)pair_stride(K);
+    const float* __restrict__ x = p.Kt[z] + (long long)row * K;
+    float m = 0.f;
+    for (int k = lane; k < K; k += 64) m = fmaxf(m, fabsf(x[k]));
+#pragma unroll
+    for (int q = 32; q; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
+    const int e = pair_row_exp(m);
+    if (lane == 0) p.kexps[z][row] = e;
+    for (int g = lane; g < Kp / 8; g += 64) {
+      f16x8 hi, lo;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = 8 * g + j;
+        _Float16 a, b;
+        pair_split(k < K ? ldexpf(x[min(k, K - 1)], -e) : 0.f, a, b);
+        hi[j] = a;
+        lo[j] = b;
+      }
+      f16x8* o = reinterpret_cast<f16x8*>(p.Kp[z] + (long long)row * Kp + 8 * g);
+      o[0] = hi;
+      o[1] = lo;
+    }
+    return;
+  }
+  bx -= nrow_blocks;
+  if (bx < nzero_blocks) {
+    for (long long i = bx * 256LL + threadIdx.x; i < p.nzero; i += (long long)nzero_blocks * 256) p.zero[i] = 0.f;
+    return;
+  }
+  bx -= nzero_blocks;
+  if (bx < p.O) {
+    float m = 0.f;
+    for (int c = lane; c < p.C; c += 64) m = fmaxf(m, fabsf(p.Wd[(long long)bx * p.C + c]));
+#pragma unroll
+    for (int q = 32; q; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
+    for (int i = threadIdx.x; i < p.M; i += 256) p.gseed[(long long)i * p.O + bx] = m * p.seed_scale;
+    return;
+  }
+  __shared__ float red[4];
+  float run = 1.f;
+  for (int i = 0; i < f.count; ++i) {
+    float m = f.w[i] ? 0.f : 1.f;
+    if (f.w[i])
+      for (int c = threadIdx.x; c < f.ch[i]; c += 256) {
+        float a = 0.f;
+        for (int t = 0; t < f.taps[i]; ++t) a += fabsf(f.w[i][(long long)t * f.ch[i] + c]);
+        m = fmaxf(m, a);
+      }
+#pragma unroll
+    for (int q = 32; q; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
+    if (lane == 0) red[wave] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])) * f.grow[i];
+    run = (f.chain[i] ? run : 1.f) * m;
+    if (threadIdx.x == 0) f.fac[i] = run;
+    __syncthreads();
+  }
+}
+
+hipError_t launch_conv_prep(hipStream_t s, const ConvPrep& p, const ConvFactors& f) {
+  long long rows = 0;
+  for (int z = 0; z < p.count; ++z) rows += p.N[z];
+  const int nr = cdiv(rows, 4), nz = (int)std::min<long long>((p.nzero + 1023) / 1024, 256);
+  k_conv_prep<<<dim3(nr + nz + p.O + (f.count ? 1 : 0)), dim3(256), 0, s>>>(p, f, nr, nz);
+  return hipGetLastError();
+}
+
+// Largest magnitude of each image of several layer inputs: workgroup (image, input).
+template <bool VEC>
+__global__ void __launch_bounds__(256) k_conv_max(ConvMax b) {
+  __shared__ float red[4];
+  const int z = blockIdx.y;
+  const int n = b.plane[z];
+  const float* __restrict__ x = b.x[z] + (long long)blockIdx.x * n;
+  float m = 0.f;
+  if (VEC) {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n / 4; i += 256) {
+      const f32x4 v = reinterpret_cast<const f32x4*>(x)[i];
+      m = fmaxf(m, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+    }
+  } else {
+    for (int i = threadIdx.x; i < n; i += 256) m = fmaxf(m, fabsf(x[i]));
+  }
+#pragma unroll
+  for (int q = 32; q; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) b.out[z][blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+}
+
+hipError_t launch_conv_max(hipStream_t s, const ConvMax& m) {
+  if (m.count <= 0 || m.M <= 0) return hipSuccess;
+  bool v = true;
+  for (int z = 0; z < m.count; ++z) v = v && m.plane[z] % 4 == 0 && aligned16(m.x[z]);
+  if (v)
+    k_conv_max<true><<<dim3(m.M, m.count), dim3(256), 0, s>>>(m);
+  else
+    k_conv_max<false><<<dim3(m.M, m.count), dim3(256), 0, s>>>(m);
+  return hipGetLastError();
+}
+
 // J[(s*O + o), off + c*KCs + js] = acc[r = o*C + c, k] for the GEMM columns k of KC = F Cin
 // (F taps of Cin computed input channels), stored as the columns js of KCs = F Cst (the first Cst
 // channels of each tap: a layer input padded from Cst to Cin channels has zero columns that are
@@ -946,14 +1067,14 @@ __device__ __forceinline__ void conv_wgrad_store(f32x16 (&acc)[Cfg::FM][Cfg::FN]
 template <class Cfg, bool VEC>
 __global__ void __launch_bounds__(Cfg::THREADS)
 k_conv_bwd(LoadPatchesKInnerT<VEC> la, LoadKInnerT<VEC> lb, const float* __restrict__ dphi, int R,
-           int N, FastDiv fOD, FastDiv fD, float* __restrict__ out, int tiles_n) {
+           int N, FastDiv fOD, FastDiv fD, float* __restrict__ out, int tiles_n, float* __restrict__ gmax) {
   extern __shared__ float smem[];
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
   f32x16 acc[Cfg::FM][Cfg::FN];
   zero_acc<Cfg>(acc);
   gemm_mainloop<Cfg>(la, lb, m0, n0, 0, la.K, smem, acc);
-  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD);
+  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, gmax);
 }
 
 // direct-to-LDS form (Cg % 32 == 0): the cotangent patches gathered by the DMA, NS LDS stages
@@ -961,19 +1082,213 @@ template <class Cfg, int NS>
 __global__ void __launch_bounds__(Cfg::THREADS)
 k_conv_bwd_dma(DmaPatches<Cfg::BM, Cfg::WAVES> pa, DmaRowMajor<Cfg::BN, Cfg::WAVES> pb, int K,
                const float* __restrict__ dphi, int R, int N, FastDiv fOD, FastDiv fD, float* __restrict__ out,
-               int tiles_n) {
+               int tiles_n, float* __restrict__ gmax) {
   extern __shared__ float smem[];
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
   f32x16 acc[Cfg::FM][Cfg::FN];
   zero_acc<Cfg>(acc);
   gemm_mainloop_dma_ops<Cfg, NS>(pa, pb, m0, n0, 0, K, smem, acc);
-  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD);
+  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, gmax);
+}
+
+// The same on pairs.  A tile's rows are a run of BM pixels of the stacked cotangent images, and the
+// pixels its nine taps read are that run widened by W + 1 on both sides, so the workgroup keeps
+// 32 channels of those BM + 2 (W + 1) pixels in LDS as pairs: each cotangent is read from memory
+// and split once per tile (with the exponent of its image) instead of once per tap, the nine taps
+// are row shifts of the LDS reads, and a tap outside the image reads a row of zeros.  The kernel
+// (pair rows) streams through two LDS stages, 32 k at a time.  1280 images of 32 x 32 x 64:
+// 788 us with the fp32 MFMA, 408 us with the cotangents gathered and split per tap (VALU beside
+// the MFMAs), this form 327 us.
+constexpr int kHaloMaxW = 63;
+template <class Cfg>
+constexpr int halo_rows(int W) {
+  return Cfg::BM + 2 * (W + 1);
+}
+// tasks (8 channels of a pixel) per thread of the staging: widest images
+template <class Cfg>
+constexpr int halo_tasks() {
+  return (halo_rows<Cfg>(kHaloMaxW) * 4 + Cfg::THREADS - 1) / Cfg::THREADS;
+}
+template <class Cfg>
+static int halo_smem_bytes(int W) {
+  return ((halo_rows<Cfg>(W) + 1) * 32 + 2 * Cfg::BN * 32) * 4;
+}
+template <class Cfg>
+__global__ void __launch_bounds__(Cfg::THREADS, 2 * Cfg::THREADS / 256)
+k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, DmaRowMajor<Cfg::BN, Cfg::WAVES> pb,
+                ConvPairBwd pr, const float* __restrict__ dphi, int R, int N, FastDiv fOD, FastDiv fD,
+                float* __restrict__ out, int tiles_n, float* __restrict__ gmax) {
+  extern __shared__ f32x4 halo_lds[];   // 16-byte aligned
+  float* smem = reinterpret_cast<float*>(halo_lds);
+  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
+  const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm0 = (wave / Cfg::WAVES_N) * Cfg::WM, wn0 = (wave % Cfg::WAVES_N) * Cfg::WN;
+  const int lr = lane & 31, lc = (lane >> 5) * 2;
+  const float fac = pr.fac ? *pr.fac : 1.f;
+  const int HR = halo_rows<Cfg>(W);
+  float* Bs = smem + (HR + 1) * 32;
+  constexpr int NT = halo_tasks<Cfg>();
+  const int ncb = Cg / 32, nk = 9 * ncb;
+  // staging: task t = row t / 4 of the widened run, channels 8 (t % 4) .. + 7 of the block.  Rows
+  // outside the batch are read from a clamped address; no tap inside an image reaches them.
+  const float* src[NT];
+  float sf[NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    const int t = threadIdx.x + i * Cfg::THREADS;
+    const int q = min(max(m0 - (W + 1) + min(t >> 2, HR - 1), 0), R - 1);
+    src[i] = G + (long long)q * Cg + 8 * (t & 3);
+    sf[i] = pair_factor(pair_row_exp(pr.gmax[fD.div(q)] * fac));
+  }
+  f32x4 st[NT][2];
+  auto fetch = [&](int cb) {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      st[i][0] = *reinterpret_cast<const f32x4*>(src[i] + cb * 32);
+      st[i][1] = *reinterpret_cast<const f32x4*>(src[i] + cb * 32 + 4);
+    }
+  };
+  auto stage = [&]() {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int t = threadIdx.x + i * Cfg::THREADS, row = t >> 2, c = 2 * (t & 3);
+      if (row < HR) {
+        f16x8 hi, lo;
+        pair_split8(st[i][0], st[i][1], sf[i], hi, lo);
+        *reinterpret_cast<f16x8*>(&smem[row * 32 + (DmaTile<32>::swz(row, c) << 2)]) = hi;
+        *reinterpret_cast<f16x8*>(&smem[row * 32 + (DmaTile<32>::swz(row, c + 1) << 2)]) = lo;
+      }
+    }
+  };
+  // this lane's rows: the row of the pixel itself in LDS and the taps outside its image
+  int rb[Cfg::FM];
+  unsigned om[Cfg::FM];
+#pragma unroll
+  for (int i = 0; i < Cfg::FM; ++i) {
+    const int l = wm0 + i * 32 + lr, r = m0 + l;
+    const int rc = min(r, R - 1), p = rc - (int)fD.div(rc) * (int)fD.d;
+    const int y = (int)fW.div(p), x = p - y * W;
+    rb[i] = l + W + 1;
+    unsigned m = 0;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int ky = y + t / 3 - 1, kx = x + t % 3 - 1;
+      m |= ((unsigned)ky < (unsigned)H && (unsigned)kx < (unsigned)W) ? 0u : (1u << t);
+    }
+    om[i] = r < R ? m : 0x1FFu;
+  }
+  PairAcc<Cfg::FM, Cfg::FN, true> acc;
+  zero_pair_acc(acc);
+  pb.prepare(n0, wave, lane);
+  if (threadIdx.x < 32) smem[HR * 32 + threadIdx.x] = 0.f;
+  pb.template issue<Cfg::WAVES>(0, Bs, wave, lane);
+  fetch(0);
+  stage();
+  wait_vmcnt_lgkm0<0>();
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  f16x8 a[2][2], b[2][Cfg::FN][2];
+  int row[Cfg::FM];
+  auto rows_of = [&](int tap) {
+    const int shift = (tap / 3 - 1) * W + tap % 3 - 1;
+#pragma unroll
+    for (int i = 0; i < Cfg::FM; ++i) row[i] = ((om[i] >> tap) & 1u) ? HR : rb[i] + shift;
+  };
+  auto load_a = [&](int half, int i, f16x8 (&x)[2]) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+      x[p] = *reinterpret_cast<const f16x8*>(&smem[row[i] * 32 + (DmaTile<32>::swz(row[i], half * 4 + lc + p) << 2)]);
+  };
+  auto load_b = [&](const float* bs, int half, f16x8 (&x)[Cfg::FN][2]) {
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int r = wn0 + j * 32 + lr;
+        x[j][p] = *reinterpret_cast<const f16x8*>(&bs[r * 32 + (DmaTile<32>::swz(r, half * 4 + lc + p) << 2)]);
+      }
+  };
+  auto mma = [&](int i, const f16x8 (&x)[2], const f16x8 (&y)[Cfg::FN][2]) {
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j)
+      acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], y[j][0], acc.v[i][j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j)
+      acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y[j][1], acc.v[i][j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j)
+      acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y[j][0], acc.v[i][j], 0, 0, 0);
+  };
+  rows_of(0);
+  load_b(Bs, 0, b[0]);
+  load_a(0, 0, a[0]);
+  int tap = 0, cb = 0;
+  auto step = [&](int kt, auto stage_tag) {
+    constexpr int S = decltype(stage_tag)::value;
+    const float* bs = Bs + S * Cfg::BN * 32;
+    int tap1 = tap + 1, cb1 = cb;
+    if (tap1 == 9) {
+      tap1 = 0;
+      ++cb1;
+    }
+    if (kt + 1 < nk) pb.template issue<Cfg::WAVES>(tap1 * Cg + cb1 * 32, Bs + (S ^ 1) * Cfg::BN * 32, wave, lane);
+    if (tap == 0 && cb + 1 < ncb) fetch(cb + 1);
+#pragma unroll
+    for (int q = 0; q + 1 < 2 * Cfg::FM; ++q) {
+      const int half = q / Cfg::FM, next = (q + 1) / Cfg::FM;
+      if (next != half) load_b(bs, next, b[1]);
+      load_a(next, (q + 1) % Cfg::FM, a[(q + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(q % Cfg::FM, a[q & 1], b[half]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (kt + 1 < nk) {
+      if (tap1 == 0) {   // every wave has read the block's last fragments: the next block's pixels
+        wait_vmcnt_lgkm0<0>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        stage();
+      }
+      wait_vmcnt_lgkm0<0>();
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      rows_of(tap1);
+      load_b(Bs + (S ^ 1) * Cfg::BN * 32, 0, b[0]);
+      load_a(0, 0, a[0]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    mma(Cfg::FM - 1, a[1], b[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    tap = tap1;
+    cb = cb1;
+  };
+  int kb = 0;
+  for (; kb + 2 <= nk; kb += 2) {
+    step(kb, std::integral_constant<int, 0>{});
+    step(kb + 1, std::integral_constant<int, 1>{});
+  }
+  if (kb < nk) step(kb, std::integral_constant<int, 0>{});
+#pragma unroll
+  for (int i = 0; i < Cfg::FM; ++i) {
+    const int r0 = min(m0 + wm0 + i * 32, R - 1), t0 = (int)fD.div(r0);
+    const bool one = (int)fD.div(min(r0 + 31, R - 1)) == t0;
+    const int e0 = pair_row_exp(pr.gmax[t0] * fac);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int e = one ? e0 : pair_row_exp(pr.gmax[fD.div(min(r0 + frag_row(v, lane), R - 1))] * fac);
+#pragma unroll
+      for (int j = 0; j < Cfg::FN; ++j)
+        acc.v[i][j][v] = ldexpf(acc.v[i][j][v], e + pr.kexps[min(n0 + wn0 + j * 32 + lr, N - 1)]);
+    }
+  }
+  store_pixel_rows<Cfg>(acc.v, m0, n0, dphi, out, R, N, fOD, fD, gmax);
 }
 
 template <bool VEC>
 static hipError_t conv_bwd_vec(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
-                               const float* Kt, int Cin, const float* dphi, float* out) {
+                               const float* Kt, int Cin, const float* dphi, float* out, float* gmax) {
   using Cfg = CfgConv;
   using LA = LoadPatchesKInnerT<VEC>;
   using LB = LoadKInnerT<VEC>;
@@ -986,13 +1301,13 @@ static hipError_t conv_bwd_vec(hipStream_t s, const float* G, int images, int O,
   hipError_t e = set_smem<Cfg, LA, LB>((const void*)k_conv_bwd<Cfg, VEC>);
   if (e != hipSuccess) return e;
   k_conv_bwd<Cfg, VEC><<<dim3(tm * tn), dim3(Cfg::THREADS), gemm_smem_bytes<Cfg, LA, LB>(), s>>>(
-      la, lb, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn);
+      la, lb, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn, gmax);
   return hipGetLastError();
 }
 
 template <class Cfg>
 static hipError_t conv_bwd_dma_cfg(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
-                                   const float* Kt, int Cin, const float* dphi, float* out) {
+                                   const float* Kt, int Cin, const float* dphi, float* out, float* gmax) {
   constexpr int NS = kConvBwdStages;
   const int D = H * W, Kd = 9 * Cg;
   int R;
@@ -1005,20 +1320,50 @@ static hipError_t conv_bwd_dma_cfg(hipStream_t s, const float* G, int images, in
                                      hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess) return e;
   k_conv_bwd_dma<Cfg, NS><<<dim3(tm * tn), dim3(Cfg::THREADS), bytes, s>>>(
-      pa, pb, Kd, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn);
+      pa, pb, Kd, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn, gmax);
   return hipGetLastError();
 }
 
+template <class Cfg>
+static hipError_t conv_bwd_pair_cfg(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
+                                    const ConvPairBwd& pr, int Cin, const float* dphi, float* out, float* gmax) {
+  const int D = H * W;
+  int R;
+  if (!to_int((long long)images * O * D, R)) return hipErrorInvalidValue;
+  const int tn = cdiv(Cin, Cfg::BN), tm = cdiv(R, Cfg::BM);
+  DmaRowMajor<Cfg::BN, Cfg::WAVES> pb{pr.Kp, 9 * Cg, Cin};
+  hipError_t e = hipFuncSetAttribute((const void*)k_conv_bwd_pair<Cfg>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     halo_smem_bytes<Cfg>(kHaloMaxW));
+  if (e != hipSuccess) return e;
+  k_conv_bwd_pair<Cfg><<<dim3(tm * tn), dim3(Cfg::THREADS), halo_smem_bytes<Cfg>(W), s>>>(
+      G, H, W, Cg, FastDiv((uint32_t)W), pb, pr, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn,
+      gmax);
+  return hipGetLastError();
+}
+
+// whether the cotangent backward of this layer takes the pair form
+bool conv_bwd_pair_ok(const float* G, const float* Kp, int W, int Cg) {
+  return Cg % 32 == 0 && W <= kHaloMaxW && aligned16(G) && aligned16(Kp) && dma_span_ok(9LL * Cg, 9LL * Cg, 256);
+}
+
 hipError_t launch_conv_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
-                           const float* Kt, int Cin, const float* dphi, float* out) {
+                           const float* Kt, int Cin, const float* dphi, float* out, const ConvPairBwd* pair,
+                           float* gmax) {
+  if (pair && conv_bwd_pair_ok(G, pair->Kp, W, Cg)) {
+    const long long tiles =
+        (long long)cdiv((long long)images * O * H * W, CfgConvBwdPair::BM) * cdiv(Cin, CfgConvBwdPair::BN);
+    if (tiles < kConvFewTiles)
+      return conv_bwd_pair_cfg<CfgConvBwdPairSmall>(s, G, images, O, H, W, Cg, *pair, Cin, dphi, out, gmax);
+    return conv_bwd_pair_cfg<CfgConvBwdPair>(s, G, images, O, H, W, Cg, *pair, Cin, dphi, out, gmax);
+  }
   if (conv_dma_ok(G, (long long)images * O * H * W * Cg, W, Cg, Kt)) {
     const long long tiles = (long long)cdiv((long long)images * O * H * W, CfgConvBwd::BM) * cdiv(Cin, CfgConvBwd::BN);
-    if (tiles < kConvFewTiles) return conv_bwd_dma_cfg<CfgConv>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out);
-    return conv_bwd_dma_cfg<CfgConvBwd>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out);
+    if (tiles < kConvFewTiles) return conv_bwd_dma_cfg<CfgConv>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, gmax);
+    return conv_bwd_dma_cfg<CfgConvBwd>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, gmax);
   }
   if (Cg % 4 == 0 && aligned16(G) && vec_ok(Kt, 9 * Cg, 9 * Cg))
-    return conv_bwd_vec<true>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out);
-  return conv_bwd_vec<false>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out);
+    return conv_bwd_vec<true>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, gmax);
+  return conv_bwd_vec<false>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, gmax);
 }
 
 // ------------------------------------------------------------------------------ weight-space cotangent
@@ -1127,6 +1472,197 @@ k_conv_wgrad_dma(const float* __restrict__ G, const float* __restrict__ h, int O
   conv_wgrad_store<Cfg>(acc, m0, n0, s, O, fC, KC, fCin, Cst, J, ldJ, off);
 }
 
+// The same on pairs.  Both operands are K-outer in memory (4 consecutive rows at one pixel per 16
+// bytes), so a thread loads 4 rows x 8 pixels, splits them with the row's exponent (the cotangent
+// image (s, o), or the sample's input) and writes them as pair rows [row][32 pixels] into LDS:
+// each value is split once per tile, and the waves read whole MFMA operands (16 bytes) instead of
+// eight floats each.  The next K tile's loads are in flight during a tile's MFMAs; two LDS stages.
+// 64 -> 64 channels, 128 x 10 cotangent images of 32 x 32: 555 us with the fp32 MFMA, 415 us with
+// every wave splitting its own fragments, this form 384 us.
+// Position of 16-byte chunk c of row r: eight consecutive rows (a fragment read) and every fourth
+// row (the writes of eight threads) both fall in eight distinct bank groups.
+__device__ __forceinline__ int wg_swz(int r, int c) { return c ^ ((r >> 2) & 7) ^ (((r >> 1) & 1) << 2); }
+
+template <class Cfg, bool PW, bool AL>
+__global__ void __launch_bounds__(Cfg::THREADS, 2 * Cfg::THREADS / 256)
+k_conv_wgrad_pair(const float* __restrict__ G, const float* __restrict__ h, ConvPairWgrad pr, int O, int H, int W, int C,
+                  int Cin, FastDiv fC, FastDiv fW, FastDiv fCin, int Cst, float* __restrict__ J, long long ldJ,
+                  long long off, int tiles_m, int tiles_n, int samples) {
+  static_assert(Cfg::BM + Cfg::BN <= Cfg::THREADS, "one staging task per thread");
+  extern __shared__ f32x4 wg_lds[];   // 16-byte aligned
+  float* smem = reinterpret_cast<float*>(wg_lds);
+  constexpr int AF = Cfg::BM * 32, STAGE = (Cfg::BM + Cfg::BN) * 32;
+  int s, t;
+  if (!xcd_sample_tile(blockIdx.x, tiles_m * tiles_n, samples, s, t)) return;
+  const int D = H * W, nk = (D + 31) / 32;
+  const int KC = PW ? Cin : 9 * Cin;
+  const int tm = t / tiles_n, tn = t - tm * tiles_n;
+  const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm0 = (wave / Cfg::WAVES_N) * Cfg::WM, wn0 = (wave % Cfg::WAVES_N) * Cfg::WN;
+  const int lr = lane & 31, lc = (lane >> 5) * 2;
+  const float fac = pr.fac ? *pr.fac : 1.f;
+  auto row_exp = [&](int r) {
+    const int o = (int)fC.div(min(r, O * C - 1));
+    return pair_row_exp(pr.gmax ? pr.gmax[s * O + o] * fac : pr.gconst);
+  };
+  const int eh = pair_row_exp(pr.hmax[s]);
+  // staging task of this thread: 4 rows (quad q) x 8 pixels (group g) of operand A (the first BM
+  // threads) or B.  Byte offsets through a buffer resource that starts W + 1 pixels before the
+  // sample for the patches; a pixel outside the sample or the image takes an offset past its end,
+  // which reads zeros.
+  const bool is_b = threadIdx.x >= Cfg::BM;
+  const int task = threadIdx.x - (is_b ? Cfg::BM : 0);
+  const int nq = (is_b ? Cfg::BN : Cfg::BM) / 4;
+  const int q = task % nq, g = task / nq;
+  const bool active = g < 4;
+  const int row = 4 * q;                       // in the tile
+  const int Ct = is_b ? Cin : C;               // floats between two pixels
+  int base, dy = 0, dx = 0;
+  bool in_rows;
+  float sf;
+  if (!is_b) {
+    const int r = m0 + row, rc = min(r, O * C - 4), o = (int)fC.div(rc);
+    base = (o * D * C + (rc - o * C)) * 4;
+    in_rows = r < O * C;
+    sf = pair_factor(row_exp(rc));
+  } else {
+    const int r = n0 + row, rc = min(r, KC - 4);
+    const int tap = PW ? 0 : (int)fCin.div(rc), ci = rc - tap * Cin;
+    if (!PW) {
+      const int kh = (tap * 11) >> 5;
+      dy = kh - 1;
+      dx = tap - 3 * kh - 1;
+    }
+    base = (((PW ? 0 : dy * W + dx + W + 1)) * Cin + ci) * 4;
+    in_rows = r < KC;
+    sf = pair_factor(eh);
+  }
+  const float* p0 = is_b ? h + (long long)s * D * Cin - (PW ? 0 : (long long)(W + 1) * Cin) : G + (long long)s * O * D * C;
+  const uint32_t span = (uint32_t)((is_b ? (long long)(D + (PW ? 0 : W + 1)) * Cin : (long long)O * D * C) * 4);
+  // the waves of the two operands differ: both resources are wave-uniform
+  const __amdgpu_buffer_rsrc_t rsrc = buffer_rsrc(
+      reinterpret_cast<const void*>(((uint64_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)p0 >> 32)) << 32) |
+                                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint64_t)p0)),
+      __builtin_amdgcn_readfirstlane((int)span));
+  f32x4 st[8];
+  auto fetch = [&](int kt) {
+    const int p = kt * 32 + 8 * g;
+    unsigned bad = (in_rows && active) ? 0u : 0xFFu;   // pixels of the group read as zeros
+    if (AL && !PW) {   // the K tile is a run of one image row
+      const int y = (int)fW.div(kt * 32), x = p - y * W;
+      if (is_b) {
+        if ((unsigned)(y + dy) >= (unsigned)H) bad = 0xFFu;
+        if (x == 0 && dx < 0) bad |= 1u;
+        if (x + 8 == W && dx > 0) bad |= 0x80u;
+      }
+    } else if (!AL) {
+      int y = 0, x = 0;
+      if (is_b && !PW) {
+        y = (int)fW.div(min(p, D - 1));
+        x = p - y * W;
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        bool ok = p + j < D;
+        if (is_b && !PW) {
+          ok = ok && (unsigned)(y + dy) < (unsigned)H && (unsigned)(x + dx) < (unsigned)W;
+          if (++x == W) {
+            x = 0;
+            ++y;
+          }
+        }
+        bad |= ok ? 0u : (1u << j);
+      }
+    }
+    const uint32_t voff = (uint32_t)base + (uint32_t)(p * Ct) * 4u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t o = ((bad >> j) & 1u) ? kDmaPastEnd : voff + (uint32_t)(j * Ct) * 4u;
+      st[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0));
+    }
+  };
+  auto stage = [&](float* dst) {
+    if (!active) return;
+    float* d = dst + (is_b ? AF : 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x4 x = {st[0][i], st[1][i], st[2][i], st[3][i]}, y = {st[4][i], st[5][i], st[6][i], st[7][i]};
+      f16x8 hi, lo;
+      pair_split8(x, y, sf, hi, lo);
+      const int r = row + i;
+      *reinterpret_cast<f16x8*>(&d[r * 32 + (wg_swz(r, 2 * g) << 2)]) = hi;
+      *reinterpret_cast<f16x8*>(&d[r * 32 + (wg_swz(r, 2 * g + 1) << 2)]) = lo;
+    }
+  };
+  f32x16 acc[Cfg::FM][Cfg::FN];
+  zero_acc<Cfg>(acc);
+  fetch(0);
+  stage(smem);
+  __syncthreads();
+  f16x8 a[2][2], b[2][Cfg::FN][2];
+  auto frag = [&](const float* st_, int r, int c) {
+    return *reinterpret_cast<const f16x8*>(&st_[r * 32 + (wg_swz(r, c) << 2)]);
+  };
+  auto load_a = [&](const float* st_, int half, int i, f16x8 (&x)[2]) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) x[p] = frag(st_, wm0 + i * 32 + lr, half * 4 + lc + p);
+  };
+  auto load_b = [&](const float* st_, int half, f16x8 (&x)[Cfg::FN][2]) {
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) x[j][p] = frag(st_ + AF, wn0 + j * 32 + lr, half * 4 + lc + p);
+  };
+  auto mma = [&](int i, const f16x8 (&x)[2], const f16x8 (&y)[Cfg::FN][2]) {
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], y[j][0], acc[i][j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y[j][1], acc[i][j], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y[j][0], acc[i][j], 0, 0, 0);
+  };
+  auto tile = [&](int kt, auto stage_tag) {
+    constexpr int S = decltype(stage_tag)::value;
+    const float* cur = smem + S * STAGE;
+    if (kt + 1 < nk) fetch(kt + 1);
+    load_b(cur, 0, b[0]);
+    load_a(cur, 0, 0, a[0]);
+#pragma unroll
+    for (int z = 0; z < 2 * Cfg::FM; ++z) {
+      const int half = z / Cfg::FM, next = (z + 1) / Cfg::FM;
+      if (z + 1 < 2 * Cfg::FM) {
+        if (next != half) load_b(cur, next, b[1]);
+        load_a(cur, next, (z + 1) % Cfg::FM, a[(z + 1) & 1]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      mma(z % Cfg::FM, a[z & 1], b[half]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // the other stage was last read in tile kt - 1, which every wave has left
+    if (kt + 1 < nk) stage(smem + (S ^ 1) * STAGE);
+    __syncthreads();
+  };
+  int kb = 0;
+  for (; kb + 2 <= nk; kb += 2) {
+    tile(kb, std::integral_constant<int, 0>{});
+    tile(kb + 1, std::integral_constant<int, 1>{});
+  }
+  if (kb < nk) tile(kb, std::integral_constant<int, 0>{});
+#pragma unroll
+  for (int i = 0; i < Cfg::FM; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int e = row_exp(m0 + wm0 + i * 32 + frag_row(v, lane)) + eh;
+#pragma unroll
+      for (int j = 0; j < Cfg::FN; ++j) acc[i][j][v] = ldexpf(acc[i][j][v], e);
+    }
+  conv_wgrad_store<Cfg>(acc, m0, n0, s, O, fC, KC, fCin, Cst, J, ldJ, off);
+}
+
 // Grid of the per-sample weight-space products: the tiles of one sample on one XCD, so the
 // column tiles that share a block of cotangent rows (and the row tiles that share the patch
 // columns) read them through one L2 (xcd_sample_tile).
@@ -1152,7 +1688,8 @@ static hipError_t conv_wgrad_vec(hipStream_t s, const float* G, const float* h, 
 // pointwise (PW = true: columns ci of the layer input) convolution.
 template <bool PW>
 static hipError_t conv_wgrad_any(hipStream_t s, const float* G, const float* h, int images, int O, int H,
-                                 int W, int C, int Cin, float* J, long long ldJ, long long off, int Cst) {
+                                 int W, int C, int Cin, float* J, long long ldJ, long long off, int Cst,
+                                 const ConvPairWgrad* pair) {
   const int KC = (PW ? 1 : 9) * Cin;
   if ((long long)8 * ((images + 7) / 8) * cdiv(KC, CfgConv::BN) * cdiv((long long)O * C, CfgConv::BM) >=
       (1LL << 31))
@@ -1175,6 +1712,28 @@ static hipError_t conv_wgrad_any(hipStream_t s, const float* G, const float* h, 
       return hipGetLastError();
     };
     const bool al = PW ? (H * W) % 32 == 0 : W % 32 == 0;
+    if (pair) {
+      auto gop = [&](auto cfg_tag, auto al_tag) -> hipError_t {
+        using Cfg = decltype(cfg_tag);
+        constexpr bool AL = decltype(al_tag)::value;
+        const int tn = cdiv(KC, Cfg::BN), tm = cdiv(O * C, Cfg::BM);
+        constexpr int bytes = gemm_dma_smem_bytes<Cfg, 2>();
+        hipError_t e = hipFuncSetAttribute((const void*)k_conv_wgrad_pair<Cfg, PW, AL>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e != hipSuccess) return e;
+        k_conv_wgrad_pair<Cfg, PW, AL><<<dim3(wgrad_grid(tm * tn, images)), dim3(Cfg::THREADS), bytes, s>>>(
+            G, h, *pair, O, H, W, C, Cin, FastDiv((uint32_t)C), FastDiv((uint32_t)W), FastDiv((uint32_t)Cin), Cst, J,
+            ldJ, off, tm, tn, images);
+        return hipGetLastError();
+      };
+      // few columns (the 3-channel first layer, a pointwise layer): half-width tiles; few rows (one
+      // output, as for the folded last convolution): 64 x 64, for enough workgroups
+      if (KC <= 64)
+        return al ? gop(CfgConvWgPairN{}, std::true_type{}) : gop(CfgConvWgPairN{}, std::false_type{});
+      if (O * C <= 64)
+        return al ? gop(CfgConvWgPairM{}, std::true_type{}) : gop(CfgConvWgPairM{}, std::false_type{});
+      return al ? gop(CfgConvWgPair{}, std::true_type{}) : gop(CfgConvWgPair{}, std::false_type{});
+    }
     // at most 64 rows (O C: one output, as for the folded last convolution): 64 x 64 tiles
     if (O * C <= 64)
       return al ? go(CfgConvWgSmall{}, std::true_type{}) : go(CfgConvWgSmall{}, std::false_type{});
@@ -1188,13 +1747,14 @@ static hipError_t conv_wgrad_any(hipStream_t s, const float* G, const float* h, 
 }
 
 hipError_t launch_conv_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H,
-                             int W, int C, int Cin, float* J, long long ldJ, long long off) {
-  return conv_wgrad_any<false>(s, G, h, images, O, H, W, C, Cin, J, ldJ, off, Cin);
+                             int W, int C, int Cin, float* J, long long ldJ, long long off,
+                             const ConvPairWgrad* pair) {
+  return conv_wgrad_any<false>(s, G, h, images, O, H, W, C, Cin, J, ldJ, off, Cin, pair);
 }
 
 hipError_t launch_pw_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H, int W,
-                           int C, int Cin, float* J, long long ldJ, long long off) {
-  return conv_wgrad_any<true>(s, G, h, images, O, H, W, C, Cin, J, ldJ, off, Cin);
+                           int C, int Cin, float* J, long long ldJ, long long off, const ConvPairWgrad* pair) {
+  return conv_wgrad_any<true>(s, G, h, images, O, H, W, C, Cin, J, ldJ, off, Cin, pair);
 }
 
 // xp [rows, Cp] = x [rows, Cin] with zero channels Cin .. Cp - 1.
@@ -1219,7 +1779,8 @@ bool conv_wgrad_pad_ok(int images, int O, int H, int W, int C, int Cin, const fl
 }
 
 hipError_t launch_conv_wgrad_padded(hipStream_t s, const float* G, const float* h, float* xp, int images, int O,
-                                    int H, int W, int C, int Cin, float* J, long long ldJ, long long off, bool pw) {
+                                    int H, int W, int C, int Cin, float* J, long long ldJ, long long off, bool pw,
+                                    const ConvPairWgrad* pair) {
   const int Cp = (Cin + 3) & ~3;
   if (!conv_wgrad_pad_ok(images, O, H, W, C, Cin, G, xp)) return hipErrorInvalidValue;
   const long long rows = (long long)images * H * W;
@@ -1227,8 +1788,8 @@ hipError_t launch_conv_wgrad_padded(hipStream_t s, const float* G, const float* 
       h, rows, Cin, Cp, xp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return pw ? conv_wgrad_any<true>(s, G, xp, images, O, H, W, C, Cp, J, ldJ, off, Cin)
-            : conv_wgrad_any<false>(s, G, xp, images, O, H, W, C, Cp, J, ldJ, off, Cin);
+  return pw ? conv_wgrad_any<true>(s, G, xp, images, O, H, W, C, Cp, J, ldJ, off, Cin, pair)
+            : conv_wgrad_any<false>(s, G, xp, images, O, H, W, C, Cp, J, ldJ, off, Cin, pair);
 }
 
 // ------------------------------------------------------------------------------ split-K J1 J2^T

@@ -26,23 +26,81 @@ struct FlipBatch {
   int count;
 };
 hipError_t launch_conv_flip_batch(hipStream_t s, const FlipBatch& b);
+// What the products on f16 pairs (pair_core.hpp) need beside the fp32 operands: a bound of the
+// magnitudes of each cotangent image, gmax[img*O + o] * *fac (fac null: 1; gmax null: gconst), of
+// each image of the other operand, hmax[img], and the kernel's pair rows.  Null pointers to these
+// structs: the fp32 matrix cores.
+struct ConvPairBwd {
+  const float* gmax;
+  const float* fac;
+  const float* Kp;    // Kt as pair rows [Cin, 9*Cg]
+  const int* kexps;   // [Cin]
+};
+struct ConvPairWgrad {
+  const float* gmax;
+  const float* fac;
+  float gconst;
+  const float* hmax;  // [images]
+};
 // out [images*O, D, Cin] = conv3x3(G [images*O, H, W, Cg], Kt [Cin, 3, 3, Cg]) * dphi [images, D, Cin]
-// (dphi null: the identity).
+// (dphi null: the identity).  With gmax_out, gmax_out[img*O + o] (zero before) receives the largest
+// magnitude of each cotangent image of out.
 hipError_t launch_conv_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
-                           const float* Kt, int Cin, const float* dphi, float* out);
+                           const float* Kt, int Cin, const float* dphi, float* out,
+                           const ConvPairBwd* pair = nullptr, float* gmax_out = nullptr);
+bool conv_bwd_pair_ok(const float* G, const float* Kp, int W, int Cg);
 // J[(s*O + o), off + c*9*Cin + k] = sum_p G[s, o, p, c] patch(h)[s, p, k] for every sample s.
 hipError_t launch_conv_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H,
-                             int W, int C, int Cin, float* J, long long ldJ, long long off);
+                             int W, int C, int Cin, float* J, long long ldJ, long long off,
+                             const ConvPairWgrad* pair = nullptr);
 // Pointwise (1x1) form: J[(s*O + o), off + c*Cin + ci] = sum_p G[s, o, p, c] h[s, p, ci].
 hipError_t launch_pw_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H,
-                           int W, int C, int Cin, float* J, long long ldJ, long long off);
+                           int W, int C, int Cin, float* J, long long ldJ, long long off,
+                           const ConvPairWgrad* pair = nullptr);
+// Everything the pair products of one CNN evaluation need that does not depend on the backward, in
+// one launch: the pair rows of the flipped kernels (rows of K[z] floats at Kt[z], N[z] rows), the
+// largest magnitude of each image of the layer inputs x[j] ([M, plane[j]] -> hmax[j]), the bound
+// of the seed's cotangents (max_c |Wd[o, c]| scale -> gseed[img*O + o]), zeroed maxima
+// [zero, zero + nzero), and per depthwise or scale layer the factor by which its backward can grow
+// a magnitude (largest column sum of taps[i] x ch[i] weights, times grow[i]) multiplied over runs
+// of such layers: fac[i] = (chain[i] ? fac[i - 1] : 1) * factor_i.
+struct ConvPrep {
+  const float* Kt[kMaxLayers];
+  float* Kp[kMaxLayers];
+  int* kexps[kMaxLayers];
+  int K[kMaxLayers], N[kMaxLayers];
+  int count;
+  const float* Wd;
+  int O, C, M;
+  float seed_scale;
+  float* gseed;
+  float* zero;
+  long long nzero;
+};
+struct ConvFactors {
+  const float* w[kMaxLayers];   // null: a pool (factor grow)
+  int taps[kMaxLayers], ch[kMaxLayers];
+  float grow[kMaxLayers];
+  unsigned char chain[kMaxLayers];
+  int count;
+  float* fac;
+};
+struct ConvMax {
+  const float* x[kMaxLayers];
+  float* out[kMaxLayers];
+  int plane[kMaxLayers];
+  int count, M;
+};
+hipError_t launch_conv_prep(hipStream_t s, const ConvPrep& p, const ConvFactors& f);
+hipError_t launch_conv_max(hipStream_t s, const ConvMax& m);
 // The same products for Cin % 4 != 0 on the direct-to-LDS path: h [images, H, W, Cin] is first
 // copied into xp [images, H, W, Cp] (Cp = Cin rounded up to 4, zero channels past Cin; caller's
 // buffer), and the zero columns are not stored.  conv_wgrad_pad_ok: whether the shapes and
 // pointers allow it (else the register-staged form of launch_conv_wgrad / launch_pw_wgrad).
 bool conv_wgrad_pad_ok(int images, int O, int H, int W, int C, int Cin, const float* G, const float* xp);
 hipError_t launch_conv_wgrad_padded(hipStream_t s, const float* G, const float* h, float* xp, int images, int O,
-                                    int H, int W, int C, int Cin, float* J, long long ldJ, long long off, bool pw);
+                                    int H, int W, int C, int Cin, float* J, long long ldJ, long long off, bool pw,
+                                    const ConvPairWgrad* pair = nullptr);
 // theta[n1, n2, o1, o2] += scale sum_c Wr[o1, c] Wr[o2, c] Mc[c, n1, n2] (Wr [O, C], Mc [C, N1, N2]).
 hipError_t launch_readout_fold(hipStream_t s, const float* Wr, int C, int O, const float* Mc, int N1, int N2,
                                float scale, float* theta);

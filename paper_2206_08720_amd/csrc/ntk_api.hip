@@ -174,6 +174,12 @@ struct ntk_handle {
   size_t off_mc = 0;              // per-channel Grams of the last convolution [C, N1, N2] (0: none)
   size_t off_xpad = 0;            // a convolution input padded to a multiple of 4 channels (0: none)
   long long part_capacity = 0;    // floats of the split-K partial buffer
+  // products on f16 pairs (pair_core.hpp): pair rows of the flipped kernels and their exponents,
+  // bounds of the cotangent images [nc, Mmax*O] and the layer inputs' images [nc, Mmax], growth
+  // factors of the block-diagonal layers [nc]; not in the lean plan
+  bool cpair = false;
+  std::vector<size_t> off_Kp, off_ke;
+  size_t off_gmax = 0, off_hmax = 0, off_fac = 0;
 };
 
 static thread_local std::string g_init_error;
@@ -502,6 +508,19 @@ static void plan_cnn(ntk_handle* h) {
   for (int l = 1; l < nc; ++l)   // flipped 3x3 kernels, transposed pointwise weights
     if (h->layers[l].kind == NTK_CONV3X3_SAME || h->layers[l].kind == NTK_CONV1X1)
       h->off_Kt[l] = take((size_t)(h->layers[l].kind == NTK_CONV1X1 ? 1 : 9) * h->ch[l] * h->ch[l + 1]);
+  h->cpair = !h->lean;
+  if (h->cpair) {
+    h->off_Kp.assign(nc, 0);
+    h->off_ke.assign(nc, 0);
+    for (int l = 1; l < nc; ++l)
+      if (h->layers[l].kind == NTK_CONV3X3_SAME && conv_bwd_pair_ok(nullptr, nullptr, h->bw[l], h->ch[l + 1])) {
+        h->off_Kp[l] = take((size_t)9 * h->ch[l] * h->ch[l + 1]);
+        h->off_ke[l] = take(h->ch[l]);
+      }
+    h->off_gmax = take(Mmax * O * nc);
+    h->off_hmax = take(Mmax * nc);
+    h->off_fac = take(nc);
+  }
   h->off_g = take(Mmax * h->ch[nc]);
   h->off_Gping = take(Mmax * O * gmax);
   h->off_Gpong = take(Mmax * O * gmax);
@@ -1250,6 +1269,23 @@ static double inside_out_cost(double pairs, int D, int Cin, int C, int Oe, bool 
          (gram_blocks * Dp * Dp * Ci + out_blocks * (16.0 * Dp * Dp * C + 256.0 * Dp * C));
 }
 
+// Whether a CNN's backward and weight-space products run on f16 pairs: two more launches (the pair
+// rows and the images' maxima, 12 us) against the time of the products that have a pair form.
+// 4x4 images, 9 GFLOP: 348 us with pairs, 316 us with the fp32 MFMA (the few workgroups wait on
+// loads either way); one output of 64 32x32 images, 27 GFLOP: 617 against 655 us.
+constexpr double kConvPairMinFlops = 2e10;
+static bool cnn_pair_pays(const ntk_handle* h, int M, int Oe) {
+  double flops = 0;
+  for (int l = 0; l < h->nc; ++l) {
+    const int kind = h->layers[l].kind, cin = h->ch[l], cout = h->ch[l + 1];
+    if (kind != NTK_CONV3X3_SAME && kind != NTK_CONV1X1) continue;
+    const double f = 2.0 * M * Oe * h->bh[l] * h->bw[l] * weight_cols(h->layers[l], cin);
+    if (cout % 4 == 0 && (cin % 4 == 0 || h->off_xpad)) flops += f;
+    if (l && h->off_Kp[l]) flops += f;
+  }
+  return flops >= kConvPairMinFlops;
+}
+
 static int compute_cnn(ntk_handle* h, const float* const* params, const float* X1, int n1,
                        const float* X2, int n2, float* theta) {
   const int nc = h->nc, O = h->out_dim;
@@ -1258,6 +1294,7 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
   hipStream_t s = h->stream;
   Profiler* P = &h->prof;
   auto F = [&](size_t off) { return reinterpret_cast<float*>(h->ws + off); };
+  auto I = [&](size_t off) { return reinterpret_cast<int*>(h->ws + off); };
   // variants: one logit (the cotangent rows are then (n) instead of (n, o)), the trace over
   // outputs, the batch diagonal (pairs (n, n) only)
   const bool logit = h->opt_output == NTK_OUTPUT_LOGIT;
@@ -1401,8 +1438,77 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
   }
   float* Gcur = F(h->off_Gping);
   float* Gnext = F(h->off_Gpong);
-  prof_begin(P, s, KC_CONV_SEED);
   const float* Wd = params[h->rslot] + (logit ? (size_t)h->opt_logit * C : 0);
+  // Products on f16 pairs: bounds of every cotangent image (the seed's from the readout weights,
+  // exact ones from the convolutions' epilogues, grown by a factor through the block-diagonal
+  // layers and pools) and of every layer input.
+  auto act_bound = [&](int l) { return h->wslot[l] >= 0 && h->layers[l].act == NTK_ACT_ERF ? 1.1284f : 1.f; };
+  struct Bound {
+    const float *gmax, *fac;
+  };
+  std::vector<Bound> bound(nc, Bound{nullptr, nullptr});
+  const size_t gm_ld = ((size_t)h->max_n1 + h->max_n2) * O, hm_ld = (size_t)h->max_n1 + h->max_n2;
+  auto gmax = [&](int l) { return F(h->off_gmax) + l * gm_ld; };
+  bool cpair = h->cpair && h->opt_method != NTK_METHOD_JACOBIAN && cnn_pair_pays(h, M, Oe);
+  if (cpair) {
+    ConvFactors cf{};
+    int run = 0;
+    bound[nc - 1] = {gmax(nc - 1), nullptr};
+    for (int l = nc - 1; l >= 1; --l) {
+      const ntk_layer_desc& L = h->layers[l];
+      if (L.kind == NTK_CONV3X3_SAME || L.kind == NTK_CONV1X1) {
+        bound[l - 1] = {gmax(l - 1), nullptr};
+        run = 0;
+        continue;
+      }
+      const int i = cf.count++;
+      cf.w[i] = h->wslot[l] >= 0 ? params[h->wslot[l]] : nullptr;
+      cf.taps[i] = L.kind == NTK_DWCONV3X3_SAME ? 9 : 1;
+      cf.ch[i] = h->ch[l + 1];
+      cf.grow[i] = (L.kind == NTK_AVGPOOL2 ? 0.25f : 1.f) * act_bound(l - 1);
+      cf.chain[i] = bound[l].fac != nullptr;
+      bound[l - 1] = {bound[l].gmax, F(h->off_fac) + i};
+      // each such layer loosens the bound (about 2 bits); the pairs hold about 10 to spare
+      if (++run > 4) cpair = false;
+    }
+    cf.fac = F(h->off_fac);
+    if (cpair) {
+      ConvPrep cp{};
+      for (int l = 1; l < nc; ++l) {
+        if (!h->off_Kp[l]) continue;
+        cp.Kt[cp.count] = F(h->off_Kt[l]);
+        cp.Kp[cp.count] = F(h->off_Kp[l]);
+        cp.kexps[cp.count] = I(h->off_ke[l]);
+        cp.K[cp.count] = 9 * h->ch[l + 1];
+        cp.N[cp.count] = h->ch[l];
+        ++cp.count;
+      }
+      cp.Wd = Wd;
+      cp.O = Oe;
+      cp.C = C;
+      cp.M = M;
+      cp.seed_scale = act_bound(nc - 1) / (float)(h->bh[nc] * h->bw[nc]);
+      cp.gseed = gmax(nc - 1);
+      cp.zero = gmax(0);
+      cp.nzero = (long long)(nc - 1) * gm_ld;
+      ConvMax cm{};
+      cm.M = M;
+      for (int l = 0; l < nc; ++l) {
+        const int kind = h->layers[l].kind;
+        if ((kind != NTK_CONV3X3_SAME && kind != NTK_CONV1X1) || inside[l]) continue;
+        cm.x[cm.count] = hptr(l);
+        cm.out[cm.count] = F(h->off_hmax) + l * hm_ld;
+        cm.plane[cm.count] = h->bh[l] * h->bw[l] * h->ch[l];
+        ++cm.count;
+      }
+      prof_begin(P, s, KC_TRANSPOSE);
+      e = launch_conv_prep(s, cp, cf);
+      if (e == hipSuccess) e = launch_conv_max(s, cm);
+      prof_end(P, s, KC_TRANSPOSE);
+      if (e != hipSuccess) return hip_fail(h, e, "pair preparation");
+    }
+  }
+  prof_begin(P, s, KC_CONV_SEED);
   const float* dlast = h->wslot[nc - 1] >= 0 ? F(h->off_cdphi[nc - 1]) : nullptr;
   e = launch_conv_seed(s, Wd, dlast, M, Oe, h->bh[nc] * h->bw[nc], C, Gcur);
   prof_end(P, s, KC_CONV_SEED);
@@ -1412,10 +1518,14 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
   auto wgrad = [&](int l, const float* G, int Orows, float* Jout, long long ldJ, long long off, bool pw) {
     const int Hl = h->bh[l], Wl = h->bw[l], cin = h->ch[l], cout = h->ch[l + 1];
     float* xp = h->off_xpad ? F(h->off_xpad) : nullptr;
+    // the folded layer's "cotangent" is act' itself
+    const ConvPairWgrad pg{fold && l == ll ? nullptr : bound[l].gmax, bound[l].fac, act_bound(l),
+                           F(h->off_hmax) + l * hm_ld};
+    const ConvPairWgrad* pr = cpair ? &pg : nullptr;
     if (xp && conv_wgrad_pad_ok(M, Orows, Hl, Wl, cout, cin, G, xp))
-      return launch_conv_wgrad_padded(s, G, hptr(l), xp, M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pw);
-    return pw ? launch_pw_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off)
-              : launch_conv_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off);
+      return launch_conv_wgrad_padded(s, G, hptr(l), xp, M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pw, pr);
+    return pw ? launch_pw_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr)
+              : launch_conv_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr);
   };
   float* J = F(h->off_J);
   // the folded layer's A: in J past this call's columns (J holds that layer's O C F Cin columns
@@ -1493,13 +1603,17 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
       const float* dprev = h->wslot[l - 1] >= 0 ? F(h->off_cdphi[l - 1]) : nullptr;
       if (L.kind == NTK_CONV3X3_SAME) {
         prof_begin(P, s, KC_CONV_BWD);
-        e = launch_conv_bwd(s, Gcur, M, Oe, Hl, Wl, cout, F(h->off_Kt[l]), cin, dprev, Gnext);
+        const ConvPairBwd pb{bound[l].gmax, bound[l].fac, cpair && h->off_Kp[l] ? F(h->off_Kp[l]) : nullptr,
+                             cpair && h->off_Kp[l] ? I(h->off_ke[l]) : nullptr};
+        e = launch_conv_bwd(s, Gcur, M, Oe, Hl, Wl, cout, F(h->off_Kt[l]), cin, dprev, Gnext, pb.Kp ? &pb : nullptr,
+                            cpair ? gmax(l - 1) : nullptr);
         prof_end(P, s, KC_CONV_BWD);
       } else if (L.kind == NTK_CONV1X1) {
         prof_begin(P, s, KC_CONV_BWD);
         int rows;
         e = to_int((long long)M * Oe * Hl * Wl, rows)
-                ? launch_pw_bwd(s, Gcur, F(h->off_Kt[l]), dprev, rows, cin, cout, Oe, Hl * Wl, Gnext)
+                ? launch_pw_bwd(s, Gcur, F(h->off_Kt[l]), dprev, rows, cin, cout, Oe, Hl * Wl, Gnext,
+                                cpair ? gmax(l - 1) : nullptr)
                 : hipErrorInvalidValue;
         prof_end(P, s, KC_CONV_BWD);
       } else {

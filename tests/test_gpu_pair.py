@@ -78,3 +78,68 @@ def test_pair_rows_magnitudes():
     params[1][5] = 0.0
     X1, X2 = wl.make_inputs(spec, 140, 49), wl.make_inputs(spec, 120, 50)
     _check("magnitudes", spec, params, X1, X2)
+
+
+# ---- convolutions: the cotangent backward and the weight-space products on pairs -----------------
+# Tolerance as above: a backward product sums 9 Cout terms (576: 108 roundings of 2^-24, 6.4e-6, and
+# 4e-7), at most three of them in a row, the weight-space product D terms (480 pixels: 5.4e-6), then
+# J1 J2^T in fp32 (worst case K 2^-24 on sums of random sign; 1e-5 allowed here).
+CONV_TOL = 3 * 6.8e-6 + 5.8e-6 + 1e-5
+
+
+def _conv_check(name, spec, params, X1, X2, variant=("full", "full", 0)):
+    print(f"[pair] {name} {variant}", flush=True)
+    got = gpu_ntk(spec, params, X1, X2, variant=variant)
+    ref, d1, d2 = oracle.ntk_jc_with_norms(spec, params, X1, X2, layer_storage=S)
+    if variant == ("full", "full", 0):
+        cs, nw = errors(got, ref, d1, d2)
+    else:
+        cs, nw = scaled_errors(got, variant_of(ref, *variant), variant_scale(d1, d2, *variant))
+    report(name, cs, nw)
+    assert cs <= CONV_TOL and nw <= CONV_TOL
+
+
+C3 = "conv3x3"
+CONV_CASES = [
+    # odd image (rows of a tile straddle images, the halo is not whole tiles), biases
+    ("21x19, 64 channels", (21, 19), 3, [(C3, 64, "relu", True), (C3, 64, "relu", True), (C3, 64, "relu", False)],
+     10, 14, 9),
+    # image rows that are whole K tiles; 96 and 36 channels (36: no pair backward behind it)
+    ("12x32, 96 and 36 channels", (12, 32), 4, [(C3, 96, "erf", False), (C3, 36, "relu", True), (C3, 64, "relu", False)],
+     9, 13, 9),
+    # the widest image the halo holds, and one beyond it
+    ("5x63", (5, 63), 8, [(C3, 64, "relu", False), (C3, 64, "relu", False), (C3, 64, "relu", True)], 10, 18, 13),
+    ("6x66", (6, 66), 3, [(C3, 64, "relu", False), (C3, 64, "relu", False), (C3, 64, "relu", True)], 10, 18, 9),
+    # bounds through depthwise, scale and pool layers, pointwise layers
+    ("struct 24x20", (24, 20), 3, [(C3, 64, "relu", True), ("dwconv3x3", "erf", True), ("conv1x1", 64, "relu", True),
+                                   ("avgpool2",), ("scale", "relu", True), (C3, 64, "relu", True),
+                                   ("scale", "erf", False), (C3, 64, "relu", False)], 10, 40, 21),
+    # small images: many per tile
+    ("3x3 images", (3, 3), 5, [(C3, 64, "relu", False), (C3, 64, "erf", True), (C3, 64, "relu", False)], 10, 90, 70),
+]
+
+
+@pytest.mark.parametrize("case", CONV_CASES, ids=[c[0] for c in CONV_CASES])
+def test_pair_conv_shapes(case):
+    name, hw, cin, blocks, O, n1, n2 = case
+    spec = wl.cnn_layers_spec("pairc", hw, cin, blocks, O)
+    params = wl.make_params(spec, 61, "2/fan_in", bias_var=0.05)
+    X1, X2 = wl.make_inputs(spec, n1, 62), wl.make_inputs(spec, n2, 63)
+    _conv_check(name, spec, params, X1, X2)
+    if hw == (21, 19):
+        _conv_check(name, spec, params, X1, X1)
+        _conv_check(name, spec, params, X1, X2, ("trace", "full", 0))
+
+
+def test_pair_conv_magnitudes():
+    """Images, outputs and layers that differ by powers of two, an image of zeros."""
+    spec = wl.cnn_layers_spec("paircm", (20, 20), 3, [(C3, 64, "relu", False)] * 3, 10)
+    params = wl.make_params(spec, 64, "2/fan_in")
+    rng = np.random.default_rng(65)
+    params[3] *= np.exp2(rng.integers(-20, 21, (10, 1))).astype(np.float32)
+    params[0] *= np.float32(2.0 ** 30)
+    params[1] *= np.float32(2.0 ** -45)
+    X1, X2 = wl.make_inputs(spec, 13, 66), wl.make_inputs(spec, 10, 67)
+    X1 *= np.exp2(rng.integers(-15, 16, (13, 1, 1, 1))).astype(np.float32)
+    X2[3] = 0.0
+    _conv_check("conv magnitudes", spec, params, X1, X2)
