@@ -59,6 +59,21 @@ __host__ __device__ inline void tile_coords(int ord, int symmetric, int tiles_m,
   tn = band * cb + (rem - tm * w);
 }
 
+// Upper triangle of a square of tiles twice as high as wide (R rows by R columns, tiles of 2 B x B):
+// row tm holds the tiles tn = 2 tm .. tiles_n - 1, enumerated row by row.
+__host__ __device__ inline int tri2_tiles(int tiles_m, int tiles_n) {
+  return tiles_m * tiles_n - tiles_m * (tiles_m - 1);
+}
+__host__ __device__ inline void tri2_index(int t, int tiles_n, int& tm, int& tn) {
+  int r = 0, base = 0;
+  while (base + (tiles_n - 2 * r) <= t) {
+    base += tiles_n - 2 * r;
+    ++r;
+  }
+  tm = r;
+  tn = 2 * r + (t - base);
+}
+
 // Start of stream-K range `lam` when U units are cut into P equal contiguous ranges.
 __host__ __device__ inline long long sk_start(int lam, long long U, int P) {
   return (long long)lam * U / P;

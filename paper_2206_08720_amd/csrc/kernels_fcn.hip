@@ -23,10 +23,24 @@ namespace ntk {
 using CfgBig = TileCfg<128, 128, 32, 64, 64>;   // 4 waves, 64x64 per wave
 using CfgBig8 = TileCfg<128, 128, 32, 32, 64>;  // 8 waves, 32x64 per wave
 using CfgSK = CfgBig8;                          // stream-K contraction
-using CfgSKPair = TileCfg<128, 128, 32, 64, 64>;   // the same on pair rows: 4 waves, 64x64 per wave
+// The same on pair rows: 8 waves of 64x64, one workgroup per CU.  Against 4 waves of 64x64 on 128x128
+// tiles, two workgroups per CU, a K tile's loads into LDS are shared by twice the products (LDS
+// bandwidth bounds both): 13.3 -> 11.2 ms at 12800 x 12800 x (3 x 4096), 2.45 -> 2.21 ms at
+// 5120 x 5120 x (8 x 2048).  With one or two outputs the tile's Gram block leaves no room for three
+// stages, and the 128x128 tiles stay.
+using CfgSKPair = TileCfg<256, 128, 32, 64, 64>;
+using CfgSKPairSmall = TileCfg<128, 128, 32, 64, 64>;
 // The stream-K contraction keeps two workgroups per compute unit (two LDS stages each, so
 // both fit the 160 KB of LDS): one workgroup's barrier waits are covered by the other's MFMAs.
 constexpr int kSkPerCu = 2, kSkStages = 2;
+template <class Cfg, bool PAIR>
+constexpr int sk_per_cu() {
+  return PAIR && Cfg::BM == 256 ? 1 : kSkPerCu;
+}
+template <class Cfg>
+constexpr int sk_pair_stages() {
+  return Cfg::BM == 256 ? 3 : 2;
+}
 // LDS stages of the direct-to-LDS loop of the layer-split contraction (64 x 64 tiles): two
 // stages (32 KB) let four workgroups share a compute unit
 constexpr int kSplitStages = 2;
@@ -1173,11 +1187,26 @@ k_ntk_fcn_lreduce(const float* __restrict__ gram_readout, float readout_scale, i
 //     theta; a split tile's partial sums go to `part` (slot 0: the first tile of a range,
 //     slot 1: its last) and k_ntk_fcn_fixup adds them in range order.
 // No workgroup waits for another; the summation order is fixed for a given device.
+template <class Cfg>
+__device__ __forceinline__ void sk_tile_coords(int t, int symmetric, int tiles_m, int tiles_n, int& tm, int& tn) {
+  static_assert(Cfg::BM == Cfg::BN || Cfg::BM == 2 * Cfg::BN, "square or two-high tiles");
+  if (symmetric && Cfg::BM == 2 * Cfg::BN) tri2_index(t, tiles_n, tm, tn);
+  else tile_coords(t, symmetric, tiles_m, tiles_n, tm, tn);
+}
+// The symmetric schedule's writes of element (r, s): itself from the diagonal of BN x BN blocks up,
+// its mirror from above the diagonal.
+template <class Cfg>
+__device__ __forceinline__ void fcn_write(float* __restrict__ theta, int N1, int N2, int O, int symmetric, int r, int s,
+                                          int n1, int o1, int n2, int o2, float v) {
+  const int br = r / Cfg::BN, bs = s / Cfg::BN;   // powers of two
+  if (!symmetric || br <= bs) theta[(((long long)n1 * N2 + n2) * O + o1) * O + o2] = v;
+  if (symmetric && br < bs) theta[(((long long)n2 * N1 + n1) * O + o2) * O + o1] = v;
+}
 // Final epilogue of a tile: add the readout summand, write theta (and its mirror).
 template <class Cfg>
 __device__ __forceinline__ void fcn_tile_out(f32x16 (&tot)[Cfg::FM][Cfg::FN], const float* gram_readout,
                                              float rscale, int N1, int N2, FastDiv fO, int R1, int R2,
-                                             int m0, int n0, bool mirror, float* smem,
+                                             int m0, int n0, int symmetric, float* smem,
                                              float* __restrict__ theta) {
   const int O = (int)fO.d;
   int n1lo, n2lo, S2;
@@ -1187,8 +1216,7 @@ __device__ __forceinline__ void fcn_tile_out(f32x16 (&tot)[Cfg::FM][Cfg::FN], co
       const int n1 = (int)fO.div(r), o1 = r - n1 * O;
       const int n2 = (int)fO.div(s), o2 = s - n2 * O;
       if (o1 == o2) v += rscale * smem[(n1 - n1lo) * S2 + (n2 - n2lo)];
-      theta[(((long long)n1 * N2 + n2) * O + o1) * O + o2] = v;
-      if (mirror) theta[(((long long)n2 * N1 + n1) * O + o2) * O + o1] = v;
+      fcn_write<Cfg>(theta, N1, N2, O, symmetric, r, s, n1, o1, n2, o2, v);
     }
   });
   __syncthreads();
@@ -1242,7 +1270,7 @@ __device__ __forceinline__ void fcn_tile_layers(const FcnContraction& c, int l0,
 // kSkPerCu workgroups per compute unit must be resident together: the register budget is that
 // of kSkPerCu * THREADS / 256 waves per SIMD
 template <class Cfg, bool VEC, bool DMA, bool PAIR = false>
-__global__ void __launch_bounds__(Cfg::THREADS, kSkPerCu * Cfg::THREADS / 256)
+__global__ void __launch_bounds__(Cfg::THREADS, (sk_per_cu<Cfg, PAIR>() * Cfg::THREADS / 256))
 k_ntk_fcn_sk(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, float* __restrict__ theta,
              int tiles_m, int tiles_n, int T, int P, float* __restrict__ part) {
   extern __shared__ float smem[];
@@ -1271,18 +1299,17 @@ k_ntk_fcn_sk(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, float*
       t = sh.first_sk + ts;
     }
     int tm, tn;
-    tile_coords(t, symmetric, tiles_m, tiles_n, tm, tn);
+    sk_tile_coords<Cfg>(t, symmetric, tiles_m, tiles_n, tm, tn);
     const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
     f32x16 tot[Cfg::FM][Cfg::FN];
     zero_acc<Cfg>(tot);
     if constexpr (PAIR) {
-      for (int l = l0; l < l1; ++l) fcn_pair_layer<Cfg, kSkStages, kPairFlushBig>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
+      for (int l = l0; l < l1; ++l) fcn_pair_layer<Cfg, sk_pair_stages<Cfg>(), kPairFlushBig>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
     } else {
       fcn_tile_layers<Cfg, VEC, DMA>(c, l0, l1, N2, fO, R1, R2, m0, n0, smem, tot);
     }
     if (l0 == 0 && l1 == L) {
-      fcn_tile_out<Cfg>(tot, c.gram_readout, c.readout_scale, N1, N2, fO, R1, R2, m0, n0, symmetric && tm != tn, smem,
-                        theta);
+      fcn_tile_out<Cfg>(tot, c.gram_readout, c.readout_scale, N1, N2, fO, R1, R2, m0, n0, symmetric, smem, theta);
     } else {
       float* dst = part + ((long long)lam * 2 + sk_slot(beg, L, ts)) * (Cfg::BM * Cfg::BN);
       int z = 0;   // opaque zero: keeps the 32 store offsets from being computed up front
@@ -1298,13 +1325,16 @@ k_ntk_fcn_sk(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, float*
 // it and is the first boundary inside it (sk_fixup_tile); kFixupSplit workgroups share that
 // tile, each thread adds the partial sums of one float4 of it (ranges in order), adds the
 // readout summand and writes theta.
-constexpr int kFixupSplit = 16;
+template <class Cfg>
+constexpr int fixup_split() {
+  return Cfg::BM * Cfg::BN / 1024;
+}
 template <class Cfg>
 __global__ void __launch_bounds__(256)
 k_ntk_fcn_fixup(int L, const float* __restrict__ gram_readout, float rscale, int N1, int N2, FastDiv fO,
                 int symmetric, float* __restrict__ theta, int tiles_m, int tiles_n, int T, int P,
                 const float* __restrict__ part) {
-  static_assert(Cfg::BM * Cfg::BN == kFixupSplit * 256 * 4, "one float4 per thread");
+  constexpr int kFixupSplit = fixup_split<Cfg>();   // one float4 per thread
   const int P8 = P >> 3;
   const int blk = blockIdx.x / kFixupSplit, sub = blockIdx.x % kFixupSplit;
   const int x = blk / (P8 - 1), j = blk % (P8 - 1) + 1;
@@ -1312,7 +1342,7 @@ k_ntk_fcn_fixup(int L, const float* __restrict__ gram_readout, float rscale, int
   const int ts = sk_fixup_tile(sh, j, P8, L);
   if (ts < 0) return;
   int tm, tn;
-  tile_coords(sh.first_sk + ts, symmetric, tiles_m, tiles_n, tm, tn);
+  sk_tile_coords<Cfg>(sh.first_sk + ts, symmetric, tiles_m, tiles_n, tm, tn);
   const int e0 = (sub * 256 + threadIdx.x) * 4;
   const long long tile_end = (long long)(ts + 1) * L;
   float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1331,7 +1361,6 @@ k_ntk_fcn_fixup(int L, const float* __restrict__ gram_readout, float rscale, int
   }
   const int O = (int)fO.d;
   const int R1 = N1 * O, R2 = N2 * O;
-  const bool mirror = symmetric && tm != tn;
   const int i = e0 / Cfg::BN, jj = e0 - i * Cfg::BN;
   const int r = tm * Cfg::BM + i;
   if (r >= R1) return;
@@ -1344,8 +1373,7 @@ k_ntk_fcn_fixup(int L, const float* __restrict__ gram_readout, float rscale, int
       const int n2 = (int)fO.div(s), o2 = s - n2 * O;
       float w = vals[k];
       if (o1 == o2) w += rscale * gram_readout[(long long)n1 * N2 + n2];
-      theta[(((long long)n1 * N2 + n2) * O + o1) * O + o2] = w;
-      if (mirror) theta[(((long long)n2 * N1 + n1) * O + o2) * O + o1] = w;
+      fcn_write<Cfg>(theta, N1, N2, O, symmetric, r, s, n1, o1, n2, o2, w);
     }
   }
 }
@@ -1414,21 +1442,21 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
   for (int l = 0; l < c.L; ++l) dma = dma && c.K[l] % 32 == 0 && dma_span_ok(c.K[l], c.K[l], 256);
   const bool pair = c.L > 0 && c.exps;
   if (pair && !dma) return hipErrorInvalidValue;   // pair rows are aligned and padded to 32 k
-  auto go_sk = [&](auto vec_tag, auto dma_tag, auto pair_tag) -> hipError_t {
+  auto go_sk = [&](auto cfg_tag, auto vec_tag, auto dma_tag, auto pair_tag) -> hipError_t {
+    using Cfg = decltype(cfg_tag);
     constexpr bool VEC = decltype(vec_tag)::value;
     constexpr bool DMA = decltype(dma_tag)::value;
     constexpr bool PAIR = decltype(pair_tag)::value;
-    using Cfg = std::conditional_t<PAIR, CfgSKPair, CfgSK>;
     using L = LoadKInnerT<VEC>;
     const int tm = cdiv(R1, Cfg::BM), tn = cdiv(R2, Cfg::BN);
-    const int T = symmetric ? tn * (tn + 1) / 2 : tm * tn;
-    const int P = kSkPerCu * num_cu;
+    const int T = !symmetric ? tm * tn : (Cfg::BM == Cfg::BN ? tn * (tn + 1) / 2 : tri2_tiles(tm, tn));
+    const int P = sk_per_cu<Cfg, PAIR>() * num_cu;
     // LDS: the main loop's stages, or the Gram block of a tile if larger
     constexpr int loop_bytes = DMA ? gemm_dma_smem_bytes<Cfg, kSkStages>() : gemm_smem_bytes<Cfg, L, L>();
     constexpr int gram_bytes = (Cfg::BM + 1) * (Cfg::BN + 1) * 4;
     constexpr int max_bytes = loop_bytes > gram_bytes ? loop_bytes : gram_bytes;
-    static_assert(kSkPerCu * max_bytes <= 160 * 1024, "the workgroups of one CU must fit its LDS");
-    const int bytes = PAIR ? pair_smem_bytes<Cfg, kSkStages>(O) : max_bytes;
+    static_assert(PAIR || kSkPerCu * max_bytes <= 160 * 1024, "the workgroups of one CU must fit its LDS");
+    const int bytes = PAIR ? pair_smem_bytes<Cfg, sk_pair_stages<Cfg>()>(O) : max_bytes;
     hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_sk<Cfg, VEC, DMA, PAIR>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (e != hipSuccess) return e;
@@ -1437,15 +1465,18 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
         c, N1, N2, fO, symmetric, theta, tm, tn, T, P, part);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_ntk_fcn_fixup<Cfg><<<dim3(8 * (P / 8 - 1) * kFixupSplit), dim3(256), 0, s>>>(
+    k_ntk_fcn_fixup<Cfg><<<dim3(8 * (P / 8 - 1) * fixup_split<Cfg>()), dim3(256), 0, s>>>(
         c.L, c.gram_readout, c.readout_scale, N1, N2, fO, symmetric, theta, tm, tn, T, P, part);
     return hipGetLastError();
   };
   const long long big_tiles = (long long)cdiv(R1, 128) * cdiv(R2, 128);
   if (fcn_uses_stream_k(c.L, big_tiles, num_cu, part != nullptr)) {
-    if (pair) return go_sk(TrueT{}, TrueT{}, TrueT{});
-    return dma ? go_sk(TrueT{}, TrueT{}, FalseT{})
-               : (v ? go_sk(TrueT{}, FalseT{}, FalseT{}) : go_sk(FalseT{}, FalseT{}, FalseT{}));
+    if (pair)
+      return pair_smem_bytes<CfgSKPair, sk_pair_stages<CfgSKPair>()>(O) <= 160 * 1024
+                 ? go_sk(CfgSKPair{}, TrueT{}, TrueT{}, TrueT{})
+                 : go_sk(CfgSKPairSmall{}, TrueT{}, TrueT{}, TrueT{});
+    return dma ? go_sk(CfgSK{}, TrueT{}, TrueT{}, FalseT{})
+               : (v ? go_sk(CfgSK{}, TrueT{}, FalseT{}, FalseT{}) : go_sk(CfgSK{}, FalseT{}, FalseT{}, FalseT{}));
   }
   if (!pair && big_tiles >= 512) return v ? go(CfgBig8{}, TrueT{}) : go(CfgBig8{}, FalseT{});
   const int NG = fcn_split_groups(R1, R2, c.L, symmetric, num_cu, part != nullptr, pair);

@@ -335,6 +335,7 @@ hipError_t launch_pair_prep(hipStream_t s, const PairWeights& b, const float* Wr
 
 // ------------------------------------------------------------------------------ backward
 using CfgPair = TileCfg<128, 128, 32, 64, 32>;      // 8 waves, two workgroups per CU
+using CfgPairBig = TileCfg<256, 128, 32, 64, 64>;   // 8 waves, one workgroup per CU
 using CfgPairSmall = TileCfg<64, 64, 32, 32, 32>;   // 4 waves
 
 // The product is formed transposed, rows n of W_l^T by columns r of G_l, so that a lane holds four
@@ -342,7 +343,7 @@ using CfgPairSmall = TileCfg<64, 64, 32, 32, 32>;   // 4 waves
 // Tiles: the row tiles in groups of 8 with all their n tiles, in contiguous ranges per XCD, so
 // the workgroups in flight on an XCD share few panels of both operands.
 template <class Cfg, int NSTAGE>
-__global__ void __launch_bounds__(Cfg::THREADS, 2 * Cfg::THREADS / 256)
+__global__ void __launch_bounds__(Cfg::THREADS, (Cfg::BM == 256 ? 1 : 2) * Cfg::THREADS / 256)
 k_pair_bwd(PairBwd p, int tiles_n, int tiles_r) {
   extern __shared__ float smem[];
   constexpr int LOOP = NSTAGE * (Cfg::BM + Cfg::BN) * 32;
@@ -457,7 +458,11 @@ k_pair_bwd(PairBwd p, int tiles_n, int tiles_r) {
 static bool pair_bwd_big(int R, int N, int num_cu) {
   return (long long)cdiv(R, CfgPair::BN) * cdiv(N, CfgPair::BM) >= num_cu;
 }
+static bool pair_bwd_huge(int R, int N, int num_cu) {
+  return (long long)cdiv(R, CfgPairBig::BN) * cdiv(N, CfgPairBig::BM) >= num_cu;
+}
 int pair_bwd_parts(int R, int N, int num_cu) {
+  if (pair_bwd_huge(R, N, num_cu)) return cdiv(N, CfgPairBig::BM);
   return cdiv(N, pair_bwd_big(R, N, num_cu) ? CfgPair::BM : CfgPairSmall::BM);
 }
 
@@ -475,6 +480,7 @@ hipError_t launch_pair_bwd(hipStream_t s, PairBwd p, int num_cu) {
     k_pair_bwd<Cfg, NSTAGE><<<dim3(8 * cdiv((long long)tn * tr, 8)), dim3(Cfg::THREADS), bytes, s>>>(p, tn, tr);
     return hipGetLastError();
   };
+  if (pair_bwd_huge(p.R, p.N, num_cu)) return go(CfgPairBig{}, std::integral_constant<int, 3>{});
   if (pair_bwd_big(p.R, p.N, num_cu)) return go(CfgPair{}, std::integral_constant<int, 2>{});
   // Few tiles are bound by the latency of their loads: the more K tiles in flight the better, as
   // far as the LDS of a CU holds the workgroups it is given

@@ -146,8 +146,10 @@ struct ntk_handle {
   std::vector<size_t> off_l1;     // column-sum maxima of W_l                      [strips of d_l]
   std::vector<size_t> off_ws;     // column statistics of W_l by row chunks
   size_t off_rmax[2] = {0, 0};    // row maxima of two neighbouring layers         [parts, Mmax*O]
-  size_t off_gp[2] = {0, 0};      // pair rows of two neighbouring layers for the variants, whose
-                                  // contractions read fp32 rows                   [Mmax*O, padded]
+  // pair rows of two neighbouring layers, for the variants (their contractions read the fp32 rows
+  // of G_l): allocated when an option selects a variant; null: the variants' backward in fp32
+  char* gp_ws = nullptr;
+  size_t gp_bytes = 0;            // of one layer, [Mmax*O, padded]
   int num_cu = 0;                 // compute units of the device (stream-K workgroup count)
   size_t off_skpart = 0;          // stream-K partial tiles of the contraction
   size_t off_fpart = 0;           // fp64 split-K partials of the small-batch forward
@@ -421,7 +423,7 @@ static void plan_fcn(ntk_handle* h) {
       h->off_ws[l] = take((size_t)pair_stats_floats(h->dims[l + 1], h->dims[l]));
     }
     for (int i = 0; i < 2 && L >= 1; ++i) h->off_rmax[i] = take(parts * Mmax * O);
-    for (int i = 0; i < 2 && L >= 2; ++i) h->off_gp[i] = take(Mmax * O * widest);
+    h->gp_bytes = L >= 2 ? align_up(Mmax * O * widest * 4) : 0;
   }
   for (int l = 0; l <= L; ++l) h->off_gram[l] = take((size_t)h->max_n1 * h->max_n2);
   if (h->lean) {   // the full theta only: no stream-K, no split forward, no one-output variants
@@ -858,9 +860,11 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
   const bool full = !logit && !trace && !diag;
   const bool pair = h->pair && !jc && L >= 1 && fcn_pair_pays(h, M, Oe, full ? (sym ? 0.5 : 1.0) * n1 * n2 : 0.0) &&
                     (full ? ntk_fcn_pair_ok((long long)n1 * O, (long long)n2 * O, L, sym ? 1 : 0, h->num_cu, true)
-                          : L >= 2);
+                          : L >= 2 && h->gp_ws);
   auto I = [&](size_t off) { return reinterpret_cast<int*>(h->ws + off); };
-  auto Gp = [&](int l) { return full ? F(h->off_G[l]) : F(h->off_gp[l & 1]); };
+  auto Gp = [&](int l) {
+    return full ? F(h->off_G[l]) : reinterpret_cast<float*>(h->gp_ws + (l & 1) * h->gp_bytes);
+  };
   const size_t ge_ld = ((size_t)h->max_n1 + h->max_n2) * O;
   auto Ge = [&](int l) { return I(h->off_ge) + l * ge_ld; };
   int gparts[2] = {1, 1};   // parts of the row maxima of the layer above, per half
@@ -2271,6 +2275,7 @@ extern "C" int ntk_free(ntk_handle* h) {
   if (h->ws) (void)hipFree(h->ws);
   destroy_sync_objects(h);
   if (h->jc_ws) (void)hipFree(h->jc_ws);
+  if (h->gp_ws) (void)hipFree(h->gp_ws);
   if (h->vp_ws) (void)hipFree(h->vp_ws);
   delete h;
   return NTK_OK;
@@ -2278,6 +2283,16 @@ extern "C" int ntk_free(ntk_handle* h) {
 
 extern "C" const char* ntk_last_error(const ntk_handle* h) {
   return h ? h->err.c_str() : g_init_error.c_str();
+}
+
+// The variants' pair-row buffers; without them (no memory, or not asked for yet) the variants'
+// backward stays on fp32 rows.
+static void ensure_variant_pairs(ntk_handle* h) {
+  if (h->cnn || !h->pair || h->gp_ws || !h->gp_bytes) return;
+  if (hipMalloc((void**)&h->gp_ws, 2 * h->gp_bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    h->gp_ws = nullptr;
+  }
 }
 
 extern "C" int ntk_set_option(ntk_handle* h, int option, int value) {
@@ -2297,6 +2312,7 @@ extern "C" int ntk_set_option(ntk_handle* h, int option, int value) {
     if (value != NTK_OUTPUT_FULL && value != NTK_OUTPUT_TRACE && value != NTK_OUTPUT_LOGIT)
       return fail(h, NTK_E_ARG, "NTK_OPT_OUTPUT takes NTK_OUTPUT_FULL, _TRACE or _LOGIT");
     h->opt_output = value;
+    if (value != NTK_OUTPUT_FULL) ensure_variant_pairs(h);
     return NTK_OK;
   }
   if (option == NTK_OPT_LOGIT) {
@@ -2324,6 +2340,7 @@ extern "C" int ntk_set_option(ntk_handle* h, int option, int value) {
     if (value != NTK_BATCH_FULL && value != NTK_BATCH_DIAGONAL)
       return fail(h, NTK_E_ARG, "NTK_OPT_BATCH takes NTK_BATCH_FULL or NTK_BATCH_DIAGONAL");
     h->opt_batch = value;
+    if (value != NTK_BATCH_FULL) ensure_variant_pairs(h);
     return NTK_OK;
   }
   return fail(h, NTK_E_ARG, "unknown option");
