@@ -1764,8 +1764,23 @@ static int vector_product_fcn(ntk_handle* h, const float* const* params, const f
   const size_t r2 = sym ? 0 : (size_t)n1;   // first row of batch 2 in the stacked arrays
   auto W = [&](int l) { return params[h->param_index[l]]; };
   hipError_t e;
+  // The summand of layer l in the tangent is h1_l theta_c^l^T = h1_l (delta_l^T h2_l)^T, which is also
+  // (h1_l h2_l^T) delta_l: n1 n2 (in + out) multiply-adds through the layer-input Gram (a bias adds 1
+  // to it) instead of (n1 + n2) in out through the weight-space vector, whichever is less in all.
+  // Depth-8 width-2048 FCN, 512 + 512 samples: 2.56 -> 1.92 ms.
+  double by_gram = 0, by_weights = 0;
+  for (int l = 0; l <= L; ++l) {
+    const double din = h->dims[l], dout = h->dims[l + 1];
+    by_gram += (double)n1 * n2 * (din + dout);
+    by_weights += ((double)n1 + n2) * din * dout;
+  }
+  const bool grams = by_gram < by_weights;
   // ---- VJP of batch 2 at v: cotangents delta_l of every pre-activation z_l (delta_L = v)
+  auto reads_w = [&](int l) {
+    return l < L && dense_bwd_w_ok(F(h->off_G[l]), W(l), n2, h->dims[l], h->dims[l + 1]);
+  };
   for (int l = 1; l < L; ++l) {
+    if (reads_w(l)) continue;
     prof_begin(P, s, KC_TRANSPOSE);
     e = launch_transpose(s, W(l), h->dims[l + 1], h->dims[l], F(h->off_Wt[l]));
     prof_end(P, s, KC_TRANSPOSE);
@@ -1781,14 +1796,46 @@ static int vector_product_fcn(ntk_handle* h, const float* const* params, const f
       // delta_{l-1} = (delta_l W_l) * act'(z_{l-1}) on the rows of batch 2
       const float* Wt = l == L ? V(h->vp_off_WLt) : F(h->off_Wt[l]);
       prof_begin(P, s, KC_DENSE_BWD);
-      e = launch_dense_bwd(s, delta(l), Wt, F(h->off_dphi[l - 1]) + r2 * h->dims[l], n2, h->dims[l],
+      if (reads_w(l))
+        e = launch_dense_bwd_w(s, delta(l), W(l), F(h->off_dphi[l - 1]) + r2 * h->dims[l], n2, h->dims[l],
+                               h->dims[l + 1], 1, F(h->off_G[l - 1]));
+      else
+        e = launch_dense_bwd(s, delta(l), Wt, F(h->off_dphi[l - 1]) + r2 * h->dims[l], n2, h->dims[l],
                            h->dims[l + 1], 1, F(h->off_G[l - 1]));
       prof_end(P, s, KC_DENSE_BWD);
       if (e != hipSuccess) return hip_fail(h, e, "VJP backward");
     }
   }
+  // delta_l^T [out, n2] of the Gram form: in the layer's weight-space buffer where it fits
+  auto delta_t = [&](int l) { return n2 <= h->dims[l] ? V(h->vp_off_tc[l]) : V(h->vp_off_dT); };
+  if (grams) {
+    GramBatch gb{};
+    gb.count = L + 1;
+    TransposeBatch tb{};
+    for (int l = 0; l <= L; ++l) {
+      gb.h1[l] = hptr(l);
+      gb.h2[l] = hptr(l) + r2 * h->dims[l];
+      gb.out[l] = F(h->off_gram[l]);
+      gb.K[l] = h->dims[l];
+      gb.beta[l] = h->layers[l].has_bias ? 1.f : 0.f;
+      if (n2 > h->dims[l] || tb.count == kMaxLayers) continue;
+      tb.W[tb.count] = delta(l);
+      tb.Wt[tb.count] = delta_t(l);
+      tb.R[tb.count] = n2;
+      tb.C[tb.count] = h->dims[l + 1];
+      ++tb.count;
+    }
+    prof_begin(P, s, KC_GRAM);
+    e = launch_gram(s, gb, n1, n2, h->num_cu);
+    prof_end(P, s, KC_GRAM);
+    if (e != hipSuccess) return hip_fail(h, e, "layer-input Grams");
+    prof_begin(P, s, KC_TRANSPOSE);
+    e = launch_transpose_batch(s, tb);
+    prof_end(P, s, KC_TRANSPOSE);
+    if (e != hipSuccess) return hip_fail(h, e, "cotangent transposes");
+  }
   // weight-space cotangent: theta_c^l = delta_l^T h2_l, bias part sum_n delta_l[n]
-  for (int l = 0; l <= L; ++l) {
+  for (int l = 0; l <= L && !grams; ++l) {
     const int dout = h->dims[l + 1], din = h->dims[l];
     prof_begin(P, s, KC_TRANSPOSE);
     e = launch_transpose(s, delta(l), n2, dout, V(h->vp_off_dT));
@@ -1819,12 +1866,18 @@ static int vector_product_fcn(ntk_handle* h, const float* const* params, const f
   float* tnext = V(h->vp_off_t1);
   for (int l = 0; l <= L; ++l) {
     const int dout = h->dims[l + 1], din = h->dims[l];
+    if (grams && (n2 > din || l >= kMaxLayers)) {
+      prof_begin(P, s, KC_TRANSPOSE);
+      e = launch_transpose(s, delta(l), n2, dout, delta_t(l));
+      prof_end(P, s, KC_TRANSPOSE);
+      if (e != hipSuccess) return hip_fail(h, e, "cotangent transposes");
+    }
     GramBatch gb{};
     gb.count = l > 0 ? 2 : 1;
-    gb.h1[0] = hptr(l);
-    gb.h2[0] = V(h->vp_off_tc[l]);
+    gb.h1[0] = grams ? F(h->off_gram[l]) : hptr(l);
+    gb.h2[0] = grams ? delta_t(l) : V(h->vp_off_tc[l]);
     gb.out[0] = V(h->vp_off_ga);
-    gb.K[0] = din;
+    gb.K[0] = grams ? n2 : din;
     gb.beta[0] = 0.f;
     if (l > 0) {
       gb.h1[1] = tcur;
@@ -1837,7 +1890,7 @@ static int vector_product_fcn(ntk_handle* h, const float* const* params, const f
     e = launch_gram(s, gb, n1, dout, h->num_cu);
     prof_end(P, s, KC_GRAM);
     if (e != hipSuccess) return hip_fail(h, e, "JVP products");
-    const float* bias_t = h->layers[l].has_bias ? V(h->vp_off_tcb[l]) : nullptr;
+    const float* bias_t = h->layers[l].has_bias && !grams ? V(h->vp_off_tcb[l]) : nullptr;
     const bool last = l == L;
     prof_begin(P, s, KC_VP_ELEMENTWISE);
     e = launch_jvp_combine(s, l > 0 ? V(h->vp_off_gb) : nullptr, V(h->vp_off_ga), bias_t,
