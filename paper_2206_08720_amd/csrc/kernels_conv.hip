@@ -38,7 +38,9 @@ constexpr int kConvBwdStages = 2, kConvWgStages = 2;
 // the same on pairs (three f16 MFMAs): 64-wide wave tiles, so that a fragment is split into pairs
 // and read from LDS for at least two of the other operand
 using CfgConvBwdPair = TileCfg<256, 64, 32, 64, 64>;       // 4 waves
-using CfgConvBwdPairSmall = TileCfg<128, 64, 32, 32, 64>;  // 4 waves
+using CfgConvBwdPairN = TileCfg<256, 32, 32, 64, 32>;      // at most 32 input channels
+using CfgConvBwdPairSmall = TileCfg<128, 64, 32, 32, 64>;
+using CfgConvBwdPairSmallN = TileCfg<128, 32, 32, 32, 32>;
 using CfgConvWgPair = TileCfg<128, 128, 32, 64, 64>;       // 4 waves
 using CfgConvWgPairN = TileCfg<128, 64, 32, 64, 32>;
 using CfgConvWgPairM = TileCfg<64, 64, 32, 32, 32>;
@@ -908,7 +910,8 @@ __global__ void __launch_bounds__(256) k_conv_prep(ConvPrep p, ConvFactors f, in
     int row = bx * 4 + wave, z = 0;
     while (z < p.count && row >= p.N[z]) row -= p.N[z++];
     if (z >= p.count) return;   // the whole wave
-    const int K = p.K[z], Kp = (int)pair_stride(K);
+    // nine taps of C channels, each padded to Cp
+    const int C = p.C[z], Cp = (int)pair_stride(C), K = 9 * C, Kp = 9 * Cp;
     const float* __restrict__ x = p.Kt[z] + (long long)row * K;
     float m = 0.f;
     for (int k = lane; k < K; k += 64) m = fmaxf(m, fabsf(x[k]));
@@ -920,9 +923,9 @@ __global__ void __launch_bounds__(256) k_conv_prep(ConvPrep p, ConvFactors f, in
       f16x8 hi, lo;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const int k = 8 * g + j;
+        const int tap = 8 * g / Cp, c = 8 * g - tap * Cp + j;
         _Float16 a, b;
-        pair_split(k < K ? ldexpf(x[min(k, K - 1)], -e) : 0.f, a, b);
+        pair_split(c < C ? ldexpf(x[tap * C + min(c, C - 1)], -e) : 0.f, a, b);
         hi[j] = a;
         lo[j] = b;
       }
@@ -940,7 +943,7 @@ __global__ void __launch_bounds__(256) k_conv_prep(ConvPrep p, ConvFactors f, in
   bx -= nzero_blocks;
   if (bx < p.O) {
     float m = 0.f;
-    for (int c = lane; c < p.C; c += 64) m = fmaxf(m, fabsf(p.Wd[(long long)bx * p.C + c]));
+    for (int c = lane; c < p.Cl; c += 64) m = fmaxf(m, fabsf(p.Wd[(long long)bx * p.Cl + c]));
 #pragma unroll
     for (int q = 32; q; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
     for (int i = threadIdx.x; i < p.M; i += 256) p.gseed[(long long)i * p.O + bx] = m * p.seed_scale;
@@ -975,22 +978,32 @@ hipError_t launch_conv_prep(hipStream_t s, const ConvPrep& p, const ConvFactors&
   return hipGetLastError();
 }
 
-// Largest magnitude of each image of several layer inputs: workgroup (image, input).
-template <bool VEC>
+// Largest magnitude of each image of several layer inputs: workgroup (image, input), eight loads in
+// flight per thread.
 __global__ void __launch_bounds__(256) k_conv_max(ConvMax b) {
   __shared__ float red[4];
   const int z = blockIdx.y;
   const int n = b.plane[z];
   const float* __restrict__ x = b.x[z] + (long long)blockIdx.x * n;
   float m = 0.f;
-  if (VEC) {
-#pragma unroll 4
-    for (int i = threadIdx.x; i < n / 4; i += 256) {
-      const f32x4 v = reinterpret_cast<const f32x4*>(x)[i];
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+  if (n % 4 == 0 && (reinterpret_cast<uintptr_t>(b.x[z]) & 15) == 0) {
+    const f32x4* __restrict__ x4 = reinterpret_cast<const f32x4*>(x);
+    for (int i = threadIdx.x; i < n / 4; i += 2048) {
+      f32x4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = x4[min(i + 256 * u, n / 4 - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        m = fmaxf(m, fmaxf(fmaxf(fabsf(v[u][0]), fabsf(v[u][1])), fmaxf(fabsf(v[u][2]), fabsf(v[u][3]))));
     }
   } else {
-    for (int i = threadIdx.x; i < n; i += 256) m = fmaxf(m, fabsf(x[i]));
+    for (int i = threadIdx.x; i < n; i += 2048) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = x[min(i + 256 * u, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) m = fmaxf(m, fabsf(v[u]));
+    }
   }
 #pragma unroll
   for (int q = 32; q; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
@@ -1001,12 +1014,7 @@ __global__ void __launch_bounds__(256) k_conv_max(ConvMax b) {
 
 hipError_t launch_conv_max(hipStream_t s, const ConvMax& m) {
   if (m.count <= 0 || m.M <= 0) return hipSuccess;
-  bool v = true;
-  for (int z = 0; z < m.count; ++z) v = v && m.plane[z] % 4 == 0 && aligned16(m.x[z]);
-  if (v)
-    k_conv_max<true><<<dim3(m.M, m.count), dim3(256), 0, s>>>(m);
-  else
-    k_conv_max<false><<<dim3(m.M, m.count), dim3(256), 0, s>>>(m);
+  k_conv_max<<<dim3(m.M, m.count), dim3(256), 0, s>>>(m);
   return hipGetLastError();
 }
 
@@ -1099,7 +1107,8 @@ k_conv_bwd_dma(DmaPatches<Cfg::BM, Cfg::WAVES> pa, DmaRowMajor<Cfg::BN, Cfg::WAV
 // are row shifts of the LDS reads, and a tap outside the image reads a row of zeros.  The kernel
 // (pair rows) streams through two LDS stages, 32 k at a time.  1280 images of 32 x 32 x 64:
 // 788 us with the fp32 MFMA, 408 us with the cotangents gathered and split per tap (VALU beside
-// the MFMAs), this form 327 us.
+// the MFMAs), this form 327 us.  Any number of channels: they are padded with zeros to a multiple
+// of 32 on the way into LDS (and in the kernel's pair rows); VEC: Cg % 4 == 0, 16-byte loads.
 constexpr int kHaloMaxW = 63;
 template <class Cfg>
 constexpr int halo_rows(int W) {
@@ -1114,7 +1123,7 @@ template <class Cfg>
 static int halo_smem_bytes(int W) {
   return ((halo_rows<Cfg>(W) + 1) * 32 + 2 * Cfg::BN * 32) * 4;
 }
-template <class Cfg>
+template <class Cfg, bool VEC>
 __global__ void __launch_bounds__(Cfg::THREADS, 2 * Cfg::THREADS / 256)
 k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, DmaRowMajor<Cfg::BN, Cfg::WAVES> pb,
                 ConvPairBwd pr, const float* __restrict__ dphi, int R, int N, FastDiv fOD, FastDiv fD,
@@ -1130,7 +1139,7 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
   const int HR = halo_rows<Cfg>(W);
   float* Bs = smem + (HR + 1) * 32;
   constexpr int NT = halo_tasks<Cfg>();
-  const int ncb = Cg / 32, nk = 9 * ncb;
+  const int ncb = (Cg + 31) / 32, nk = 9 * ncb;
   // staging: task t = row t / 4 of the widened run, channels 8 (t % 4) .. + 7 of the block.  Rows
   // outside the batch are read from a clamped address; no tap inside an image reaches them.
   const float* src[NT];
@@ -1139,15 +1148,28 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
   for (int i = 0; i < NT; ++i) {
     const int t = threadIdx.x + i * Cfg::THREADS;
     const int q = min(max(m0 - (W + 1) + min(t >> 2, HR - 1), 0), R - 1);
-    src[i] = G + (long long)q * Cg + 8 * (t & 3);
+    src[i] = G + (long long)q * Cg;
     sf[i] = pair_factor(pair_row_exp(pr.gmax[fD.div(q)] * fac));
   }
   f32x4 st[NT][2];
   auto fetch = [&](int cb) {
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
-      st[i][0] = *reinterpret_cast<const f32x4*>(src[i] + cb * 32);
-      st[i][1] = *reinterpret_cast<const f32x4*>(src[i] + cb * 32 + 4);
+      const int c0 = cb * 32 + 8 * (threadIdx.x & 3);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int c = c0 + 4 * u;
+        if (VEC) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(src[i] + min(c, Cg - 4));
+          st[i][u] = c < Cg ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float v = src[i][min(c + k, Cg - 1)];
+            st[i][u][k] = c + k < Cg ? v : 0.f;
+          }
+        }
+      }
     }
   };
   auto stage = [&]() {
@@ -1233,7 +1255,7 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
       tap1 = 0;
       ++cb1;
     }
-    if (kt + 1 < nk) pb.template issue<Cfg::WAVES>(tap1 * Cg + cb1 * 32, Bs + (S ^ 1) * Cfg::BN * 32, wave, lane);
+    if (kt + 1 < nk) pb.template issue<Cfg::WAVES>((tap1 * ncb + cb1) * 32, Bs + (S ^ 1) * Cfg::BN * 32, wave, lane);
     if (tap == 0 && cb + 1 < ncb) fetch(cb + 1);
 #pragma unroll
     for (int q = 0; q + 1 < 2 * Cfg::FM; ++q) {
@@ -1324,38 +1346,47 @@ static hipError_t conv_bwd_dma_cfg(hipStream_t s, const float* G, int images, in
   return hipGetLastError();
 }
 
-template <class Cfg>
+template <class Cfg, bool VEC>
 static hipError_t conv_bwd_pair_cfg(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
                                     const ConvPairBwd& pr, int Cin, const float* dphi, float* out, float* gmax) {
-  const int D = H * W;
+  const int D = H * W, Kd = 9 * (int)pair_stride(Cg);
   int R;
   if (!to_int((long long)images * O * D, R)) return hipErrorInvalidValue;
   const int tn = cdiv(Cin, Cfg::BN), tm = cdiv(R, Cfg::BM);
-  DmaRowMajor<Cfg::BN, Cfg::WAVES> pb{pr.Kp, 9 * Cg, Cin};
-  hipError_t e = hipFuncSetAttribute((const void*)k_conv_bwd_pair<Cfg>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     halo_smem_bytes<Cfg>(kHaloMaxW));
+  DmaRowMajor<Cfg::BN, Cfg::WAVES> pb{pr.Kp, Kd, Cin};
+  hipError_t e = hipFuncSetAttribute((const void*)k_conv_bwd_pair<Cfg, VEC>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, halo_smem_bytes<Cfg>(kHaloMaxW));
   if (e != hipSuccess) return e;
-  k_conv_bwd_pair<Cfg><<<dim3(tm * tn), dim3(Cfg::THREADS), halo_smem_bytes<Cfg>(W), s>>>(
+  k_conv_bwd_pair<Cfg, VEC><<<dim3(tm * tn), dim3(Cfg::THREADS), halo_smem_bytes<Cfg>(W), s>>>(
       G, H, W, Cg, FastDiv((uint32_t)W), pb, pr, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn,
       gmax);
   return hipGetLastError();
 }
 
-// whether the cotangent backward of this layer takes the pair form
-bool conv_bwd_pair_ok(const float* G, const float* Kp, int W, int Cg) {
-  return Cg % 32 == 0 && W <= kHaloMaxW && aligned16(G) && aligned16(Kp) && dma_span_ok(9LL * Cg, 9LL * Cg, 256);
+// whether the cotangent backward of a layer takes the pair form
+bool conv_bwd_pair_ok(int W, int Cg) {
+  const long long Kd = 9 * pair_stride(Cg);
+  return W <= kHaloMaxW && dma_span_ok(Kd, Kd, 256);
+}
+
+static hipError_t conv_bwd_pair(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
+                                const ConvPairBwd& pr, int Cin, const float* dphi, float* out, float* gmax) {
+  const bool vec = Cg % 4 == 0 && aligned16(G);
+  auto go = [&](auto cfg_tag) {
+    using Cfg = decltype(cfg_tag);
+    return vec ? conv_bwd_pair_cfg<Cfg, true>(s, G, images, O, H, W, Cg, pr, Cin, dphi, out, gmax)
+               : conv_bwd_pair_cfg<Cfg, false>(s, G, images, O, H, W, Cg, pr, Cin, dphi, out, gmax);
+  };
+  // few rows: 128-row tiles, for more workgroups; few channels: 32 columns
+  const bool few = (long long)cdiv((long long)images * O * H * W, 256) * cdiv(Cin, 64) < kConvFewTiles;
+  if (Cin <= 32) return few ? go(CfgConvBwdPairSmallN{}) : go(CfgConvBwdPairN{});
+  return few ? go(CfgConvBwdPairSmall{}) : go(CfgConvBwdPair{});
 }
 
 hipError_t launch_conv_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
                            const float* Kt, int Cin, const float* dphi, float* out, const ConvPairBwd* pair,
                            float* gmax) {
-  if (pair && conv_bwd_pair_ok(G, pair->Kp, W, Cg)) {
-    const long long tiles =
-        (long long)cdiv((long long)images * O * H * W, CfgConvBwdPair::BM) * cdiv(Cin, CfgConvBwdPair::BN);
-    if (tiles < kConvFewTiles)
-      return conv_bwd_pair_cfg<CfgConvBwdPairSmall>(s, G, images, O, H, W, Cg, *pair, Cin, dphi, out, gmax);
-    return conv_bwd_pair_cfg<CfgConvBwdPair>(s, G, images, O, H, W, Cg, *pair, Cin, dphi, out, gmax);
-  }
+  if (pair) return conv_bwd_pair(s, G, images, O, H, W, Cg, *pair, Cin, dphi, out, gmax);
   if (conv_dma_ok(G, (long long)images * O * H * W * Cg, W, Cg, Kt)) {
     const long long tiles = (long long)cdiv((long long)images * O * H * W, CfgConvBwd::BM) * cdiv(Cin, CfgConvBwd::BN);
     if (tiles < kConvFewTiles) return conv_bwd_dma_cfg<CfgConv>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, gmax);
@@ -1483,15 +1514,19 @@ k_conv_wgrad_dma(const float* __restrict__ G, const float* __restrict__ h, int O
 // row (the writes of eight threads) both fall in eight distinct bank groups.
 __device__ __forceinline__ int wg_swz(int r, int c) { return c ^ ((r >> 2) & 7) ^ (((r >> 1) & 1) << 2); }
 
-template <class Cfg, bool PW, bool AL>
+// VA, VB: C % 4 == 0, Cin % 4 == 0 with aligned operands, one 16-byte load per pixel; otherwise the
+// four rows of a task have addresses (and taps) of their own.
+template <class Cfg, bool PW, bool AL, bool VA, bool VB>
 __global__ void __launch_bounds__(Cfg::THREADS, 2 * Cfg::THREADS / 256)
 k_conv_wgrad_pair(const float* __restrict__ G, const float* __restrict__ h, ConvPairWgrad pr, int O, int H, int W, int C,
                   int Cin, FastDiv fC, FastDiv fW, FastDiv fCin, int Cst, float* __restrict__ J, long long ldJ,
                   long long off, int tiles_m, int tiles_n, int samples) {
-  static_assert(Cfg::BM + Cfg::BN <= Cfg::THREADS, "one staging task per thread");
+  static_assert(Cfg::BM + Cfg::BN <= Cfg::THREADS && Cfg::BM % 64 == 0, "one staging task per thread, per wave one operand");
+  static_assert(!AL || (VA && VB), "the aligned form loads vectors");
   extern __shared__ f32x4 wg_lds[];   // 16-byte aligned
   float* smem = reinterpret_cast<float*>(wg_lds);
   constexpr int AF = Cfg::BM * 32, STAGE = (Cfg::BM + Cfg::BN) * 32;
+  constexpr int NR = VA && VB ? 1 : 4;       // addresses per task
   int s, t;
   if (!xcd_sample_tile(blockIdx.x, tiles_m * tiles_n, samples, s, t)) return;
   const int D = H * W, nk = (D + 31) / 32;
@@ -1509,64 +1544,60 @@ k_conv_wgrad_pair(const float* __restrict__ G, const float* __restrict__ h, Conv
   const int eh = pair_row_exp(pr.hmax[s]);
   // staging task of this thread: 4 rows (quad q) x 8 pixels (group g) of operand A (the first BM
   // threads) or B.  Byte offsets through a buffer resource that starts W + 1 pixels before the
-  // sample for the patches; a pixel outside the sample or the image takes an offset past its end,
-  // which reads zeros.
-  const bool is_b = threadIdx.x >= Cfg::BM;
+  // sample for the patches; a pixel outside the sample or the image, or a row past the operand,
+  // takes an offset past its end, which reads zeros.
+  const bool is_b = __builtin_amdgcn_readfirstlane(threadIdx.x >= Cfg::BM ? 1 : 0) != 0;
   const int task = threadIdx.x - (is_b ? Cfg::BM : 0);
   const int nq = (is_b ? Cfg::BN : Cfg::BM) / 4;
   const int q = task % nq, g = task / nq;
   const bool active = g < 4;
   const int row = 4 * q;                       // in the tile
   const int Ct = is_b ? Cin : C;               // floats between two pixels
-  int base, dy = 0, dx = 0;
-  bool in_rows;
-  float sf;
-  if (!is_b) {
-    const int r = m0 + row, rc = min(r, O * C - 4), o = (int)fC.div(rc);
-    base = (o * D * C + (rc - o * C)) * 4;
-    in_rows = r < O * C;
-    sf = pair_factor(row_exp(rc));
-  } else {
-    const int r = n0 + row, rc = min(r, KC - 4);
-    const int tap = PW ? 0 : (int)fCin.div(rc), ci = rc - tap * Cin;
-    if (!PW) {
-      const int kh = (tap * 11) >> 5;
-      dy = kh - 1;
-      dx = tap - 3 * kh - 1;
+  const bool vec = is_b ? VB : VA;
+  int base[NR], dy[NR], dx[NR];
+  bool in_rows[NR];
+  float sf[4];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    dy[i] = dx[i] = 0;
+    if (!is_b) {
+      const int r = m0 + row + i, rc = min(r, O * C - (vec ? 4 : 1)), o = (int)fC.div(rc);
+      base[i] = (o * D * C + (rc - o * C)) * 4;
+      in_rows[i] = r < O * C;
+    } else {
+      const int r = n0 + row + i, rc = min(r, KC - (vec ? 4 : 1));
+      const int tap = PW ? 0 : (int)fCin.div(rc), ci = rc - tap * Cin;
+      if (!PW) {
+        const int kh = (tap * 11) >> 5;
+        dy[i] = kh - 1;
+        dx[i] = tap - 3 * kh - 1;
+      }
+      base[i] = ((PW ? 0 : dy[i] * W + dx[i] + W + 1) * Cin + ci) * 4;
+      in_rows[i] = r < KC;
     }
-    base = (((PW ? 0 : dy * W + dx + W + 1)) * Cin + ci) * 4;
-    in_rows = r < KC;
-    sf = pair_factor(eh);
   }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) sf[i] = pair_factor(is_b ? eh : row_exp(m0 + row + (vec ? 0 : i)));
   const float* p0 = is_b ? h + (long long)s * D * Cin - (PW ? 0 : (long long)(W + 1) * Cin) : G + (long long)s * O * D * C;
   const uint32_t span = (uint32_t)((is_b ? (long long)(D + (PW ? 0 : W + 1)) * Cin : (long long)O * D * C) * 4);
-  // the waves of the two operands differ: both resources are wave-uniform
-  const __amdgpu_buffer_rsrc_t rsrc = buffer_rsrc(
-      reinterpret_cast<const void*>(((uint64_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)p0 >> 32)) << 32) |
-                                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint64_t)p0)),
-      __builtin_amdgcn_readfirstlane((int)span));
-  f32x4 st[8];
-  auto fetch = [&](int kt) {
-    const int p = kt * 32 + 8 * g;
-    unsigned bad = (in_rows && active) ? 0u : 0xFFu;   // pixels of the group read as zeros
-    if (AL && !PW) {   // the K tile is a run of one image row
-      const int y = (int)fW.div(kt * 32), x = p - y * W;
-      if (is_b) {
-        if ((unsigned)(y + dy) >= (unsigned)H) bad = 0xFFu;
-        if (x == 0 && dx < 0) bad |= 1u;
-        if (x + 8 == W && dx > 0) bad |= 0x80u;
-      }
-    } else if (!AL) {
-      int y = 0, x = 0;
+  const __amdgpu_buffer_rsrc_t rsrc = buffer_rsrc(p0, span);   // wave-uniform: is_b is
+  // the lambdas are forced inline: called as functions they would keep the arrays in scratch memory
+  float st[4][8];   // [row][pixel]
+  // the pixels of this thread's group that a row with tap (dyr, dxr) reads as zeros
+  auto outside = [&](bool in_row, int dyr, int dxr, int p, int y, int x) __attribute__((always_inline)) {
+    unsigned bad = (in_row && active) ? 0u : 0xFFu;
+    if (AL) {   // the K tile is whole and (patches) a run of one image row
       if (is_b && !PW) {
-        y = (int)fW.div(min(p, D - 1));
-        x = p - y * W;
+        if ((unsigned)(y + dyr) >= (unsigned)H) bad = 0xFFu;
+        if (x == 0 && dxr < 0) bad |= 1u;
+        if (x + 8 == W && dxr > 0) bad |= 0x80u;
       }
+    } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         bool ok = p + j < D;
         if (is_b && !PW) {
-          ok = ok && (unsigned)(y + dy) < (unsigned)H && (unsigned)(x + dx) < (unsigned)W;
+          ok = ok && (unsigned)(y + dyr) < (unsigned)H && (unsigned)(x + dxr) < (unsigned)W;
           if (++x == W) {
             x = 0;
             ++y;
@@ -1575,25 +1606,50 @@ k_conv_wgrad_pair(const float* __restrict__ G, const float* __restrict__ h, Conv
         bad |= ok ? 0u : (1u << j);
       }
     }
-    const uint32_t voff = (uint32_t)base + (uint32_t)(p * Ct) * 4u;
+    return bad;
+  };
+  auto fetch = [&](int kt) __attribute__((always_inline)) {
+    const int p = kt * 32 + 8 * g;
+    int y = 0, x = 0;
+    if (is_b && !PW) {
+      y = (int)fW.div(AL ? kt * 32 : min(p, D - 1));
+      x = p - y * W;
+    }
+    if (vec) {
+      const unsigned bad = outside(in_rows[0], dy[0], dx[0], p, y, x);
+      const uint32_t voff = (uint32_t)base[0] + (uint32_t)(p * Ct) * 4u;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t o = ((bad >> j) & 1u) ? kDmaPastEnd : voff + (uint32_t)(j * Ct) * 4u;
-      st[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, o, 0, 0));
+      for (int j = 0; j < 8; ++j) {
+        const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                      rsrc, ((bad >> j) & 1u) ? kDmaPastEnd : voff + (uint32_t)(j * Ct) * 4u,
+                                                      0, 0));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st[i][j] = v[i];
+      }
+    } else {
+      static_for<0, NR>([&](auto it) __attribute__((always_inline)) {
+        constexpr int i = decltype(it)::value;
+        const unsigned bad = outside(in_rows[i], dy[i], dx[i], p, y, x);
+        const uint32_t voff = (uint32_t)base[i] + (uint32_t)(p * Ct) * 4u;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          st[i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                   rsrc, ((bad >> j) & 1u) ? kDmaPastEnd : voff + (uint32_t)(j * Ct) * 4u, 0, 0));
+      });
     }
   };
-  auto stage = [&](float* dst) {
+  auto stage = [&](float* dst) __attribute__((always_inline)) {
     if (!active) return;
     float* d = dst + (is_b ? AF : 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const f32x4 x = {st[0][i], st[1][i], st[2][i], st[3][i]}, y = {st[4][i], st[5][i], st[6][i], st[7][i]};
+    static_for<0, 4>([&](auto it) __attribute__((always_inline)) {
+      constexpr int i = decltype(it)::value;
+      const f32x4 x = {st[i][0], st[i][1], st[i][2], st[i][3]}, y = {st[i][4], st[i][5], st[i][6], st[i][7]};
       f16x8 hi, lo;
-      pair_split8(x, y, sf, hi, lo);
+      pair_split8(x, y, sf[i], hi, lo);
       const int r = row + i;
       *reinterpret_cast<f16x8*>(&d[r * 32 + (wg_swz(r, 2 * g) << 2)]) = hi;
       *reinterpret_cast<f16x8*>(&d[r * 32 + (wg_swz(r, 2 * g + 1) << 2)]) = lo;
-    }
+    });
   };
   f32x16 acc[Cfg::FM][Cfg::FN];
   zero_acc<Cfg>(acc);
@@ -1694,6 +1750,36 @@ static hipError_t conv_wgrad_any(hipStream_t s, const float* G, const float* h, 
   if ((long long)8 * ((images + 7) / 8) * cdiv(KC, CfgConv::BN) * cdiv((long long)O * C, CfgConv::BM) >=
       (1LL << 31))
     return hipErrorInvalidValue;
+  const bool spans = (long long)O * H * W * C * 4 < (1LL << 31) && ((long long)H * W + W + 1) * Cin * 4 < (1LL << 31);
+  if (pair && spans) {
+    const bool va = C % 4 == 0 && aligned16(G), vb = Cin % 4 == 0 && aligned16(h);
+    const bool al = va && vb && (PW ? (H * W) % 32 == 0 : W % 32 == 0);
+    auto go = [&](auto cfg_tag, auto al_tag, auto va_tag, auto vb_tag) -> hipError_t {
+      using Cfg = decltype(cfg_tag);
+      constexpr bool AL = decltype(al_tag)::value, VA = decltype(va_tag)::value, VB = decltype(vb_tag)::value;
+      const int tn = cdiv(KC, Cfg::BN), tm = cdiv(O * C, Cfg::BM);
+      constexpr int bytes = gemm_dma_smem_bytes<Cfg, 2>();
+      hipError_t e = hipFuncSetAttribute((const void*)k_conv_wgrad_pair<Cfg, PW, AL, VA, VB>,
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+      if (e != hipSuccess) return e;
+      k_conv_wgrad_pair<Cfg, PW, AL, VA, VB><<<dim3(wgrad_grid(tm * tn, images)), dim3(Cfg::THREADS), bytes, s>>>(
+          G, h, *pair, O, H, W, C, Cin, FastDiv((uint32_t)C), FastDiv((uint32_t)W), FastDiv((uint32_t)Cin), Cst, J, ldJ,
+          off, tm, tn, images);
+      return hipGetLastError();
+    };
+    auto gov = [&](auto cfg_tag) -> hipError_t {
+      using T = std::true_type;
+      using F = std::false_type;
+      if (al) return go(cfg_tag, T{}, T{}, T{});
+      if (va) return vb ? go(cfg_tag, F{}, T{}, T{}) : go(cfg_tag, F{}, T{}, F{});
+      return vb ? go(cfg_tag, F{}, F{}, T{}) : go(cfg_tag, F{}, F{}, F{});
+    };
+    // few columns (the 3-channel first layer, a pointwise layer): half-width tiles; few rows (one
+    // output, as for the folded last convolution): 64 x 64, for enough workgroups
+    if (KC <= 64) return gov(CfgConvWgPairN{});
+    if (O * C <= 64) return gov(CfgConvWgPairM{});
+    return gov(CfgConvWgPair{});
+  }
   // direct-to-LDS: one sample's cotangents and layer input each within a buffer resource
   if (C % 4 == 0 && Cin % 4 == 0 && aligned16(G) && aligned16(h) && (long long)O * H * W * C * 4 < (1LL << 31) &&
       (long long)H * W * Cin * 4 < (1LL << 31)) {
@@ -1712,28 +1798,6 @@ static hipError_t conv_wgrad_any(hipStream_t s, const float* G, const float* h, 
       return hipGetLastError();
     };
     const bool al = PW ? (H * W) % 32 == 0 : W % 32 == 0;
-    if (pair) {
-      auto gop = [&](auto cfg_tag, auto al_tag) -> hipError_t {
-        using Cfg = decltype(cfg_tag);
-        constexpr bool AL = decltype(al_tag)::value;
-        const int tn = cdiv(KC, Cfg::BN), tm = cdiv(O * C, Cfg::BM);
-        constexpr int bytes = gemm_dma_smem_bytes<Cfg, 2>();
-        hipError_t e = hipFuncSetAttribute((const void*)k_conv_wgrad_pair<Cfg, PW, AL>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        if (e != hipSuccess) return e;
-        k_conv_wgrad_pair<Cfg, PW, AL><<<dim3(wgrad_grid(tm * tn, images)), dim3(Cfg::THREADS), bytes, s>>>(
-            G, h, *pair, O, H, W, C, Cin, FastDiv((uint32_t)C), FastDiv((uint32_t)W), FastDiv((uint32_t)Cin), Cst, J,
-            ldJ, off, tm, tn, images);
-        return hipGetLastError();
-      };
-      // few columns (the 3-channel first layer, a pointwise layer): half-width tiles; few rows (one
-      // output, as for the folded last convolution): 64 x 64, for enough workgroups
-      if (KC <= 64)
-        return al ? gop(CfgConvWgPairN{}, std::true_type{}) : gop(CfgConvWgPairN{}, std::false_type{});
-      if (O * C <= 64)
-        return al ? gop(CfgConvWgPairM{}, std::true_type{}) : gop(CfgConvWgPairM{}, std::false_type{});
-      return al ? gop(CfgConvWgPair{}, std::true_type{}) : gop(CfgConvWgPair{}, std::false_type{});
-    }
     // at most 64 rows (O C: one output, as for the folded last convolution): 64 x 64 tiles
     if (O * C <= 64)
       return al ? go(CfgConvWgSmall{}, std::true_type{}) : go(CfgConvWgSmall{}, std::false_type{});

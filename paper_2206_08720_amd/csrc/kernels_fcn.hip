@@ -1193,14 +1193,20 @@ __device__ __forceinline__ void sk_tile_coords(int t, int symmetric, int tiles_m
   if (symmetric && Cfg::BM == 2 * Cfg::BN) tri2_index(t, tiles_n, tm, tn);
   else tile_coords(t, symmetric, tiles_m, tiles_n, tm, tn);
 }
-// The symmetric schedule's writes of element (r, s): itself from the diagonal of BN x BN blocks up,
-// its mirror from above the diagonal.
+// The symmetric schedule's writes of element (r, s) of the tile at (m0, n0): itself and, off the
+// diagonal, its mirror.  A two-high tile is two blocks of BN x BN: itself from the diagonal of blocks
+// up, the mirror from above it.
 template <class Cfg>
-__device__ __forceinline__ void fcn_write(float* __restrict__ theta, int N1, int N2, int O, int symmetric, int r, int s,
-                                          int n1, int o1, int n2, int o2, float v) {
-  const int br = r / Cfg::BN, bs = s / Cfg::BN;   // powers of two
-  if (!symmetric || br <= bs) theta[(((long long)n1 * N2 + n2) * O + o1) * O + o2] = v;
-  if (symmetric && br < bs) theta[(((long long)n2 * N1 + n1) * O + o2) * O + o1] = v;
+__device__ __forceinline__ void fcn_write(float* __restrict__ theta, int N1, int N2, int O, int symmetric, int m0, int n0,
+                                          int r, int s, int n1, int o1, int n2, int o2, float v) {
+  bool direct = true, mirror = symmetric && m0 != n0;
+  if constexpr (Cfg::BM != Cfg::BN) {
+    const int br = r / Cfg::BN, bs = s / Cfg::BN;   // powers of two
+    direct = !symmetric || br <= bs;
+    mirror = symmetric && br < bs;
+  }
+  if (direct) theta[(((long long)n1 * N2 + n2) * O + o1) * O + o2] = v;
+  if (mirror) theta[(((long long)n2 * N1 + n1) * O + o2) * O + o1] = v;
 }
 // Final epilogue of a tile: add the readout summand, write theta (and its mirror).
 template <class Cfg>
@@ -1216,7 +1222,7 @@ __device__ __forceinline__ void fcn_tile_out(f32x16 (&tot)[Cfg::FM][Cfg::FN], co
       const int n1 = (int)fO.div(r), o1 = r - n1 * O;
       const int n2 = (int)fO.div(s), o2 = s - n2 * O;
       if (o1 == o2) v += rscale * smem[(n1 - n1lo) * S2 + (n2 - n2lo)];
-      fcn_write<Cfg>(theta, N1, N2, O, symmetric, r, s, n1, o1, n2, o2, v);
+      fcn_write<Cfg>(theta, N1, N2, O, symmetric, m0, n0, r, s, n1, o1, n2, o2, v);
     }
   });
   __syncthreads();
@@ -1373,7 +1379,7 @@ k_ntk_fcn_fixup(int L, const float* __restrict__ gram_readout, float rscale, int
       const int n2 = (int)fO.div(s), o2 = s - n2 * O;
       float w = vals[k];
       if (o1 == o2) w += rscale * gram_readout[(long long)n1 * N2 + n2];
-      fcn_write<Cfg>(theta, N1, N2, O, symmetric, r, s, n1, o1, n2, o2, w);
+      fcn_write<Cfg>(theta, N1, N2, O, symmetric, tm * Cfg::BM, tn * Cfg::BN, r, s, n1, o1, n2, o2, w);
     }
   }
 }

@@ -33,7 +33,7 @@ hipError_t launch_conv_flip_batch(hipStream_t s, const FlipBatch& b);
 struct ConvPairBwd {
   const float* gmax;
   const float* fac;
-  const float* Kp;    // Kt as pair rows [Cin, 9*Cg]
+  const float* Kp;    // Kt as pair rows [Cin, 9 pair_stride(Cg)], the channels of a tap padded
   const int* kexps;   // [Cin]
 };
 struct ConvPairWgrad {
@@ -48,7 +48,7 @@ struct ConvPairWgrad {
 hipError_t launch_conv_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
                            const float* Kt, int Cin, const float* dphi, float* out,
                            const ConvPairBwd* pair = nullptr, float* gmax_out = nullptr);
-bool conv_bwd_pair_ok(const float* G, const float* Kp, int W, int Cg);
+bool conv_bwd_pair_ok(int W, int Cg);
 // J[(s*O + o), off + c*9*Cin + k] = sum_p G[s, o, p, c] patch(h)[s, p, k] for every sample s.
 hipError_t launch_conv_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H,
                              int W, int C, int Cin, float* J, long long ldJ, long long off,
@@ -58,7 +58,7 @@ hipError_t launch_pw_wgrad(hipStream_t s, const float* G, const float* h, int im
                            int W, int C, int Cin, float* J, long long ldJ, long long off,
                            const ConvPairWgrad* pair = nullptr);
 // Everything the pair products of one CNN evaluation need that does not depend on the backward, in
-// one launch: the pair rows of the flipped kernels (rows of K[z] floats at Kt[z], N[z] rows), the
+// one launch: the pair rows of the flipped kernels (N[z] rows of 9 taps of C[z] channels), the
 // largest magnitude of each image of the layer inputs x[j] ([M, plane[j]] -> hmax[j]), the bound
 // of the seed's cotangents (max_c |Wd[o, c]| scale -> gseed[img*O + o]), zeroed maxima
 // [zero, zero + nzero), and per depthwise or scale layer the factor by which its backward can grow
@@ -68,10 +68,10 @@ struct ConvPrep {
   const float* Kt[kMaxLayers];
   float* Kp[kMaxLayers];
   int* kexps[kMaxLayers];
-  int K[kMaxLayers], N[kMaxLayers];
+  int C[kMaxLayers], N[kMaxLayers];
   int count;
-  const float* Wd;
-  int O, C, M;
+  const float* Wd;   // [O, Cl]
+  int O, Cl, M;
   float seed_scale;
   float* gseed;
   float* zero;

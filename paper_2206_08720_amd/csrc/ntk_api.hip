@@ -515,8 +515,8 @@ static void plan_cnn(ntk_handle* h) {
     h->off_Kp.assign(nc, 0);
     h->off_ke.assign(nc, 0);
     for (int l = 1; l < nc; ++l)
-      if (h->layers[l].kind == NTK_CONV3X3_SAME && conv_bwd_pair_ok(nullptr, nullptr, h->bw[l], h->ch[l + 1])) {
-        h->off_Kp[l] = take((size_t)9 * h->ch[l] * h->ch[l + 1]);
+      if (h->layers[l].kind == NTK_CONV3X3_SAME && conv_bwd_pair_ok(h->bw[l], h->ch[l + 1])) {
+        h->off_Kp[l] = take((size_t)9 * h->ch[l] * pair_stride(h->ch[l + 1]));
         h->off_ke[l] = take(h->ch[l]);
       }
     h->off_gmax = take(Mmax * O * nc);
@@ -1277,17 +1277,21 @@ static double inside_out_cost(double pairs, int D, int Cin, int C, int Oe, bool 
 // rows and the images' maxima, 12 us) against the time of the products that have a pair form.
 // 4x4 images, 9 GFLOP: 348 us with pairs, 316 us with the fp32 MFMA (the few workgroups wait on
 // loads either way); one output of 64 32x32 images, 27 GFLOP: 617 against 655 us.
-constexpr double kConvPairMinFlops = 2e10;
+// Channel counts that the direct-to-LDS fp32 kernels do not take (not a multiple of 32 behind a
+// backward, of 4 in a weight-space product) repay pairs far earlier.
+constexpr double kConvPairMinFlops = 2e10, kConvPairMinFlopsRagged = 1e9;
 static bool cnn_pair_pays(const ntk_handle* h, int M, int Oe) {
   double flops = 0;
+  bool ragged = false;
   for (int l = 0; l < h->nc; ++l) {
     const int kind = h->layers[l].kind, cin = h->ch[l], cout = h->ch[l + 1];
     if (kind != NTK_CONV3X3_SAME && kind != NTK_CONV1X1) continue;
     const double f = 2.0 * M * Oe * h->bh[l] * h->bw[l] * weight_cols(h->layers[l], cin);
-    if (cout % 4 == 0 && (cin % 4 == 0 || h->off_xpad)) flops += f;
+    flops += f;
     if (l && h->off_Kp[l]) flops += f;
+    ragged = ragged || cout % 4 != 0 || (l && kind == NTK_CONV3X3_SAME && cout % 32 != 0);
   }
-  return flops >= kConvPairMinFlops;
+  return flops >= (ragged ? kConvPairMinFlopsRagged : kConvPairMinFlops);
 }
 
 static int compute_cnn(ntk_handle* h, const float* const* params, const float* X1, int n1,
@@ -1483,13 +1487,13 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
         cp.Kt[cp.count] = F(h->off_Kt[l]);
         cp.Kp[cp.count] = F(h->off_Kp[l]);
         cp.kexps[cp.count] = I(h->off_ke[l]);
-        cp.K[cp.count] = 9 * h->ch[l + 1];
+        cp.C[cp.count] = h->ch[l + 1];
         cp.N[cp.count] = h->ch[l];
         ++cp.count;
       }
       cp.Wd = Wd;
       cp.O = Oe;
-      cp.C = C;
+      cp.Cl = C;
       cp.M = M;
       cp.seed_scale = act_bound(nc - 1) / (float)(h->bh[nc] * h->bw[nc]);
       cp.gseed = gmax(nc - 1);

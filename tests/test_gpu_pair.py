@@ -114,6 +114,12 @@ CONV_CASES = [
     ("struct 24x20", (24, 20), 3, [(C3, 64, "relu", True), ("dwconv3x3", "erf", True), ("conv1x1", 64, "relu", True),
                                    ("avgpool2",), ("scale", "relu", True), (C3, 64, "relu", True),
                                    ("scale", "erf", False), (C3, 64, "relu", False)], 10, 40, 21),
+    # channels that are no multiple of 32, 4 or anything, scalar loads in each operand's place
+    ("30x26, 24, 47 and 33 channels", (30, 26), 1, [(C3, 24, "erf", True), (C3, 47, "erf", True), ("avgpool2",),
+                                                    (C3, 33, "erf", True)], 7, 31, 18),
+    ("15x15, 20, 45, 36 and pointwise 13", (15, 15), 5, [(C3, 20, "relu", False), (C3, 45, "relu", True),
+                                                         (C3, 36, "relu", False), ("conv1x1", 13, "relu", True),
+                                                         (C3, 17, "relu", False)], 6, 21, 14),
     # small images: many per tile
     ("3x3 images", (3, 3), 5, [(C3, 64, "relu", False), (C3, 64, "erf", True), (C3, 64, "relu", False)], 10, 90, 70),
 ]
