@@ -1274,21 +1274,23 @@ static double inside_out_cost(double pairs, int D, int Cin, int C, int Oe, bool 
 }
 
 // Whether a CNN's backward and weight-space products run on f16 pairs: two more launches (the pair
-// rows and the images' maxima, 12 us) against the time of the products that have a pair form.
-// 4x4 images, 9 GFLOP: 348 us with pairs, 316 us with the fp32 MFMA (the few workgroups wait on
-// loads either way); one output of 64 32x32 images, 27 GFLOP: 617 against 655 us.
+// rows and the images' maxima, 12 us) against the time of the products that have a pair form (the
+// folded last layer's `fold` has no cotangents in it, an inside-out layer no weight-space product).
+// 4x4 images, 5 GFLOP: 348 us with pairs, 316 us with the fp32 MFMA (the few workgroups wait on
+// loads either way); ten outputs of 32 16x16 images, 19 GFLOP: 302 against 348 us.
 // Channel counts that the direct-to-LDS fp32 kernels do not take (not a multiple of 32 behind a
-// backward, of 4 in a weight-space product) repay pairs far earlier.
-constexpr double kConvPairMinFlops = 2e10, kConvPairMinFlopsRagged = 1e9;
-static bool cnn_pair_pays(const ntk_handle* h, int M, int Oe) {
+// backward, of 4 in a weight-space product) repay pairs earlier: 3.5 GFLOP 255 against 241 us,
+// 4.2 GFLOP 272 against 340 us.
+constexpr double kConvPairMinFlops = 1.2e10, kConvPairMinFlopsRagged = 4e9;
+static bool cnn_pair_pays(const ntk_handle* h, int M, int Oe, const std::vector<char>& inside, bool fold) {
   double flops = 0;
   bool ragged = false;
   for (int l = 0; l < h->nc; ++l) {
     const int kind = h->layers[l].kind, cin = h->ch[l], cout = h->ch[l + 1];
     if (kind != NTK_CONV3X3_SAME && kind != NTK_CONV1X1) continue;
-    const double f = 2.0 * M * Oe * h->bh[l] * h->bw[l] * weight_cols(h->layers[l], cin);
-    flops += f;
-    if (l && h->off_Kp[l]) flops += f;
+    const double f = 2.0 * M * h->bh[l] * h->bw[l] * weight_cols(h->layers[l], cin);
+    if (!inside[l]) flops += f * (fold && l == h->nc - 1 ? 1 : Oe);
+    if (l && h->off_Kp[l]) flops += f * Oe;
     ragged = ragged || cout % 4 != 0 || (l && kind == NTK_CONV3X3_SAME && cout % 32 != 0);
   }
   return flops >= (ragged ? kConvPairMinFlopsRagged : kConvPairMinFlops);
@@ -1457,7 +1459,7 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
   std::vector<Bound> bound(nc, Bound{nullptr, nullptr});
   const size_t gm_ld = ((size_t)h->max_n1 + h->max_n2) * O, hm_ld = (size_t)h->max_n1 + h->max_n2;
   auto gmax = [&](int l) { return F(h->off_gmax) + l * gm_ld; };
-  bool cpair = h->cpair && h->opt_method != NTK_METHOD_JACOBIAN && cnn_pair_pays(h, M, Oe);
+  bool cpair = h->cpair && h->opt_method != NTK_METHOD_JACOBIAN && cnn_pair_pays(h, M, Oe, inside, fold);
   if (cpair) {
     ConvFactors cf{};
     int run = 0;

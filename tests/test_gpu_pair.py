@@ -121,7 +121,8 @@ CONV_CASES = [
                                                          (C3, 36, "relu", False), ("conv1x1", 13, "relu", True),
                                                          (C3, 17, "relu", False)], 6, 21, 14),
     # small images: many per tile
-    ("3x3 images", (3, 3), 5, [(C3, 64, "relu", False), (C3, 64, "erf", True), (C3, 64, "relu", False)], 10, 90, 70),
+    ("3x3 images", (3, 3), 5, [(C3, 60, "relu", False), (C3, 60, "erf", True)] + [(C3, 60, "relu", False)] * 4,
+     10, 90, 70),
 ]
 
 
