@@ -1510,6 +1510,8 @@ k_conv_wgrad_dma(const float* __restrict__ G, const float* __restrict__ h, int O
 // eight floats each.  The next K tile's loads are in flight during a tile's MFMAs; two LDS stages.
 // 64 -> 64 channels, 128 x 10 cotangent images of 32 x 32: 555 us with the fp32 MFMA, 415 us with
 // every wave splitting its own fragments, this form 384 us.
+// The first column tile also adds up the bias columns: a pass of their own over 1280 cotangent images of
+// 32 x 32 x 64 took 70 us (1689 us for the biased network of five convolutions, 1830 us with it).
 // Position of 16-byte chunk c of row r: eight consecutive rows (a fragment read) and every fourth
 // row (the writes of eight threads) both fall in eight distinct bank groups.
 __device__ __forceinline__ int wg_swz(int r, int c) { return c ^ ((r >> 2) & 7) ^ (((r >> 1) & 1) << 2); }
@@ -1638,8 +1640,16 @@ k_conv_wgrad_pair(const float* __restrict__ G, const float* __restrict__ h, Conv
       });
     }
   };
+  // the row tile's first column tile also sums its cotangents over the pixels (the bias columns):
+  // they pass through these registers anyway
+  const bool sums = !is_b && tn == 0 && pr.bias >= 0;
+  float rs[4] = {};
   auto stage = [&](float* dst) __attribute__((always_inline)) {
     if (!active) return;
+    if (sums)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        rs[i] += ((st[i][0] + st[i][1]) + (st[i][2] + st[i][3])) + ((st[i][4] + st[i][5]) + (st[i][6] + st[i][7]));
     float* d = dst + (is_b ? AF : 0);
     static_for<0, 4>([&](auto it) __attribute__((always_inline)) {
       constexpr int i = decltype(it)::value;
@@ -1708,6 +1718,18 @@ k_conv_wgrad_pair(const float* __restrict__ G, const float* __restrict__ h, Conv
     tile(kb + 1, std::integral_constant<int, 1>{});
   }
   if (kb < nk) tile(kb, std::integral_constant<int, 0>{});
+  if (tn == 0 && pr.bias >= 0) {   // every wave has left the stages
+    if (sums)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) smem[g * Cfg::BM + row + i] = rs[i];
+    __syncthreads();
+    const int r = m0 + threadIdx.x;
+    if (threadIdx.x < Cfg::BM && r < O * C) {
+      const int o = (int)fC.div(r);
+      J[((long long)s * O + o) * ldJ + pr.bias + (r - o * C)] =
+          (smem[threadIdx.x] + smem[Cfg::BM + threadIdx.x]) + (smem[2 * Cfg::BM + threadIdx.x] + smem[3 * Cfg::BM + threadIdx.x]);
+    }
+  }
 #pragma unroll
   for (int i = 0; i < Cfg::FM; ++i)
 #pragma unroll
@@ -1747,7 +1769,7 @@ static hipError_t conv_wgrad_vec(hipStream_t s, const float* G, const float* h, 
 template <bool PW>
 static hipError_t conv_wgrad_any(hipStream_t s, const float* G, const float* h, int images, int O, int H,
                                  int W, int C, int Cin, float* J, long long ldJ, long long off, int Cst,
-                                 const ConvPairWgrad* pair) {
+                                 const ConvPairWgrad* pair, bool* bias_done) {
   const int KC = (PW ? 1 : 9) * Cin;
   if ((long long)8 * ((images + 7) / 8) * cdiv(KC, CfgConv::BN) * cdiv((long long)O * C, CfgConv::BM) >=
       (1LL << 31))
@@ -1760,6 +1782,7 @@ static hipError_t conv_wgrad_any(hipStream_t s, const float* G, const float* h, 
                                : O * C <= 64 ? (long long)cdiv(KC, CfgConvWgPairM::BN)
                                              : (long long)cdiv(O * C, CfgConvWgPair::BM) * cdiv(KC, CfgConvWgPair::BN);
   if (pair && spans && pair_tiles * images >= kConvWgPairMinGroups) {
+    if (bias_done) *bias_done = pair->bias >= 0;
     const bool va = C % 4 == 0 && aligned16(G), vb = Cin % 4 == 0 && aligned16(h);
     const bool al = va && vb && (PW ? (H * W) % 32 == 0 : W % 32 == 0);
     auto go = [&](auto cfg_tag, auto al_tag, auto va_tag, auto vb_tag) -> hipError_t {
@@ -1820,13 +1843,13 @@ static hipError_t conv_wgrad_any(hipStream_t s, const float* G, const float* h, 
 
 hipError_t launch_conv_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H,
                              int W, int C, int Cin, float* J, long long ldJ, long long off,
-                             const ConvPairWgrad* pair) {
-  return conv_wgrad_any<false>(s, G, h, images, O, H, W, C, Cin, J, ldJ, off, Cin, pair);
+                             const ConvPairWgrad* pair, bool* bias_done) {
+  return conv_wgrad_any<false>(s, G, h, images, O, H, W, C, Cin, J, ldJ, off, Cin, pair, bias_done);
 }
 
 hipError_t launch_pw_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H, int W,
-                           int C, int Cin, float* J, long long ldJ, long long off, const ConvPairWgrad* pair) {
-  return conv_wgrad_any<true>(s, G, h, images, O, H, W, C, Cin, J, ldJ, off, Cin, pair);
+                           int C, int Cin, float* J, long long ldJ, long long off, const ConvPairWgrad* pair, bool* bias_done) {
+  return conv_wgrad_any<true>(s, G, h, images, O, H, W, C, Cin, J, ldJ, off, Cin, pair, bias_done);
 }
 
 // xp [rows, Cp] = x [rows, Cin] with zero channels Cin .. Cp - 1.
@@ -1852,7 +1875,7 @@ bool conv_wgrad_pad_ok(int images, int O, int H, int W, int C, int Cin, const fl
 
 hipError_t launch_conv_wgrad_padded(hipStream_t s, const float* G, const float* h, float* xp, int images, int O,
                                     int H, int W, int C, int Cin, float* J, long long ldJ, long long off, bool pw,
-                                    const ConvPairWgrad* pair) {
+                                    const ConvPairWgrad* pair, bool* bias_done) {
   const int Cp = (Cin + 3) & ~3;
   if (!conv_wgrad_pad_ok(images, O, H, W, C, Cin, G, xp)) return hipErrorInvalidValue;
   const long long rows = (long long)images * H * W;
@@ -1860,8 +1883,8 @@ hipError_t launch_conv_wgrad_padded(hipStream_t s, const float* G, const float* 
       h, rows, Cin, Cp, xp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return pw ? conv_wgrad_any<true>(s, G, xp, images, O, H, W, C, Cp, J, ldJ, off, Cin, pair)
-            : conv_wgrad_any<false>(s, G, xp, images, O, H, W, C, Cp, J, ldJ, off, Cin, pair);
+  return pw ? conv_wgrad_any<true>(s, G, xp, images, O, H, W, C, Cp, J, ldJ, off, Cin, pair, bias_done)
+            : conv_wgrad_any<false>(s, G, xp, images, O, H, W, C, Cp, J, ldJ, off, Cin, pair, bias_done);
 }
 
 // ------------------------------------------------------------------------------ split-K J1 J2^T

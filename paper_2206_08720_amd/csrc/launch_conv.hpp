@@ -41,6 +41,7 @@ struct ConvPairWgrad {
   const float* fac;
   float gconst;
   const float* hmax;  // [images]
+  long long bias;     // column of J of the layer's bias cotangents, sum_p G[s, o, p, c]; -1: none
 };
 // out [images*O, D, Cin] = conv3x3(G [images*O, H, W, Cg], Kt [Cin, 3, 3, Cg]) * dphi [images, D, Cin]
 // (dphi null: the identity).  With gmax_out, gmax_out[img*O + o] (zero before) receives the largest
@@ -49,14 +50,15 @@ hipError_t launch_conv_bwd(hipStream_t s, const float* G, int images, int O, int
                            const float* Kt, int Cin, const float* dphi, float* out,
                            const ConvPairBwd* pair = nullptr, float* gmax_out = nullptr);
 bool conv_bwd_pair_ok(int W, int Cg);
-// J[(s*O + o), off + c*9*Cin + k] = sum_p G[s, o, p, c] patch(h)[s, p, k] for every sample s.
+// J[(s*O + o), off + c*9*Cin + k] = sum_p G[s, o, p, c] patch(h)[s, p, k] for every sample s.  The
+// pair form sums the bias cotangents too (pair->bias); bias_done is then set.
 hipError_t launch_conv_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H,
                              int W, int C, int Cin, float* J, long long ldJ, long long off,
-                             const ConvPairWgrad* pair = nullptr);
+                             const ConvPairWgrad* pair = nullptr, bool* bias_done = nullptr);
 // Pointwise (1x1) form: J[(s*O + o), off + c*Cin + ci] = sum_p G[s, o, p, c] h[s, p, ci].
 hipError_t launch_pw_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H,
                            int W, int C, int Cin, float* J, long long ldJ, long long off,
-                           const ConvPairWgrad* pair = nullptr);
+                           const ConvPairWgrad* pair = nullptr, bool* bias_done = nullptr);
 // Everything the pair products of one CNN evaluation need that does not depend on the backward, in
 // one launch: the pair rows of the flipped kernels (N[z] rows of 9 taps of C[z] channels), the
 // largest magnitude of each image of the layer inputs x[j] ([M, plane[j]] -> hmax[j]), the bound
@@ -100,7 +102,7 @@ hipError_t launch_conv_max(hipStream_t s, const ConvMax& m);
 bool conv_wgrad_pad_ok(int images, int O, int H, int W, int C, int Cin, const float* G, const float* xp);
 hipError_t launch_conv_wgrad_padded(hipStream_t s, const float* G, const float* h, float* xp, int images, int O,
                                     int H, int W, int C, int Cin, float* J, long long ldJ, long long off, bool pw,
-                                    const ConvPairWgrad* pair = nullptr);
+                                    const ConvPairWgrad* pair = nullptr, bool* bias_done = nullptr);
 // theta[n1, n2, o1, o2] += scale sum_c Wr[o1, c] Wr[o2, c] Mc[c, n1, n2] (Wr [O, C], Mc [C, N1, N2]).
 hipError_t launch_readout_fold(hipStream_t s, const float* Wr, int C, int O, const float* Mc, int N1, int N2,
                                float scale, float* theta);

@@ -1525,17 +1525,18 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
   if (e != hipSuccess) return hip_fail(h, e, "conv seed");
   // weight-space product of layer l's 3x3 (pw: pointwise) convolution: inputs with Cin % 4 != 0
   // padded to the direct-to-LDS form when possible
-  auto wgrad = [&](int l, const float* G, int Orows, float* Jout, long long ldJ, long long off, bool pw) {
+  auto wgrad = [&](int l, const float* G, int Orows, float* Jout, long long ldJ, long long off, bool pw,
+                   long long bias, bool* bias_done) {
     const int Hl = h->bh[l], Wl = h->bw[l], cin = h->ch[l], cout = h->ch[l + 1];
     float* xp = h->off_xpad ? F(h->off_xpad) : nullptr;
     // the folded layer's "cotangent" is act' itself
     const ConvPairWgrad pg{fold && l == ll ? nullptr : bound[l].gmax, bound[l].fac, act_bound(l),
-                           F(h->off_hmax) + l * hm_ld};
+                           F(h->off_hmax) + l * hm_ld, bias};
     const ConvPairWgrad* pr = cpair ? &pg : nullptr;
     if (xp && conv_wgrad_pad_ok(M, Orows, Hl, Wl, cout, cin, G, xp))
-      return launch_conv_wgrad_padded(s, G, hptr(l), xp, M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pw, pr);
-    return pw ? launch_pw_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr)
-              : launch_conv_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr);
+      return launch_conv_wgrad_padded(s, G, hptr(l), xp, M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pw, pr, bias_done);
+    return pw ? launch_pw_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr, bias_done)
+              : launch_conv_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr, bias_done);
   };
   float* J = F(h->off_J);
   // the folded layer's A: in J past this call's columns (J holds that layer's O C F Cin columns
@@ -1547,14 +1548,15 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
     const ntk_layer_desc& L = h->layers[l];
     const int Hl = h->bh[l], Wl = h->bw[l], cin = h->ch[l], cout = h->ch[l + 1];
     const float* w = h->wslot[l] >= 0 ? params[h->wslot[l]] : nullptr;
+    bool bias_done = false;   // by the weight-space product
     // Gcur: the cotangent of layer l's pre-activation (of its output for a pool), [M*Oe, ., ., cout]
     if (fold && l == ll) {
       // A [M, C, F Cin] from act'(z) in place of the O cotangents (the "fold" above), in J past
       // the columns of this call
       const float* dz = F(h->off_cdphi[ll]);
       prof_begin(P, s, KC_CONV_WGRAD);
-      e = L.kind == NTK_CONV3X3_SAME ? wgrad(l, dz, 1, fold_A, 9LL * cin * cout, 0, false)
-                                     : wgrad(l, dz, 1, fold_A, (long long)cin * cout, 0, true);
+      e = L.kind == NTK_CONV3X3_SAME ? wgrad(l, dz, 1, fold_A, 9LL * cin * cout, 0, false, -1, nullptr)
+                                     : wgrad(l, dz, 1, fold_A, (long long)cin * cout, 0, true, -1, nullptr);
       prof_end(P, s, KC_CONV_WGRAD);
       if (e != hipSuccess) return hip_fail(h, e, "last convolution's channel cotangents");
       if (L.has_bias) {
@@ -1573,11 +1575,11 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
         theta_written = true;
       } else {
         prof_begin(P, s, KC_CONV_WGRAD);
-        e = wgrad(l, Gcur, Oe, J, Kcall, jw[l], false);
+        e = wgrad(l, Gcur, Oe, J, Kcall, jw[l], false, L.has_bias ? jb[l] : -1, &bias_done);
         prof_end(P, s, KC_CONV_WGRAD);
         if (e != hipSuccess) return hip_fail(h, e, "conv weight-space cotangent");
       }
-      if (L.has_bias) {
+      if (L.has_bias && !bias_done) {
         prof_begin(P, s, KC_STRUCT_WGRAD);
         e = launch_pix_wgrad(s, Gcur, nullptr, M, Oe, Hl, Wl, cout, 0, 1, J, Kcall, 0, jb[l], nullptr, 0);
         prof_end(P, s, KC_STRUCT_WGRAD);
@@ -1592,10 +1594,10 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
         theta_written = true;
       } else {
         prof_begin(P, s, KC_CONV_WGRAD);
-        e = wgrad(l, Gcur, Oe, J, Kcall, jw[l], true);
+        e = wgrad(l, Gcur, Oe, J, Kcall, jw[l], true, L.has_bias ? jb[l] : -1, &bias_done);
         prof_end(P, s, KC_CONV_WGRAD);
       }
-      if (e == hipSuccess && L.has_bias) {
+      if (e == hipSuccess && L.has_bias && !bias_done) {
         prof_begin(P, s, KC_STRUCT_WGRAD);
         e = launch_pix_wgrad(s, Gcur, nullptr, M, Oe, Hl, Wl, cout, 0, 1, J, Kcall, 0, jb[l], nullptr, 0);
         prof_end(P, s, KC_STRUCT_WGRAD);
