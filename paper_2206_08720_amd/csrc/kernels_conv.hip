@@ -1961,28 +1961,214 @@ k_ntk_splitk_dma(const float* __restrict__ J1, const float* __restrict__ J2, int
   });
 }
 
+// The same products on pairs, split into f16 values on the way through registers into LDS (a thread:
+// 8 k of a row, four threads a row's K tile; two LDS stages, the next tile's loads in flight during the
+// MFMAs).  No row maxima are known before, so a row's exponent follows what has been read: it starts
+// from its first K tile with two bits to spare, and a K tile that passes the top raises it, which
+// scales the row's (column's) sums so far by the power of two in between.  The decision is per K
+// tile and workgroup, through flags and exponent steps in LDS beside the stage; past the first tiles
+// of a chunk it is rare.  Bound by the MFMAs and the splits: 640 x 640 x 75 456: 553 us
+// with the fp32 MFMA (112 TF/s), 313 here (197 TF/s).
+template <class Cfg, bool VEC>
+__global__ void __launch_bounds__(Cfg::THREADS, 2)
+k_ntk_splitk_pair(const float* __restrict__ J1, const float* __restrict__ J2, int R1, int R2, int K, long long ld,
+                  int chunk, int splits, int tiles, int symmetric, float* __restrict__ part, int tiles_n) {
+  constexpr int ROWS = Cfg::BM + Cfg::BN, STAGE = ROWS * 32, NT = ROWS * 4 / Cfg::THREADS;
+  static_assert(Cfg::THREADS == 256 && Cfg::BM % 64 == 0 && Cfg::BN % 64 == 0, "64 rows of one operand per task");
+  extern __shared__ f32x4 sk_lds[];   // 16-byte aligned
+  float* smem = reinterpret_cast<float*>(sk_lds);
+  int* steps = reinterpret_cast<int*>(smem + 2 * STAGE);   // [2][ROWS]
+  int* flags = steps + 2 * ROWS;                           // [2][4], per wave
+  const int x = blockIdx.x & 7, jb = blockIdx.x >> 3;
+  const long long items = (long long)tiles * splits;
+  const long long item = x * items / 8 + jb;
+  if (item >= (x + 1) * items / 8) return;
+  const int z = (int)(item / tiles), t = (int)(item - (long long)z * tiles);
+  int tm, tn;
+  if (symmetric) {
+    tri_index_c(t, tiles_n, tm, tn);
+  } else {
+    tm = t / tiles_n;
+    tn = t % tiles_n;
+  }
+  const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
+  const int k0 = z * chunk, k1 = min(K, k0 + chunk), nk = (k1 - k0 + 31) / 32;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm0 = (wave / Cfg::WAVES_N) * Cfg::WM, wn0 = (wave % Cfg::WAVES_N) * Cfg::WN;
+  const int lr = lane & 31, lc = (lane >> 5) * 2;
+  const int g = threadIdx.x & 3, trow = threadIdx.x >> 2;
+  // rows of a tile through buffer resources; a row past the operand or a k past the chunk reads zeros
+  const int rows_a = min(Cfg::BM, R1 - m0), rows_b = min(Cfg::BN, R2 - n0);
+  const __amdgpu_buffer_rsrc_t ra = buffer_rsrc(J1 + m0 * ld, (uint32_t)(((rows_a - 1) * ld + K) * 4));
+  const __amdgpu_buffer_rsrc_t rb = buffer_rsrc(J2 + n0 * ld, (uint32_t)(((rows_b - 1) * ld + K) * 4));
+  int exps[NT];
+  static_for<0, NT>([&](auto it) __attribute__((always_inline)) { exps[decltype(it)::value] = -126; });
+  f32x4 st[NT][2];
+  auto fetch = [&](int kt) __attribute__((always_inline)) {
+    const int k = k0 + kt * 32 + 8 * g;
+    static_for<0, NT>([&](auto it) __attribute__((always_inline)) {
+      constexpr int i = decltype(it)::value;
+      constexpr bool is_b = i * 64 >= Cfg::BM;
+      const int r = i * 64 - (is_b ? Cfg::BM : 0) + trow;
+      const bool in = r < (is_b ? rows_b : rows_a);
+      const uint32_t voff = ((uint32_t)r * (uint32_t)ld + (uint32_t)k) * 4u;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (VEC) {
+          st[i][h] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                   is_b ? rb : ra, in && k + 4 * h < k1 ? voff + 16u * h : kDmaPastEnd, 0, 0));
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            st[i][h][j] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(
+                           is_b ? rb : ra, in && k + 4 * h + j < k1 ? voff + 16u * h + 4u * j : kDmaPastEnd, 0, 0));
+        }
+      }
+    });
+  };
+  auto swz = [](int r, int c) { return c ^ (r & 7); };
+  auto stage = [&](int sidx) __attribute__((always_inline)) {
+    float* d = smem + sidx * STAGE;
+    bool raised = false;
+    static_for<0, NT>([&](auto it) __attribute__((always_inline)) {
+      constexpr int i = decltype(it)::value;
+      const f32x4 u = st[i][0], v = st[i][1];
+      float m = fmaxf(fmaxf(fmaxf(fabsf(u[0]), fabsf(u[1])), fmaxf(fabsf(u[2]), fabsf(u[3]))),
+                      fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+      m = fmaxf(m, __shfl_xor(m, 1));
+      m = fmaxf(m, __shfl_xor(m, 2));
+      const int e = m > 0.f ? pair_row_exp(m) : -126, step = e > exps[i] ? exps[i] - (e + 2) : 0;
+      exps[i] -= step;
+      raised = raised || step != 0;
+      const int r = i * 64 + trow;
+      if (g == 0) steps[sidx * ROWS + r] = step;
+      f16x8 hi, lo;
+      pair_split8(u, v, pair_factor(exps[i]), hi, lo);
+      *reinterpret_cast<f16x8*>(&d[r * 32 + (swz(r, 2 * g) << 2)]) = hi;
+      *reinterpret_cast<f16x8*>(&d[r * 32 + (swz(r, 2 * g + 1) << 2)]) = lo;
+    });
+    const int any = __any(raised) ? 1 : 0;
+    if (lane == 0) flags[sidx * 4 + wave] = any;
+  };
+  f32x16 acc[Cfg::FM][Cfg::FN];
+  zero_acc<Cfg>(acc);
+  // acc[r][c] times 2^(v[r] + v[BM + c]), v in LDS
+  auto scale = [&](const int* v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j) {
+      const int ec = v[Cfg::BM + wn0 + j * 32 + lr];
+#pragma unroll
+      for (int i = 0; i < Cfg::FM; ++i)
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+          acc[i][j][q] = ldexpf(acc[i][j][q], v[wm0 + i * 32 + frag_row(q, lane)] + ec);
+    }
+  };
+  auto frag = [&](const float* p, int r, int c) __attribute__((always_inline)) {
+    return *reinterpret_cast<const f16x8*>(&p[r * 32 + (swz(r, c) << 2)]);
+  };
+  auto tile = [&](int kt, auto stage_tag) __attribute__((always_inline)) {
+    constexpr int S = decltype(stage_tag)::value;
+    const float* cur = smem + S * STAGE;
+    if (kt + 1 < nk) fetch(kt + 1);
+    if (__builtin_amdgcn_readfirstlane(flags[S * 4] | flags[S * 4 + 1] | flags[S * 4 + 2] | flags[S * 4 + 3]))
+      scale(steps + S * ROWS);
+    f16x8 a[2][2], b[Cfg::FN][2];
+    static_for<0, 2>([&](auto ht) __attribute__((always_inline)) {
+      constexpr int half = decltype(ht)::value;
+#pragma unroll
+      for (int j = 0; j < Cfg::FN; ++j)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) b[j][p] = frag(cur, Cfg::BM + wn0 + j * 32 + lr, half * 4 + lc + p);
+      static_for<0, Cfg::FM>([&](auto it) __attribute__((always_inline)) {
+        constexpr int i = decltype(it)::value;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) a[i & 1][p] = frag(cur, wm0 + i * 32 + lr, half * 4 + lc + p);
+#pragma unroll
+        for (int j = 0; j < Cfg::FN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i & 1][1], b[j][0], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < Cfg::FN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i & 1][0], b[j][1], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < Cfg::FN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i & 1][0], b[j][0], acc[i][j], 0, 0, 0);
+      });
+    });
+    // the other stage, its steps and flags were last read in tile kt - 1, which every wave has left
+    if (kt + 1 < nk) stage(S ^ 1);
+    __syncthreads();
+  };
+  fetch(0);
+  stage(0);
+  __syncthreads();
+  int kb = 0;
+  for (; kb + 2 <= nk; kb += 2) {
+    tile(kb, std::integral_constant<int, 0>{});
+    tile(kb + 1, std::integral_constant<int, 1>{});
+  }
+  if (kb < nk) tile(kb, std::integral_constant<int, 0>{});
+  static_for<0, NT>([&](auto it) __attribute__((always_inline)) {
+    constexpr int i = decltype(it)::value;
+    if (g == 0) steps[i * 64 + trow] = exps[i];
+  });
+  __syncthreads();
+  scale(steps);
+  float* P = part + (long long)z * R1 * R2;
+  for_each_acc<Cfg>(acc, m0, n0, [&](int r, int c, float v) {
+    if (r < R1 && c < R2) P[(long long)r * R2 + c] = v;
+  });
+}
+
 // theta[n1][n2][o1][o2] = w[n1, n2] sum_z part[z][r1][r2] + (o1 == o2) rscale gram[n1, n2], or,
 // with accumulate, theta += w[n1, n2] sum_z part[z][r1][r2] (the readout summand is then
 // already in theta).  w = null means 1; gram = null means no readout summand.
-__global__ void k_ntk_reduce(const float* __restrict__ part, int splits, int N1, int N2, int O,
-                             int symmetric, int tile, const float* __restrict__ w,
-                             const float* __restrict__ gram, float rscale, int accumulate,
-                             float* __restrict__ theta) {
+// ZG threads per entry, each a contiguous range of the partials, added in order through LDS: with few
+// entries and many partials (64 x 64 entries, 295 partials: 35 us with ZG = 1, 9 with 8) one thread's
+// chain of loads would be all there is.
+template <int ZG>
+__global__ void __launch_bounds__(256)
+k_ntk_reduce(const float* __restrict__ part, int splits, int N1, int N2, int O,
+             int symmetric, int tile, const float* __restrict__ w,
+             const float* __restrict__ gram, float rscale, int accumulate,
+             float* __restrict__ theta) {
+  constexpr int EB = 256 / ZG;   // entries per workgroup and pass
+  __shared__ float sums[ZG > 1 ? 256 : 1];
   const int R1 = N1 * O, R2 = N2 * O;   // below 2^31: the launcher checked them
   const long long total = (long long)R1 * R2;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int r1 = (int)(i / R2), r2 = (int)(i - (long long)r1 * R2);
-    long long src = i;
-    if (symmetric && (r1 / tile) > (r2 / tile)) src = (long long)r2 * R2 + r1;
-    float a[4] = {0.f, 0.f, 0.f, 0.f};   // four independent chains keep several loads in flight
-    int z = 0;
-    for (; z + 4 <= splits; z += 4) {
+  const int zg = ZG > 1 ? threadIdx.x / EB : 0, te = ZG > 1 ? threadIdx.x % EB : threadIdx.x;
+  const int z0 = ZG > 1 ? (int)((long long)splits * zg / ZG) : 0;
+  const int z1 = ZG > 1 ? (int)((long long)splits * (zg + 1) / ZG) : splits;
+  for (long long i0 = blockIdx.x * (long long)EB; i0 < total; i0 += (long long)gridDim.x * EB) {
+    const long long i = i0 + te;
+    const bool in = i < total;
+    if (ZG == 1 && !in) return;   // later passes of this thread lie further on
+    const int r1 = in ? (int)(i / R2) : 0, r2 = in ? (int)(i - (long long)r1 * R2) : 0;
+    float v = 0.f;
+    if (in) {
+      long long src = i;
+      if (symmetric && (r1 / tile) > (r2 / tile)) src = (long long)r2 * R2 + r1;
+      float a[4] = {0.f, 0.f, 0.f, 0.f};   // four independent chains keep several loads in flight
+      int z = z0;
+      for (; z + 4 <= z1; z += 4) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) a[u] += part[(long long)(z + u) * total + src];
+        for (int u = 0; u < 4; ++u) a[u] += part[(long long)(z + u) * total + src];
+      }
+      for (; z < z1; ++z) a[0] += part[(long long)z * total + src];
+      v = (a[0] + a[1]) + (a[2] + a[3]);
     }
-    for (; z < splits; ++z) a[0] += part[(long long)z * total + src];
-    float v = (a[0] + a[1]) + (a[2] + a[3]);
+    if (ZG > 1) {
+      sums[threadIdx.x] = v;
+      __syncthreads();
+      if (zg == 0) {
+        v = 0.f;
+#pragma unroll
+        for (int u = 0; u < ZG; ++u) v += sums[u * EB + te];
+      }
+      __syncthreads();
+    }
+    if (!in || zg) continue;
     const int n1 = r1 / O, o1 = r1 - n1 * O, n2 = r2 / O, o2 = r2 - n2 * O;
     if (w) v *= w[(long long)n1 * N2 + n2];
     float* dst = theta + (((long long)n1 * N2 + n2) * O + o1) * O + o2;
@@ -2029,9 +2215,31 @@ static hipError_t splitk_vec(hipStream_t s, const float* J1, const float* J2, in
   return hipGetLastError();
 }
 
+// Pairs from 0.3 GFLOP and 4096 columns on: 64 x 64 x 75 000, 38 us with the fp32 MFMA, 25 with pairs;
+// 217 x 126 x 10 700, 24 and 21.  640 x 640 x 1728 (chunks of eight K tiles, the first of which sets the
+// exponents): 22 us either way, the evaluation around it 315 and 318.
+constexpr double kSplitKPairMinFlops = 3e8;
+constexpr long long kSplitKPairMinK = 4096;
 hipError_t launch_ntk_splitk(hipStream_t s, const float* J1, const float* J2, int R1, int R2,
                              long long K, long long ld, int symmetric, int chunk, int splits,
                              float* part) {
+  if (K >= kSplitKPairMinK && 2.0 * R1 * R2 * K >= kSplitKPairMinFlops && dma_span_ok(ld, K, 128)) {
+    using Cfg = CfgSplitK;
+    const int tm = cdiv(R1, Cfg::BM), tn = cdiv(R2, Cfg::BN);
+    const int tiles = symmetric ? tn * (tn + 1) / 2 : tm * tn;
+    constexpr int rows = Cfg::BM + Cfg::BN, bytes = 2 * rows * 128 + 2 * rows * 4 + 32;
+    const unsigned blocks = (unsigned)(8 * (((long long)tiles * splits + 7) / 8));
+    auto go = [&](auto vec_tag) -> hipError_t {
+      constexpr bool VEC = decltype(vec_tag)::value;
+      hipError_t e = hipFuncSetAttribute((const void*)k_ntk_splitk_pair<Cfg, VEC>,
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+      if (e != hipSuccess) return e;
+      k_ntk_splitk_pair<Cfg, VEC><<<dim3(blocks), dim3(Cfg::THREADS), bytes, s>>>(
+          J1, J2, R1, R2, (int)K, ld, chunk, splits, tiles, symmetric, part, tn);
+      return hipGetLastError();
+    };
+    return vec_ok(J1, ld, K) && vec_ok(J2, ld, K) ? go(std::true_type{}) : go(std::false_type{});
+  }
   if (vec_ok(J1, ld, K) && vec_ok(J2, ld, K) && K % 32 == 0 && chunk % 32 == 0 && dma_span_ok(ld, K, 128)) {
     using Cfg = CfgSplitKDma;
     static_assert(Cfg::BM == CfgSplitK::BM && Cfg::BN == CfgSplitK::BN, "the reduction's tile grid");
@@ -2057,9 +2265,16 @@ hipError_t launch_ntk_reduce(hipStream_t s, const float* part, int splits, int N
   int R1, R2;
   if (!to_int((long long)N1 * O, R1) || !to_int((long long)N2 * O, R2)) return hipErrorInvalidValue;
   const long long total = (long long)R1 * R2;
-  const int blocks = (int)std::min<long long>((total + 255) / 256, 256 * 64);
-  k_ntk_reduce<<<dim3(blocks), dim3(256), 0, s>>>(part, splits, N1, N2, O, symmetric, CfgSplitK::BM,
-                                                  w, gram, rscale, accumulate, theta);
+  auto go = [&](auto zg_tag) {
+    constexpr int ZG = decltype(zg_tag)::value, EB = 256 / ZG;
+    k_ntk_reduce<ZG><<<dim3((unsigned)std::min<long long>((total + EB - 1) / EB, 256 * 64)), dim3(256), 0, s>>>(
+        part, splits, N1, N2, O, symmetric, CfgSplitK::BM, w, gram, rscale, accumulate, theta);
+  };
+  // one thread per entry from two workgroups a compute unit on, or for a few partials
+  if (total < 512 * 256 && splits >= 16)
+    go(std::integral_constant<int, 8>{});
+  else
+    go(std::integral_constant<int, 1>{});
   return hipGetLastError();
 }
 

@@ -150,3 +150,18 @@ def test_pair_conv_magnitudes():
     X1 *= np.exp2(rng.integers(-15, 16, (13, 1, 1, 1))).astype(np.float32)
     X2[3] = 0.0
     _conv_check("conv magnitudes", spec, params, X1, X2)
+
+
+@pytest.mark.parametrize("scaling", ["growing", "shrinking", "dead channels"])
+@pytest.mark.parametrize("n1,n2", [(43, 27), (40, 40)])
+def test_pair_splitk_row_exponents(scaling, n1, n2):
+    """J1 J2^T on pairs, whose row exponents follow the columns: 5 x 9 x 91 weight and 91 bias columns
+    (scalar loads, a ragged last K tile) whose channels differ by 2^45, or are zero at first."""
+    spec = wl.cnn_layers_spec("pairs", (6, 6), 5, [(C3, 91, "relu", True), (C3, 40, "relu", False)], 13)
+    params = wl.make_params(spec, 71, "2/fan_in", bias_var=0.05)
+    f = np.exp2(np.arange(91) / 2).astype(np.float32)
+    f = {"growing": f, "shrinking": f[::-1], "dead channels": (np.arange(91) > 50).astype(np.float32)}[scaling]
+    params[2] *= f
+    X1 = wl.make_inputs(spec, n1, 72)
+    X2 = X1 if n1 == n2 else wl.make_inputs(spec, n2, 73)
+    _conv_check("split-K " + scaling, spec, params, X1, X2)
