@@ -1201,8 +1201,8 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
     }
     om[i] = r < R ? m : 0x1FFu;
   }
-  PairAcc<Cfg::FM, Cfg::FN, true> acc;
-  zero_pair_acc(acc);
+  f32x16 acc[Cfg::FM][Cfg::FN];
+  zero_acc<Cfg>(acc);
   pb.prepare(n0, wave, lane);
   if (threadIdx.x < 32) smem[HR * 32 + threadIdx.x] = 0.f;
   pb.template issue<Cfg::WAVES>(0, Bs, wave, lane);
@@ -1235,13 +1235,13 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
   auto mma = [&](int i, const f16x8 (&x)[2], const f16x8 (&y)[Cfg::FN][2]) {
 #pragma unroll
     for (int j = 0; j < Cfg::FN; ++j)
-      acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], y[j][0], acc.v[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], y[j][0], acc[i][j], 0, 0, 0);
 #pragma unroll
     for (int j = 0; j < Cfg::FN; ++j)
-      acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y[j][1], acc.v[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y[j][1], acc[i][j], 0, 0, 0);
 #pragma unroll
     for (int j = 0; j < Cfg::FN; ++j)
-      acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y[j][0], acc.v[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], y[j][0], acc[i][j], 0, 0, 0);
   };
   rows_of(0);
   load_b(Bs, 0, b[0]);
@@ -1302,10 +1302,10 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
       const int e = one ? e0 : pair_row_exp(pr.gmax[fD.div(min(r0 + frag_row(v, lane), R - 1))] * fac);
 #pragma unroll
       for (int j = 0; j < Cfg::FN; ++j)
-        acc.v[i][j][v] = ldexpf(acc.v[i][j][v], e + pr.kexps[min(n0 + wn0 + j * 32 + lr, N - 1)]);
+        acc[i][j][v] = ldexpf(acc[i][j][v], e + pr.kexps[min(n0 + wn0 + j * 32 + lr, N - 1)]);
     }
   }
-  store_pixel_rows<Cfg>(acc.v, m0, n0, dphi, out, R, N, fOD, fD, gmax);
+  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, gmax);
 }
 
 template <bool VEC>

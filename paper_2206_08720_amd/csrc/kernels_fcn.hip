@@ -20,7 +20,6 @@
 
 namespace ntk {
 
-using CfgBig = TileCfg<128, 128, 32, 64, 64>;   // 4 waves, 64x64 per wave
 using CfgBig8 = TileCfg<128, 128, 32, 32, 64>;  // 8 waves, 32x64 per wave
 using CfgSK = CfgBig8;                          // stream-K contraction
 // The same on pair rows: 8 waves of 64x64, one workgroup per CU.  Against 4 waves of 64x64 on 128x128

@@ -162,10 +162,8 @@ __device__ __forceinline__ void pair_mainloop(const float* __restrict__ A, long 
 }
 
 // ------------------------------------------------------------------------------ fp32 tiles
-// The same products from operands that stay fp32 in memory and LDS (the convolutions' gathers):
-// a wave splits its fragments into pairs in registers, after the LDS read, scaled by one factor
-// per row (lane): about 100 cycles per fragment of 8 k per lane, against 3 MFMAs of 32 cycles for
-// every fragment of the other operand it meets.
+// The same products from operands that stay fp32 in memory (the convolutions' gathers, the rows of J):
+// a kernel splits them in registers on their way into LDS, scaled by one factor per row.
 __device__ __forceinline__ float pair_factor(int e) { return ldexpf(1.f, -max(e, -126)); }
 // the exponent of a row whose largest magnitude is at most m (its factor: pair_factor)
 __device__ __forceinline__ int pair_row_exp(float m) { return max(pair_exp(m) - kPairTop, -126); }
@@ -188,75 +186,5 @@ __device__ __forceinline__ void pair_split8(const f32x4& x, const f32x4& y, floa
     lo[j + 1] = l[1];
   }
 }
-
-// Accumulators and row factors of the direct-to-LDS loop of gemm_core.hpp on pairs: A fp32, B fp32
-// or (BPAIR) pair rows.
-template <int FM, int FN, bool BPAIR>
-struct PairAcc {
-  f32x16 v[FM][FN];
-  float sa[FM], sb[BPAIR ? 1 : FN];
-};
-template <int FM, int FN, bool BPAIR>
-__device__ __forceinline__ void zero_pair_acc(PairAcc<FM, FN, BPAIR>& a) {
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) a.v[i][j][v] = 0.f;
-}
-
-// Two blocks of 16 k.  The 8 k of a lane (half-wave h) in a block: 8 h .. 8 h + 7 when B is pair
-// rows (their groups of 8 k), else 4 h .. 4 h + 3 and 8 + 4 h .. 8 + 4 h + 3 (the reads of a K-outer
-// tile by the two half-waves then fall in disjoint banks); A and B take the same k.
-template <class Cfg, class TA, class TB, int FM, int FN, bool BPAIR>
-struct MmaBlocks<Cfg, TA, TB, PairAcc<FM, FN, BPAIR>> {
-  static constexpr int NB = 2;
-  struct Frag {
-    f32x4 a[FM][2], b[FN][2];
-  };
-  __device__ static __forceinline__ void load(const float* As, const float* Bs, int blk, int wm0, int wn0, int lane,
-                                              Frag& f) {
-    const int lr = lane & 31, h = lane >> 5;
-    const int k0 = blk * 16 + (BPAIR ? 8 : 4) * h, k1 = k0 + (BPAIR ? 4 : 8);
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      f.a[i][0] = TA::frag(As, wm0 + i * 32 + lr, k0);
-      f.a[i][1] = TA::frag(As, wm0 + i * 32 + lr, k1);
-    }
-    // pair rows: the 16-byte chunks of hi and of lo of group 2 blk + h
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      f.b[j][0] = TB::frag(Bs, wn0 + j * 32 + lr, k0);
-      f.b[j][1] = TB::frag(Bs, wn0 + j * 32 + lr, k1);
-    }
-  }
-  __device__ static __forceinline__ void mma(const Frag& f, PairAcc<FM, FN, BPAIR>& acc) {
-    f16x8 ah[FM], al[FM], bh[FN], bl[FN];
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      if constexpr (BPAIR) {
-        bh[j] = __builtin_bit_cast(f16x8, f.b[j][0]);
-        bl[j] = __builtin_bit_cast(f16x8, f.b[j][1]);
-      } else {
-        pair_split8(f.b[j][0], f.b[j][1], acc.sb[j], bh[j], bl[j]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < FM; ++i) pair_split8(f.a[i][0], f.a[i][1], acc.sa[i], ah[i], al[i]);
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[i], bh[j], acc.v[i][j], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[i], bl[j], acc.v[i][j], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) acc.v[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[i], bh[j], acc.v[i][j], 0, 0, 0);
-  }
-};
 
 }  // namespace ntk
