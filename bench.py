@@ -36,6 +36,8 @@ sys.path.insert(0, ROOT)
 METRIC = "NTK entries/sec (N1·N2·O²) and fp32 MFMA TFLOP/s, FCN depth 8 width 2048"
 FP32_MFMA_PEAK_TFLOPS = 157.3      # MI355X dense fp32 matrix peak
 FP64_MFMA_PEAK_TFLOPS = 78.6       # MI355X dense fp64 matrix peak (the forward passes)
+# products on pairs of f16 values: three f16 MFMAs each, so a third of the dense f16 peak
+PAIR_MFMA_PEAK_TFLOPS = 2500.0 / 3.0
 HBM_PEAK_GBS = 8000.0
 
 # kernel class -> stage of the FLOP counter
@@ -43,7 +45,9 @@ STAGE_OF = {"dense_fwd": "forward", "dense_bwd": "backward", "gram": "gram",
             "ntk_fcn": "contraction", "conv_fwd": "forward", "conv_bwd": "backward",
             "conv_wgrad": "wgrad", "ntk_splitk": "contraction", "conv_pairsum": "pairsum",
             "ntk_diag": "contraction", "struct_fwd": "struct_forward",
-            "struct_bwd": "struct_backward", "struct_wgrad": "struct_wgrad"}
+            "struct_bwd": "struct_backward", "struct_wgrad": "struct_wgrad",
+            "dense_bwd_pair": "backward", "ntk_fcn_pair": "contraction", "conv_bwd_pair": "backward",
+            "conv_wgrad_pair": "wgrad"}
 # kernel class -> stage of the NTK-vector product's counter
 VP_STAGE_OF = {"dense_fwd": "forward", "dense_bwd": "vjp_backward", "gram": "gram_products",
                "conv_fwd": "forward_and_jvp", "conv_bwd": "vjp_backward",
@@ -270,23 +274,31 @@ def main():
     value = entries / (ms * 1e-3)
     tflops = fl["total"] / (ms * 1e-3) / 1e12
 
+    # a stage whose layers are shared between a class and its *_pair form is priced as a whole
+    stage_time = {}
+    for k, (tot, cnt) in prof.items():
+        if stage_of.get(k) in fl:
+            t, c = stage_time.get(stage_of[k], (0.0, 0))
+            stage_time[stage_of[k]] = (t + tot, c + cnt)
     kernels = {}
     for k, (tot, cnt) in prof.items():
         per_step = cnt / args.steps
         kernels[k] = {"ms_per_step": tot / args.steps, "launches_per_step": per_step}
         st = stage_of.get(k)
-        if st and st in fl and cnt:
-            kernels[k]["tflops"] = fl[st] / (tot / args.steps * 1e-3) / 1e12
+        if st in stage_time and cnt:
+            kernels[k]["tflops"] = fl[st] / (stage_time[st][0] / args.steps * 1e-3) / 1e12
     # the dominant matrix-core kernel class (the memory-bound struct_* classes are not priced
     # against the MFMA peak)
     dom = max((k for k in prof if stage_of.get(k) in fl and not stage_of[k].startswith("struct")),
               key=lambda k: prof[k][0])
-    tot, cnt = prof[dom]
+    tot, cnt = stage_time[stage_of[dom]]
     avg_ms = tot / cnt
     flop_per_launch = fl[stage_of[dom]] / (cnt / args.steps)
     achieved = flop_per_launch / (avg_ms * 1e-3) / 1e12
-    # every priced class runs on the matrix cores: the forward in fp64, the rest in fp32
-    peak = FP64_MFMA_PEAK_TFLOPS if stage_of[dom] == "forward" else FP32_MFMA_PEAK_TFLOPS
+    # every priced class runs on the matrix cores: the forward in fp64, the *_pair classes on pairs
+    # of f16 values, the rest in fp32
+    peak = (FP64_MFMA_PEAK_TFLOPS if stage_of[dom] == "forward" else
+            PAIR_MFMA_PEAK_TFLOPS if dom.endswith("_pair") else FP32_MFMA_PEAK_TFLOPS)
     roofline = {"kernel": dom, "bound": "mfma", "achieved": achieved,
                 "peak": peak, "unit": "TFLOP/s",
                 "frac": achieved / peak, "traffic": measured_traffic(name, dom),
@@ -297,8 +309,9 @@ def main():
     num_cu, clock_khz = _lib.device_info()
     ceiling = {"fp32_tflops": _lib.mfma_peak("fp32"), "fp64_tflops": _lib.mfma_peak("fp64"),
                "kernel": "independent MFMA chains, 4 waves per SIMD"}
-    roofline["measured_ceiling"] = ceiling["fp32_tflops"]
-    roofline["frac_of_measured_ceiling"] = achieved / ceiling["fp32_tflops"]
+    if peak != PAIR_MFMA_PEAK_TFLOPS:       # no f16 chain is measured here
+        roofline["measured_ceiling"] = ceiling["fp64_tflops" if stage_of[dom] == "forward" else "fp32_tflops"]
+        roofline["frac_of_measured_ceiling"] = achieved / roofline["measured_ceiling"]
 
     res = {
         "metric": METRIC if args.op == "ntk" else "NTK-vector product outputs/sec (N1 O)",

@@ -1746,7 +1746,18 @@ k_conv_wgrad_pair(const float* __restrict__ G, const float* __restrict__ h, Conv
 // columns) read them through one L2 (xcd_sample_tile).
 static unsigned wgrad_grid(int tiles, int images) { return (unsigned)(8 * ((images + 7) / 8) * tiles); }
 
+// Pairs need a workgroup per compute unit: a K tile's loads and splits are one serial chain, which
+// other workgroups have to hide.  38 workgroups of 23 K tiles: 72 us, 51 with the fp32 form; 152:
+// 31 and 20; 294: 66 and 106.
 constexpr long long kConvWgPairMinGroups = 256;
+bool conv_wgrad_takes_pairs(int images, int O, int H, int W, int C, int Cin, bool pw) {
+  const int KC = (pw ? 1 : 9) * Cin;
+  const bool spans = (long long)O * H * W * C * 4 < (1LL << 31) && ((long long)H * W + W + 1) * Cin * 4 < (1LL << 31);
+  const long long tiles = KC <= 64 ? (long long)cdiv(O * C, CfgConvWgPairN::BM)
+                          : O * C <= 64 ? (long long)cdiv(KC, CfgConvWgPairM::BN)
+                                        : (long long)cdiv(O * C, CfgConvWgPair::BM) * cdiv(KC, CfgConvWgPair::BN);
+  return spans && tiles * images >= kConvWgPairMinGroups;
+}
 
 template <bool VA, bool VB, bool PW>
 static hipError_t conv_wgrad_vec(hipStream_t s, const float* G, const float* h, int images, int O,
@@ -1774,14 +1785,7 @@ static hipError_t conv_wgrad_any(hipStream_t s, const float* G, const float* h, 
   if ((long long)8 * ((images + 7) / 8) * cdiv(KC, CfgConv::BN) * cdiv((long long)O * C, CfgConv::BM) >=
       (1LL << 31))
     return hipErrorInvalidValue;
-  const bool spans = (long long)O * H * W * C * 4 < (1LL << 31) && ((long long)H * W + W + 1) * Cin * 4 < (1LL << 31);
-  // (pairs need a workgroup per compute unit: a K tile's loads and splits are one serial chain, which
-  // other workgroups have to hide.  38 workgroups of 23 K tiles: 72 us, 51 with the fp32 form; 152:
-  // 31 and 20; 294: 66 and 106.)
-  const long long pair_tiles = KC <= 64 ? (long long)cdiv(O * C, CfgConvWgPairN::BM)
-                               : O * C <= 64 ? (long long)cdiv(KC, CfgConvWgPairM::BN)
-                                             : (long long)cdiv(O * C, CfgConvWgPair::BM) * cdiv(KC, CfgConvWgPair::BN);
-  if (pair && spans && pair_tiles * images >= kConvWgPairMinGroups) {
+  if (pair && conv_wgrad_takes_pairs(images, O, H, W, C, Cin, PW)) {
     if (bias_done) *bias_done = pair->bias >= 0;
     const bool va = C % 4 == 0 && aligned16(G), vb = Cin % 4 == 0 && aligned16(h);
     const bool al = va && vb && (PW ? (H * W) % 32 == 0 : W % 32 == 0);

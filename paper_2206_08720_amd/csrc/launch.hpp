@@ -46,6 +46,13 @@ enum KernelClass {
   KC_STRUCT_FWD,     // depthwise / scale / pool forward
   KC_STRUCT_BWD,     // depthwise / scale / pool backward
   KC_STRUCT_WGRAD,   // depthwise / scale / bias weight-space cotangents (pixel sums)
+  // products on f16 pairs (pair_core.hpp) and their preparation
+  KC_PAIR_ROWS,       // pair rows of the weights and cotangents, image maxima
+  KC_PAIR_PREP,       // the same with the Grams, one launch (small fully-connected nets)
+  KC_DENSE_BWD_PAIR,
+  KC_NTK_FCN_PAIR,
+  KC_CONV_BWD_PAIR,
+  KC_CONV_WGRAD_PAIR,
   KC_COUNT
 };
 const char* kernel_class_name(int cls);

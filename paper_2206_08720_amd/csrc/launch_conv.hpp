@@ -59,6 +59,8 @@ hipError_t launch_conv_wgrad(hipStream_t s, const float* G, const float* h, int 
 hipError_t launch_pw_wgrad(hipStream_t s, const float* G, const float* h, int images, int O, int H,
                            int W, int C, int Cin, float* J, long long ldJ, long long off,
                            const ConvPairWgrad* pair = nullptr, bool* bias_done = nullptr);
+// Whether a weight-space product given `pair` takes its pair form (Cin: the padded count in the padded form).
+bool conv_wgrad_takes_pairs(int images, int O, int H, int W, int C, int Cin, bool pw);
 // Everything the pair products of one CNN evaluation need that does not depend on the backward, in
 // one launch: the pair rows of the flipped kernels (N[z] rows of 9 taps of C[z] channels), the
 // largest magnitude of each image of the layer inputs x[j] ([M, plane[j]] -> hmax[j]), the bound

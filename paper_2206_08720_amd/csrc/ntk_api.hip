@@ -27,7 +27,8 @@ const char* kernel_class_name(int cls) {
   static const char* names[KC_COUNT] = {
       "dense_fwd", "dense_bwd", "bwd_seed",  "gram",       "ntk_fcn",    "transpose",    "conv_fwd",
       "conv_bwd",  "conv_seed", "gap",       "conv_wgrad", "ntk_splitk", "ntk_reduce", "conv_pairsum",
-      "copy",      "ntk_diag",  "jc_jacobian", "vp_elementwise", "struct_fwd", "struct_bwd", "struct_wgrad"};
+      "copy",      "ntk_diag",  "jc_jacobian", "vp_elementwise", "struct_fwd", "struct_bwd", "struct_wgrad",
+      "pair_rows", "pair_prep", "dense_bwd_pair", "ntk_fcn_pair", "conv_bwd_pair", "conv_wgrad_pair"};
   return (cls >= 0 && cls < KC_COUNT) ? names[cls] : "?";
 }
 
@@ -887,9 +888,9 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
   auto transposes = [&](hipStream_t st) -> int {
     if (pair) {
       if (prep) return NTK_OK;
-      prof_begin(P, st, KC_TRANSPOSE);
+      prof_begin(P, st, KC_PAIR_ROWS);
       hipError_t err = launch_pair_weights(st, pair_weights());
-      prof_end(P, st, KC_TRANSPOSE);
+      prof_end(P, st, KC_PAIR_ROWS);
       return err == hipSuccess ? NTK_OK : hip_fail(h, err, "weight pair rows");
     }
     if (L < 2 || bwd_w) return NTK_OK;
@@ -1087,24 +1088,26 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
     if (aux && (e = hipStreamWaitEvent(s, h->ev_tr, 0)) != hipSuccess) return hip_fail(h, e, "stream join");
     if (L >= 1) {
       if (pair) {
-        prof_begin(P, s, KC_BWD_SEED);
+        const int cls = prep ? KC_PAIR_PREP : KC_PAIR_ROWS;
+        prof_begin(P, s, cls);
         if (prep)
           e = launch_pair_prep(s, pair_weights(), WL, F(h->off_dphi[L - 1]), M * Oe, Oe, h->dims[L], Gp(L - 1),
                                Ge(L - 1), F(h->off_rmax[(L - 1) & 1]), gram_batch(), n1, n2, h->num_cu);
         else
           e = seed_pairs(s, 0, M);
-        prof_end(P, s, KC_BWD_SEED);
+        prof_end(P, s, cls);
         if (e != hipSuccess) return hip_fail(h, e, "readout cotangents");
       }
       if (split && (rc = fork(h->ev_seed, s, aux)) != NTK_OK) return rc;
-      prof_begin(P, s, KC_DENSE_BWD);
+      const int cls = pair ? KC_DENSE_BWD_PAIR : KC_DENSE_BWD;
+      prof_begin(P, s, cls);
       for (int l = L - 1; l >= 1; --l) {
         e = bwd_layer(s, l, 0, MA);
         if (e == hipSuccess && split) e = bwd_layer(aux, l, MA, M);
         if (e != hipSuccess) return hip_fail(h, e, "dense backward");
       }
       if (split && (rc = fork(h->ev_bwd, aux, s)) != NTK_OK) return rc;
-      prof_end(P, s, KC_DENSE_BWD);
+      prof_end(P, s, cls);
     }
     if (!jc && aux && (e = hipStreamWaitEvent(s, h->ev_gram, 0)) != hipSuccess)
       return hip_fail(h, e, "stream join");
@@ -1196,9 +1199,10 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
   }
   c.gram_readout = F(h->off_gram[L]);
   c.readout_scale = 1.f;
-  prof_begin(P, s, KC_NTK_FCN);
+  const int cls = pair ? KC_NTK_FCN_PAIR : KC_NTK_FCN;
+  prof_begin(P, s, cls);
   e = launch_ntk_fcn(s, c, n1, n2, O, sym ? 1 : 0, theta, h->num_cu, h->lean ? nullptr : F(h->off_skpart));
-  prof_end(P, s, KC_NTK_FCN);
+  prof_end(P, s, cls);
   if (e != hipSuccess) return hip_fail(h, e, "ntk contraction");
   return NTK_OK;
 }
@@ -1511,10 +1515,10 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
         cm.plane[cm.count] = h->bh[l] * h->bw[l] * h->ch[l];
         ++cm.count;
       }
-      prof_begin(P, s, KC_TRANSPOSE);
+      prof_begin(P, s, KC_PAIR_ROWS);
       e = launch_conv_prep(s, cp, cf);
       if (e == hipSuccess) e = launch_conv_max(s, cm);
-      prof_end(P, s, KC_TRANSPOSE);
+      prof_end(P, s, KC_PAIR_ROWS);
       if (e != hipSuccess) return hip_fail(h, e, "pair preparation");
     }
   }
@@ -1526,17 +1530,23 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
   // weight-space product of layer l's 3x3 (pw: pointwise) convolution: inputs with Cin % 4 != 0
   // padded to the direct-to-LDS form when possible
   auto wgrad = [&](int l, const float* G, int Orows, float* Jout, long long ldJ, long long off, bool pw,
-                   long long bias, bool* bias_done) {
+                   long long bias, bool* bias_done) -> hipError_t {
     const int Hl = h->bh[l], Wl = h->bw[l], cin = h->ch[l], cout = h->ch[l + 1];
     float* xp = h->off_xpad ? F(h->off_xpad) : nullptr;
     // the folded layer's "cotangent" is act' itself
     const ConvPairWgrad pg{fold && l == ll ? nullptr : bound[l].gmax, bound[l].fac, act_bound(l),
                            F(h->off_hmax) + l * hm_ld, bias};
-    const ConvPairWgrad* pr = cpair ? &pg : nullptr;
-    if (xp && conv_wgrad_pad_ok(M, Orows, Hl, Wl, cout, cin, G, xp))
-      return launch_conv_wgrad_padded(s, G, hptr(l), xp, M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pw, pr, bias_done);
-    return pw ? launch_pw_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr, bias_done)
-              : launch_conv_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr, bias_done);
+    const bool padded = xp && conv_wgrad_pad_ok(M, Orows, Hl, Wl, cout, cin, G, xp);
+    const ConvPairWgrad* pr =
+        cpair && conv_wgrad_takes_pairs(M, Orows, Hl, Wl, cout, padded ? (cin + 3) & ~3 : cin, pw) ? &pg : nullptr;
+    const int cls = pr ? KC_CONV_WGRAD_PAIR : KC_CONV_WGRAD;
+    prof_begin(P, s, cls);
+    const hipError_t err =
+        padded ? launch_conv_wgrad_padded(s, G, hptr(l), xp, M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pw, pr, bias_done)
+        : pw   ? launch_pw_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr, bias_done)
+               : launch_conv_wgrad(s, G, hptr(l), M, Orows, Hl, Wl, cout, cin, Jout, ldJ, off, pr, bias_done);
+    prof_end(P, s, cls);
+    return err;
   };
   float* J = F(h->off_J);
   // the folded layer's A: in J past this call's columns (J holds that layer's O C F Cin columns
@@ -1554,10 +1564,8 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
       // A [M, C, F Cin] from act'(z) in place of the O cotangents (the "fold" above), in J past
       // the columns of this call
       const float* dz = F(h->off_cdphi[ll]);
-      prof_begin(P, s, KC_CONV_WGRAD);
       e = L.kind == NTK_CONV3X3_SAME ? wgrad(l, dz, 1, fold_A, 9LL * cin * cout, 0, false, -1, nullptr)
                                      : wgrad(l, dz, 1, fold_A, (long long)cin * cout, 0, true, -1, nullptr);
-      prof_end(P, s, KC_CONV_WGRAD);
       if (e != hipSuccess) return hip_fail(h, e, "last convolution's channel cotangents");
       if (L.has_bias) {
         prof_begin(P, s, KC_STRUCT_WGRAD);
@@ -1574,9 +1582,7 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
         if (e != hipSuccess) return hip_fail(h, e, "conv inside-out pair sum");
         theta_written = true;
       } else {
-        prof_begin(P, s, KC_CONV_WGRAD);
         e = wgrad(l, Gcur, Oe, J, Kcall, jw[l], false, L.has_bias ? jb[l] : -1, &bias_done);
-        prof_end(P, s, KC_CONV_WGRAD);
         if (e != hipSuccess) return hip_fail(h, e, "conv weight-space cotangent");
       }
       if (L.has_bias && !bias_done) {
@@ -1593,9 +1599,7 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
         prof_end(P, s, KC_CONV_PAIRSUM);
         theta_written = true;
       } else {
-        prof_begin(P, s, KC_CONV_WGRAD);
         e = wgrad(l, Gcur, Oe, J, Kcall, jw[l], true, L.has_bias ? jb[l] : -1, &bias_done);
-        prof_end(P, s, KC_CONV_WGRAD);
       }
       if (e == hipSuccess && L.has_bias && !bias_done) {
         prof_begin(P, s, KC_STRUCT_WGRAD);
@@ -1614,12 +1618,13 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
       // to the cotangent of layer l-1's pre-activation (its output, when it has no activation)
       const float* dprev = h->wslot[l - 1] >= 0 ? F(h->off_cdphi[l - 1]) : nullptr;
       if (L.kind == NTK_CONV3X3_SAME) {
-        prof_begin(P, s, KC_CONV_BWD);
         const ConvPairBwd pb{bound[l].gmax, bound[l].fac, cpair && h->off_Kp[l] ? F(h->off_Kp[l]) : nullptr,
                              cpair && h->off_Kp[l] ? I(h->off_ke[l]) : nullptr};
+        const int cls = pb.Kp ? KC_CONV_BWD_PAIR : KC_CONV_BWD;
+        prof_begin(P, s, cls);
         e = launch_conv_bwd(s, Gcur, M, Oe, Hl, Wl, cout, F(h->off_Kt[l]), cin, dprev, Gnext, pb.Kp ? &pb : nullptr,
                             cpair ? gmax(l - 1) : nullptr);
-        prof_end(P, s, KC_CONV_BWD);
+        prof_end(P, s, cls);
       } else if (L.kind == NTK_CONV1X1) {
         prof_begin(P, s, KC_CONV_BWD);
         int rows;
