@@ -94,49 +94,54 @@ struct TransposeBatch {
 hipError_t launch_transpose_batch(hipStream_t s, const TransposeBatch& b);
 
 // ---- fp32 products on the f16 matrix cores (pair rows, pair_core.hpp) ----------------------
-// The transposed weights of all layers as pair rows: out[z] holds N[z] rows of pair_stride(K[z])
-// floats for W[z] [K, N]; exps[z][n] the row exponents; l1[z][i] the largest sum_k |W[k, n]| of
-// the i-th strip of kPairStrip columns (cdiv(N, kPairStrip) strips).
-constexpr int kPairStrip = 64;
+// The transposed weights of all layers as balanced pair rows (kernels_pair.hip): out[z] holds N[z]
+// rows of pair_stride(K[z]) floats for W[z] [K, N] with row k scaled by 2^-kexps[z][k]; exps[z][n] the
+// rows' exponents.  launch_pair_wstats writes kexps and kfac = 2^kexps (pair_stride(K) of each; 0 and 1
+// past K) and the scratch that launch_pair_weights reads.
 template <int ML>
 struct PairWeightsT {
   const float* W[ML];
   float* out[ML];
   int* exps[ML];
-  float* l1[ML];
-  float* stats[ML];   // scratch, pair_stats_floats(K, N)
+  int* kexps[ML];
+  float* kfac[ML];
+  int* stats[ML];   // scratch, pair_stats_ints(K, N)
   int K[ML], N[ML];
   int count;
 };
 using PairWeights = PairWeightsT<kMaxLayers>;
-long long pair_stats_floats(long long K, long long N);
+long long pair_stats_ints(long long K, long long N);
+hipError_t launch_pair_wstats(hipStream_t s, const PairWeights& b);
 hipError_t launch_pair_weights(hipStream_t s, const PairWeights& b);
-// Pair rows of Wr[o, c] dphi[n, c], r = (n, o) < R, c < K; exponents and the rows' largest scaled
-// elements.
-hipError_t launch_pair_seed(hipStream_t s, const float* Wr, const float* dphi, int R, int O, int K, float* out,
-                            int* exps, float* rmax);
+// Pair rows (stride pair_stride(K)) of R rows r = (n, o) of K floats: of `in` (row stride ldin), or,
+// with in null, of Wr[o, c] dphi[n, c].
+struct PairRows {
+  const float* in;
+  long long ldin;
+  const float* Wr;
+  const float* dphi;
+  FastDiv fO;
+  int R, K;
+  float* out;          // the rows as they are (may be `in` with ldin = pair_stride(K)) and their
+  int* exps;           //   exponents, or null
+  const float* kfac;   // the rows with column k scaled by kfac[k], and their exponents, or null
+  float* bout;
+  int* bexps;
+};
+hipError_t launch_pair_rows(hipStream_t s, const PairRows& p);
 // One layer of the cotangent backward, out[r, n] = (sum_k G[r, k] W[k, n]) * dphi[r / O, n].
 struct PairBwd {
-  const float* G;         // pair rows [R, Kp]
+  const float* G;         // balanced pair rows [R, Kp]
   const int* exps_in;     // [R]
-  const float* rmax_in;   // rmax_parts x [rmax_ld]: maxima of scaled |G| over parts of a row
-  int rmax_parts;
-  long long rmax_ld;
-  const float* W;         // pair rows of the transposed weights [N, Kp]
+  const float* W;         // balanced pair rows of the transposed weights [N, Kp]
   const int* wexps;       // [N]
-  const float* l1;        // l1_parts column-sum maxima
-  int l1_parts;
-  int act_exp;            // |dphi| <= 2^act_exp
   const float* dphi;      // [R / O, N]
   int R, N, Kp;
   FastDiv fO;
-  float* out;             // pair rows [R, pair_stride(N)], or null
-  float* out32;           // fp32 rows [R, N], or null
-  int* exps_out;          // [R]
-  float* rmax_out;        // pair_bwd_parts x [rmax_ld]
+  float* out;             // fp32 rows [R, ldo]
+  long long ldo;
   int vec;                // set by the launcher
 };
-int pair_bwd_parts(int R, int N, int num_cu);
 hipError_t launch_pair_bwd(hipStream_t s, PairBwd p, int num_cu);
 
 template <int ML>
@@ -152,9 +157,10 @@ using GramBatch = GramBatchT<kMaxLayers + 1>;
 // out_l[n1, n2] = h1_l[n1] . h2_l[n2] + beta_l for every l (rows of h have stride K_l).
 // Batches whose 64 x 64 tiles would not fill num_cu compute units run in 16 x 16 blocks.
 hipError_t launch_gram(hipStream_t s, const GramBatch& g, int N1, int N2, int num_cu);
-// launch_pair_weights, launch_pair_seed and launch_gram, in one launch for small problems.
-hipError_t launch_pair_prep(hipStream_t s, const PairWeights& b, const float* Wr, const float* dphi, int R, int O, int K,
-                            float* out, int* exps, float* rmax, const GramBatch& g, int N1, int N2, int num_cu);
+// launch_pair_weights, launch_pair_rows (of the seed) and launch_gram, in one launch for small
+// problems.
+hipError_t launch_pair_prep(hipStream_t s, const PairWeights& b, const PairRows& p, const GramBatch& g, int N1, int N2,
+                            int num_cu);
 // launch_dense_bwd_w and launch_gram together, in one launch where the layer's tiles leave
 // compute units idle and the Grams take 16 x 16 blocks.
 hipError_t launch_dense_bwd_w_gram(hipStream_t s, const float* G, const float* W, const float* dphi, int R, int N,

@@ -144,13 +144,10 @@ struct ntk_handle {
   bool pair = false;
   size_t off_ge = 0;              // exponents of the rows of G_l                  [L, Mmax*O]
   std::vector<size_t> off_we;     // exponents of the rows of Wt_l, l = 1..L-1     [d_l]
-  std::vector<size_t> off_l1;     // column-sum maxima of W_l                      [strips of d_l]
+  std::vector<size_t> off_kd;     // exponents of the rows of W_l, their powers    [2, d_{l+1} padded]
   std::vector<size_t> off_ws;     // column statistics of W_l by row chunks
-  size_t off_rmax[2] = {0, 0};    // row maxima of two neighbouring layers         [parts, Mmax*O]
-  // pair rows of two neighbouring layers, for the variants (their contractions read the fp32 rows
-  // of G_l): allocated when an option selects a variant; null: the variants' backward in fp32
-  char* gp_ws = nullptr;
-  size_t gp_bytes = 0;            // of one layer, [Mmax*O, padded]
+  size_t off_Gb = 0, off_be = 0;  // balanced pair rows of the layer the backward is at, exponents
+  size_t gb_ld = 0;               // [Mmax*O, widest padded row]
   int num_cu = 0;                 // compute units of the device (stream-K workgroup count)
   size_t off_skpart = 0;          // stream-K partial tiles of the contraction
   size_t off_fpart = 0;           // fp64 split-K partials of the small-batch forward
@@ -374,7 +371,7 @@ static bool pair_in_range(const ntk_handle& t) {
   for (size_t l = 0; l + 1 < t.layers.size(); ++l) {
     const long long in = t.layers[l].in, out = t.layers[l].out;
     if (smul(MO, pair_stride(out)) > kMaxElems || smul(in, pair_stride(out)) > kMaxElems ||
-        smul(MO, (out + 63) / 64) > kMaxElems || !dma_span_ok(pair_stride(out), pair_stride(out), 256))
+        !dma_span_ok(pair_stride(out), pair_stride(out), 256))
       return false;
   }
   return true;
@@ -411,20 +408,18 @@ static void plan_fcn(ntk_handle* h) {
   for (int l = 1; l < L; ++l) h->off_Wt[l] = take((size_t)h->dims[l] * row(h->dims[l + 1]));
   if (h->pair) {
     h->off_we.assign(std::max(L, 1), 0);
-    h->off_l1.assign(std::max(L, 1), 0);
+    h->off_kd.assign(std::max(L, 1), 0);
     h->off_ws.assign(std::max(L, 1), 0);
     h->off_ge = take((size_t)L * Mmax * O);
-    size_t parts = 1, widest = 0;
-    for (int l = 0; l < L; ++l) {
-      parts = std::max(parts, (size_t)(h->dims[l + 1] + 63) / 64);
-      widest = std::max(widest, row(h->dims[l + 1]));
-      if (l == 0) continue;
+    h->off_be = take(Mmax * O);
+    h->gb_ld = 0;
+    for (int l = 1; l < L; ++l) {
+      h->gb_ld = std::max(h->gb_ld, row(h->dims[l + 1]));
       h->off_we[l] = take(h->dims[l]);
-      h->off_l1[l] = take((h->dims[l] + kPairStrip - 1) / kPairStrip);
-      h->off_ws[l] = take((size_t)pair_stats_floats(h->dims[l + 1], h->dims[l]));
+      h->off_kd[l] = take(2 * row(h->dims[l + 1]));
+      h->off_ws[l] = take((size_t)pair_stats_ints(h->dims[l + 1], h->dims[l]));
     }
-    for (int i = 0; i < 2 && L >= 1; ++i) h->off_rmax[i] = take(parts * Mmax * O);
-    h->gp_bytes = L >= 2 ? align_up(Mmax * O * widest * 4) : 0;
+    h->off_Gb = take(Mmax * O * h->gb_ld);
   }
   for (int l = 0; l <= L; ++l) h->off_gram[l] = take((size_t)h->max_n1 * h->max_n2);
   if (h->lean) {   // the full theta only: no stream-K, no split forward, no one-output variants
@@ -806,12 +801,14 @@ static int fcn_forward(ntk_handle* h, const float* const* params, const float* X
 }
 
 // Whether the backward (and the contraction of `pairs` input pairs) of a fully-connected net runs
-// on pair rows.  It costs one more launch (the weights' and the seed's pair rows), so small
-// problems keep the fp32 kernels: equal at 3.7 GFLOP on widths that take the direct-to-LDS fp32
-// kernels (64 + 64 samples, width 512, depth 4: 85.2 against 83.8 us; 1.4 GFLOP, width 128:
-// 55.0 against 57.3), below 1 GFLOP on widths that do not (width 250, depth 4: 122 against
-// 90 us).  Layers narrower than 128 keep fp32: sums that short are no more exact on pairs.
-constexpr double kPairMinFlops = 3e9, kPairMinFlopsRagged = 5e8;
+// on pair rows.  It costs launches (the weights' statistics and pair rows, a pass over the rows per
+// layer), so small problems keep the fp32 kernels.  Widths that take the direct-to-LDS fp32 kernels
+// are even at 7.8 GFLOP (width 512, depth 4: 103 us in fp32, 106 on pairs at 5.4 GFLOP; 130.5, 130.4 at
+// 7.8; 196, 169 at 10.7; width 128: 129, 133 at 7.2; width 1024: 186, 168 at 11.4; the batch diagonal of
+// width 512: 153.4, 152.5 at 8.1); those that do not, below 0.5 GFLOP (widths 500, 401, 333: 112, 92 at
+// 0.7; width 250: 113, 107 at 0.4).  Layers narrower than 128 keep fp32: sums that short are no more
+// exact on pairs.
+constexpr double kPairMinFlops = 8e9, kPairMinFlopsRagged = 5e8;
 static bool fcn_pair_pays(const ntk_handle* h, int M, int Oe, double pairs) {
   double flops = 0;
   bool ragged = false;
@@ -861,14 +858,10 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
   const bool full = !logit && !trace && !diag;
   const bool pair = h->pair && !jc && L >= 1 && fcn_pair_pays(h, M, Oe, full ? (sym ? 0.5 : 1.0) * n1 * n2 : 0.0) &&
                     (full ? ntk_fcn_pair_ok((long long)n1 * O, (long long)n2 * O, L, sym ? 1 : 0, h->num_cu, true)
-                          : L >= 2 && h->gp_ws);
+                          : L >= 2);
   auto I = [&](size_t off) { return reinterpret_cast<int*>(h->ws + off); };
-  auto Gp = [&](int l) {
-    return full ? F(h->off_G[l]) : reinterpret_cast<float*>(h->gp_ws + (l & 1) * h->gp_bytes);
-  };
   const size_t ge_ld = ((size_t)h->max_n1 + h->max_n2) * O;
   auto Ge = [&](int l) { return I(h->off_ge) + l * ge_ld; };
-  int gparts[2] = {1, 1};   // parts of the row maxima of the layer above, per half
   auto pair_weights = [&]() {
     PairWeights pw{};
     pw.count = std::max(0, L - 1);
@@ -876,8 +869,9 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
       pw.W[l - 1] = params[h->param_index[l]];
       pw.out[l - 1] = F(h->off_Wt[l]);
       pw.exps[l - 1] = I(h->off_we[l]);
-      pw.l1[l - 1] = F(h->off_l1[l]);
-      pw.stats[l - 1] = F(h->off_ws[l]);
+      pw.kexps[l - 1] = I(h->off_kd[l]);
+      pw.kfac[l - 1] = F(h->off_kd[l]) + pair_stride(h->dims[l + 1]);
+      pw.stats[l - 1] = I(h->off_ws[l]);
       pw.K[l - 1] = h->dims[l + 1];
       pw.N[l - 1] = h->dims[l];
     }
@@ -887,9 +881,9 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
   const bool prep = pair && !aux && !diag;
   auto transposes = [&](hipStream_t st) -> int {
     if (pair) {
-      if (prep) return NTK_OK;
       prof_begin(P, st, KC_PAIR_ROWS);
-      hipError_t err = launch_pair_weights(st, pair_weights());
+      hipError_t err = launch_pair_wstats(st, pair_weights());
+      if (err == hipSuccess && !prep) err = launch_pair_weights(st, pair_weights());
       prof_end(P, st, KC_PAIR_ROWS);
       return err == hipSuccess ? NTK_OK : hip_fail(h, err, "weight pair rows");
     }
@@ -950,14 +944,34 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
   // alone in NTK_OUTPUT_LOGIT: the cotangent rows are then (n) instead of (n, o)): written by the
   // epilogue of the last forward layer, G[n, o, c] = WL[o, c] act'(z[n, c])
   const float* WL = params[h->param_index[L]] + (logit ? (size_t)h->opt_logit * h->dims[L] : 0);
-  // the readout cotangents of the samples [r0, r1) as pair rows
-  auto seed_pairs = [&](hipStream_t st, int r0, int r1) -> hipError_t {
-    const int l = L - 1, K = h->dims[L];
-    gparts[r0 ? 1 : 0] = 1;
-    return launch_pair_seed(st, WL, F(h->off_dphi[l]) + (size_t)r0 * K, (r1 - r0) * Oe, Oe, K,
-                            Gp(l) + (size_t)r0 * Oe * pair_stride(K), Ge(l) + (size_t)r0 * Oe,
-                            F(h->off_rmax[l & 1]) + (size_t)r0 * Oe);
+  // Pair rows of G_l for the samples [r0, r1): for the full contraction in place of its fp32 rows, and
+  // balanced for the backward, in one buffer for all layers (the two halves of the samples run on
+  // streams of their own and may be at different layers, so a half's rows start at the same place in
+  // every layer).
+  auto pair_rows = [&](int l, int r0, int r1, bool seed) {
+    const size_t row0 = (size_t)r0 * Oe;
+    const int K = h->dims[l + 1];
+    PairRows p{};
+    if (seed) {
+      p.Wr = WL;
+      p.dphi = F(h->off_dphi[l]) + (size_t)r0 * K;
+    } else {
+      p.ldin = full ? pair_stride(K) : K;
+      p.in = F(h->off_G[l]) + row0 * p.ldin;
+    }
+    p.fO = FastDiv((uint32_t)Oe);
+    p.R = (r1 - r0) * Oe;
+    p.K = K;
+    p.out = full ? F(h->off_G[l]) + row0 * pair_stride(K) : nullptr;
+    p.exps = Ge(l) + row0;
+    if (l >= 1) {
+      p.kfac = F(h->off_kd[l]) + pair_stride(K);
+      p.bout = F(h->off_Gb) + row0 * h->gb_ld;
+      p.bexps = I(h->off_be) + row0;
+    }
+    return p;
   };
+  auto seed_pairs = [&](hipStream_t st, int r0, int r1) { return launch_pair_rows(st, pair_rows(L - 1, r0, r1, true)); };
   // one layer of the cotangent backward for the samples [r0, r1)
   auto bwd_layer = [&](hipStream_t st, int l, int r0, int r1) -> hipError_t {
     const size_t K = h->dims[l + 1], N = h->dims[l];
@@ -965,26 +979,18 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
       const size_t row0 = (size_t)r0 * Oe;
       PairBwd b{};
       b.Kp = (int)pair_stride(K);
-      b.G = Gp(l) + row0 * b.Kp;
-      b.exps_in = Ge(l) + row0;
-      b.rmax_in = F(h->off_rmax[l & 1]) + row0;
-      b.rmax_parts = gparts[r0 ? 1 : 0];
-      b.rmax_ld = (long long)M * Oe;
+      b.G = F(h->off_Gb) + row0 * h->gb_ld;
+      b.exps_in = I(h->off_be) + row0;
       b.W = F(h->off_Wt[l]);
       b.wexps = I(h->off_we[l]);
-      b.l1 = F(h->off_l1[l]);
-      b.l1_parts = (int)(N + kPairStrip - 1) / kPairStrip;
-      b.act_exp = h->layers[l - 1].act == NTK_ACT_ERF ? 1 : 0;   // |erf'| <= 2 / sqrt(pi)
       b.dphi = F(h->off_dphi[l - 1]) + (size_t)r0 * N;
       b.R = (r1 - r0) * Oe;
       b.N = (int)N;
       b.fO = FastDiv((uint32_t)Oe);
-      b.out = full || l > 1 ? Gp(l - 1) + row0 * pair_stride(N) : nullptr;
-      b.out32 = full ? nullptr : F(h->off_G[l - 1]) + row0 * N;
-      b.exps_out = Ge(l - 1) + row0;
-      b.rmax_out = F(h->off_rmax[(l - 1) & 1]) + row0;
-      gparts[r0 ? 1 : 0] = pair_bwd_parts(b.R, b.N, h->num_cu);
-      return launch_pair_bwd(st, b, h->num_cu);
+      b.ldo = full ? pair_stride(N) : (long long)N;
+      b.out = F(h->off_G[l - 1]) + row0 * b.ldo;
+      hipError_t err = launch_pair_bwd(st, b, h->num_cu);
+      return err == hipSuccess ? launch_pair_rows(st, pair_rows(l - 1, r0, r1, false)) : err;
     }
     if (bwd_w && gram_in_bwd && l == L - 1)
       return launch_dense_bwd_w_gram(st, F(h->off_G[l]) + (size_t)r0 * Oe * K, params[h->param_index[l]],
@@ -1091,8 +1097,7 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
         const int cls = prep ? KC_PAIR_PREP : KC_PAIR_ROWS;
         prof_begin(P, s, cls);
         if (prep)
-          e = launch_pair_prep(s, pair_weights(), WL, F(h->off_dphi[L - 1]), M * Oe, Oe, h->dims[L], Gp(L - 1),
-                               Ge(L - 1), F(h->off_rmax[(L - 1) & 1]), gram_batch(), n1, n2, h->num_cu);
+          e = launch_pair_prep(s, pair_weights(), pair_rows(L - 1, 0, M, true), gram_batch(), n1, n2, h->num_cu);
         else
           e = seed_pairs(s, 0, M);
         prof_end(P, s, cls);
@@ -2341,7 +2346,6 @@ extern "C" int ntk_free(ntk_handle* h) {
   if (h->ws) (void)hipFree(h->ws);
   destroy_sync_objects(h);
   if (h->jc_ws) (void)hipFree(h->jc_ws);
-  if (h->gp_ws) (void)hipFree(h->gp_ws);
   if (h->vp_ws) (void)hipFree(h->vp_ws);
   delete h;
   return NTK_OK;
@@ -2349,16 +2353,6 @@ extern "C" int ntk_free(ntk_handle* h) {
 
 extern "C" const char* ntk_last_error(const ntk_handle* h) {
   return h ? h->err.c_str() : g_init_error.c_str();
-}
-
-// The variants' pair-row buffers; without them (no memory, or not asked for yet) the variants'
-// backward stays on fp32 rows.
-static void ensure_variant_pairs(ntk_handle* h) {
-  if (h->cnn || !h->pair || h->gp_ws || !h->gp_bytes) return;
-  if (hipMalloc((void**)&h->gp_ws, 2 * h->gp_bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    h->gp_ws = nullptr;
-  }
 }
 
 extern "C" int ntk_set_option(ntk_handle* h, int option, int value) {
@@ -2378,7 +2372,6 @@ extern "C" int ntk_set_option(ntk_handle* h, int option, int value) {
     if (value != NTK_OUTPUT_FULL && value != NTK_OUTPUT_TRACE && value != NTK_OUTPUT_LOGIT)
       return fail(h, NTK_E_ARG, "NTK_OPT_OUTPUT takes NTK_OUTPUT_FULL, _TRACE or _LOGIT");
     h->opt_output = value;
-    if (value != NTK_OUTPUT_FULL) ensure_variant_pairs(h);
     return NTK_OK;
   }
   if (option == NTK_OPT_LOGIT) {
@@ -2406,7 +2399,6 @@ extern "C" int ntk_set_option(ntk_handle* h, int option, int value) {
     if (value != NTK_BATCH_FULL && value != NTK_BATCH_DIAGONAL)
       return fail(h, NTK_E_ARG, "NTK_OPT_BATCH takes NTK_BATCH_FULL or NTK_BATCH_DIAGONAL");
     h->opt_batch = value;
-    if (value != NTK_BATCH_FULL) ensure_variant_pairs(h);
     return NTK_OK;
   }
   return fail(h, NTK_E_ARG, "unknown option");

@@ -39,6 +39,21 @@ constexpr int kPairTop = 15;
 // finite either way)
 __device__ __forceinline__ int pair_exp(float m) { return (m > 0.f && m < __builtin_inff()) ? ilogbf(m) + 1 : 0; }
 
+// The same with the elements' own exponents, as integers, so that exponents of rows and of columns add
+// up without leaving the range of a float: |x| < 2^pair_e(x) for a finite x != 0; a value that is not
+// finite sets no exponent (its row's sums are not finite in any case).
+constexpr int kPairNone = -4096;
+__device__ __forceinline__ int pair_e(float x) {
+  const float a = fabsf(x);
+  return a > 0.f && a < __builtin_inff() ? __builtin_amdgcn_frexp_expf(x) : kPairNone;
+}
+__device__ __forceinline__ float pair_max(float m, float x) {
+  const float a = fabsf(x);
+  return a < __builtin_inff() ? fmaxf(m, a) : m;
+}
+// the row's exponent from its elements' largest one
+__device__ __forceinline__ int pair_row_e(int e) { return (e <= kPairNone / 2 ? 0 : e) - kPairTop; }
+
 __device__ __forceinline__ void pair_split(float v, _Float16& hi, _Float16& lo) {
   hi = (_Float16)v;
   lo = (_Float16)(v - (float)hi);
