@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "index_math.hpp"
+#include "launch.hpp"
 
 namespace ntk {
 
@@ -394,21 +395,65 @@ __device__ __forceinline__ const float& at_bytes(const float* base, uint32_t byt
 // r0 + 8*(v/4) + 4*(l/32) + v%4 (v = 0..15) of column l%32 of the fragment.
 __device__ __forceinline__ int frag_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
+// Integer maxima of the bits of magnitudes: order-free, so deterministic.
+__device__ __forceinline__ void gmax_update(float* gmax, float m) {
+  atomicMax(reinterpret_cast<unsigned*>(gmax), __float_as_uint(m));
+}
+// The maxima of one cotangent image's values that a lane has seen, and their way to memory (WIDTH lanes
+// hold values of the same image; every lane of them takes part).
+struct ImageMaxLane {
+  float a = 0.f, b = 0.f;
+  __device__ __forceinline__ void add(float x, float f) {
+    a = fmaxf(a, fabsf(x));
+    b = fmaxf(b, fabsf(x * f));
+  }
+  template <int WIDTH = 64>
+  __device__ __forceinline__ void flush(const ImageMax& mx, int image, bool write = true) const {
+    float u = a, v = b;
+#pragma unroll
+    for (int q = WIDTH / 2; q; q >>= 1) u = fmaxf(u, __shfl_xor(u, q));
+    if (mx.bal) {
+#pragma unroll
+      for (int q = WIDTH / 2; q; q >>= 1) v = fmaxf(v, __shfl_xor(v, q));
+    }
+    if ((threadIdx.x & (WIDTH - 1)) == 0 && write) {
+      gmax_update(mx.raw + image, u);
+      if (mx.bal) gmax_update(mx.bal + image, v);
+    }
+  }
+  // The same from a workgroup of four waves on one image: one update, since updates of an address are
+  // serialized across the XCDs.
+  __device__ __forceinline__ void flush_block(const ImageMax& mx, int image) const {
+    __shared__ float red[4][2];
+    float u = a, v = b;
+#pragma unroll
+    for (int q = 32; q; q >>= 1) {
+      u = fmaxf(u, __shfl_xor(u, q));
+      v = fmaxf(v, __shfl_xor(v, q));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      red[threadIdx.x >> 6][0] = u;
+      red[threadIdx.x >> 6][1] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < (mx.bal ? 2 : 1))
+      gmax_update((threadIdx.x ? mx.bal : mx.raw) + image,
+                  fmaxf(fmaxf(red[0][threadIdx.x], red[1][threadIdx.x]), fmaxf(red[2][threadIdx.x], red[3][threadIdx.x])));
+    __syncthreads();
+  }
+};
+
 // Epilogue of the cotangent backward through a convolution (3x3 or pointwise):
 // out[r, c] = acc[r, c] * dphi[img*D + p, c] for rows r = (img*O + o)*D + p of the O cotangent
 // images of each image (null dphi: the identity).  A fragment that lies inside R and inside
 // one cotangent image (no multiple of D in (r0, r0 + 31]) maps to 32 consecutive rows of dphi,
 // so its row arithmetic is done once and an element costs an offset, a load, a multiply and a
-// store (32-bit byte offsets: N < 2^25); other fragments take the per-element form.  With gmax,
-// gmax[r / D] (the cotangent image) also takes the largest magnitude stored, by integer maxima of
-// the bits (order-free, so deterministic).
-__device__ __forceinline__ void gmax_update(float* gmax, float m) {
-  atomicMax(reinterpret_cast<unsigned*>(gmax), __float_as_uint(m));
-}
-template <class Cfg>
-__device__ __forceinline__ void store_pixel_rows(f32x16 (&acc)[Cfg::FM][Cfg::FN], int m0, int n0,
+// store (32-bit byte offsets: N < 2^25); other fragments take the per-element form.  mx:
+// the maxima of the cotangent images r / D.
+template <class Cfg, bool MAXIMA>
+__device__ __forceinline__ void store_pixel_rows_t(f32x16 (&acc)[Cfg::FM][Cfg::FN], int m0, int n0,
                                                  const float* __restrict__ dphi, float* __restrict__ out, int R,
-                                                 int N, FastDiv fOD, FastDiv fD, float* __restrict__ gmax) {
+                                                 int N, FastDiv fOD, FastDiv fD, const ImageMax& mx) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm0 = (wave / Cfg::WAVES_N) * Cfg::WM;
@@ -423,12 +468,13 @@ __device__ __forceinline__ void store_pixel_rows(f32x16 (&acc)[Cfg::FM][Cfg::FN]
       const int img = (int)fOD.div(r0);
       float* ob = out + (long long)r0 * N;
       const float* db = dphi ? dphi + ((long long)img * D + (r0 - t0 * D)) * N : nullptr;
-      float mx = 0.f;
+      ImageMaxLane m;
 #pragma unroll
       for (int fn = 0; fn < Cfg::FN; ++fn) {
         const int c = n0 + wn0 + fn * 32 + (lane & 31);
         if (c >= N) continue;
-        if (db) {
+        const float f = MAXIMA && mx.bal ? mx.f[c] : 0.f;
+        if (dphi) {
           float d[16];
 #pragma unroll
           for (int v = 0; v < 16; ++v) d[v] = at_bytes(db, (uint32_t)(frag_row(v, lane) * N + c) * 4u);
@@ -436,21 +482,17 @@ __device__ __forceinline__ void store_pixel_rows(f32x16 (&acc)[Cfg::FM][Cfg::FN]
           for (int v = 0; v < 16; ++v) {
             const float x = acc[fm][fn][v] * d[v];
             at_bytes(ob, (uint32_t)(frag_row(v, lane) * N + c) * 4u) = x;
-            mx = fmaxf(mx, fabsf(x));
+            if (MAXIMA) m.add(x, f);
           }
         } else {
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             at_bytes(ob, (uint32_t)(frag_row(v, lane) * N + c) * 4u) = acc[fm][fn][v];
-            mx = fmaxf(mx, fabsf(acc[fm][fn][v]));
+            if (MAXIMA) m.add(acc[fm][fn][v], f);
           }
         }
       }
-      if (gmax) {
-#pragma unroll
-        for (int q = 32; q; q >>= 1) mx = fmaxf(mx, __shfl_xor(mx, q));
-        if (lane == 0) gmax_update(gmax + t0, mx);
-      }
+      if (MAXIMA) m.flush(mx, t0);
     } else {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -458,7 +500,7 @@ __device__ __forceinline__ void store_pixel_rows(f32x16 (&acc)[Cfg::FM][Cfg::FN]
         const int rc = min(r, R - 1);
         const int img = (int)fOD.div(rc), t = (int)fD.div(rc);
         const int p = rc - t * D;
-        float mx = 0.f;
+        ImageMaxLane m;
 #pragma unroll
         for (int fn = 0; fn < Cfg::FN; ++fn) {
           const int c = n0 + wn0 + fn * 32 + (lane & 31);
@@ -466,17 +508,20 @@ __device__ __forceinline__ void store_pixel_rows(f32x16 (&acc)[Cfg::FM][Cfg::FN]
             const float d = dphi ? dphi[((long long)img * D + p) * N + c] : 1.f;
             const float x = acc[fm][fn][v] * d;
             out[(long long)r * N + c] = x;
-            mx = fmaxf(mx, fabsf(x));
+            if (MAXIMA) m.add(x, mx.bal ? mx.f[c] : 0.f);
           }
         }
-        if (gmax) {   // the 32 lanes of a half-wave hold one row
-#pragma unroll
-          for (int q = 16; q; q >>= 1) mx = fmaxf(mx, __shfl_xor(mx, q));
-          if ((lane & 31) == 0 && r < R) gmax_update(gmax + t, mx);
-        }
+        if (MAXIMA) m.flush<32>(mx, t, r < R);   // the 32 lanes of a half-wave hold one row
       }
     }
   }
+}
+template <class Cfg>
+__device__ __forceinline__ void store_pixel_rows(f32x16 (&acc)[Cfg::FM][Cfg::FN], int m0, int n0,
+                                                 const float* __restrict__ dphi, float* __restrict__ out, int R,
+                                                 int N, FastDiv fOD, FastDiv fD, const ImageMax& mx) {
+  if (mx.raw) store_pixel_rows_t<Cfg, true>(acc, m0, n0, dphi, out, R, N, fOD, fD, mx);
+  else store_pixel_rows_t<Cfg, false>(acc, m0, n0, dphi, out, R, N, fOD, fD, mx);
 }
 
 // ------------------------------------------------------------------------------ loaders

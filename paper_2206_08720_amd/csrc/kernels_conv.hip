@@ -900,10 +900,15 @@ hipError_t launch_conv_flip_batch(hipStream_t s, const FlipBatch& b) {
 }
 
 // ------------------------------------------------------------------------------ pair preparation
-// One wave per row of a flipped kernel (pair rows), then workgroups that zero the maxima, one
-// workgroup per output o for the seed's bound, and one for the factors of the block-diagonal
-// layers.
-__global__ void __launch_bounds__(256) k_conv_prep(ConvPrep p, ConvFactors f, int nrow_blocks, int nzero_blocks) {
+// A row of a pair operand has the exponent of its true largest element, and where a sum runs over
+// channels of different scales (the backward) both operands are balanced, as kernels_pair.hip explains.
+// k_conv_prep: one wave per row of a flipped kernel (pair rows), one workgroup per layer for its balancing
+// factors, one per image for its O seed cotangents' maxima, then workgroups that zero the others.  The
+// seed is Wd[o, c] / D act'(z[p, c]): rounding is monotone, so its largest element over the pixels is that
+// of the channel's largest act', and the maxima of the seed need no pass over it (taken in the kernel that
+// writes it, they took that from 70 to 235 us: 1280 cotangent images of 32 x 32 x 64, six shuffles and an
+// atomic per wave and image).
+__global__ void __launch_bounds__(256) k_conv_prep(ConvPrep p, int nrow_blocks) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int bx = blockIdx.x;
   if (bx < nrow_blocks) {
@@ -913,19 +918,23 @@ __global__ void __launch_bounds__(256) k_conv_prep(ConvPrep p, ConvFactors f, in
     // nine taps of C channels, each padded to Cp
     const int C = p.C[z], Cp = (int)pair_stride(C), K = 9 * C, Kp = 9 * Cp;
     const float* __restrict__ x = p.Kt[z] + (long long)row * K;
-    float m = 0.f;
-    for (int k = lane; k < K; k += 64) m = fmaxf(m, fabsf(x[k]));
+    const float* __restrict__ km = p.kmax[z];
+    int m = kPairNone;
+    for (int k = lane; k < K; k += 64) {
+      const int e = pair_e(x[k]);
+      if (e > kPairNone) m = max(m, e - pair_bal_exp(km[k % C]));
+    }
 #pragma unroll
-    for (int q = 32; q; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
-    const int e = pair_row_exp(m);
+    for (int q = 32; q; q >>= 1) m = max(m, __shfl_xor(m, q));
+    const int e = pair_row_e(m);
     if (lane == 0) p.kexps[z][row] = e;
     for (int g = lane; g < Kp / 8; g += 64) {
       f16x8 hi, lo;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const int tap = 8 * g / Cp, c = 8 * g - tap * Cp + j;
+        const int tap = 8 * g / Cp, c = 8 * g - tap * Cp + j, cc = min(c, C - 1);
         _Float16 a, b;
-        pair_split(c < C ? ldexpf(x[tap * C + min(c, C - 1)], -e) : 0.f, a, b);
+        pair_split(c < C ? ldexpf(x[tap * C + cc], -pair_bal_exp(km[cc]) - e) : 0.f, a, b);
         hi[j] = a;
         lo[j] = b;
       }
@@ -936,54 +945,107 @@ __global__ void __launch_bounds__(256) k_conv_prep(ConvPrep p, ConvFactors f, in
     return;
   }
   bx -= nrow_blocks;
-  if (bx < nzero_blocks) {
-    for (long long i = bx * 256LL + threadIdx.x; i < p.nzero; i += (long long)nzero_blocks * 256) p.zero[i] = 0.f;
+  if (bx < p.count) {
+    const int C = p.C[bx];
+    for (int c = threadIdx.x; c < (int)pair_stride(C); c += 256)
+      p.kfac[bx][c] = c < C ? ldexpf(1.f, pair_bal_exp(p.kmax[bx][c])) : 1.f;
     return;
   }
-  bx -= nzero_blocks;
-  if (bx < p.O) {
-    float m = 0.f;
-    for (int c = lane; c < p.Cl; c += 64) m = fmaxf(m, fabsf(p.Wd[(long long)bx * p.Cl + c]));
-#pragma unroll
-    for (int q = 32; q; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
-    for (int i = threadIdx.x; i < p.M; i += 256) p.gseed[(long long)i * p.O + bx] = m * p.seed_scale;
-    return;
-  }
-  __shared__ float red[4];
-  float run = 1.f;
-  for (int i = 0; i < f.count; ++i) {
-    float m = f.w[i] ? 0.f : 1.f;
-    if (f.w[i])
-      for (int c = threadIdx.x; c < f.ch[i]; c += 256) {
-        float a = 0.f;
-        for (int t = 0; t < f.taps[i]; ++t) a += fabsf(f.w[i][(long long)t * f.ch[i] + c]);
-        m = fmaxf(m, a);
+  bx -= p.count;
+  const int nseed = p.seed ? p.M : 0;
+  if (bx < nseed) {
+    const float* __restrict__ dm = p.dmax ? p.dmax + (long long)bx * p.Cl : nullptr;
+    for (int o = wave; o < p.O; o += 4) {
+      float a = 0.f, b = 0.f;
+      for (int c = lane; c < p.Cl; c += 64) {
+        const float w = p.Wd[(long long)o * p.Cl + c] * p.inv_d;
+        const float x = fabsf(dm ? w * dm[c] : w);
+        a = fmaxf(a, x);
+        if (p.seed_kmax) b = fmaxf(b, x * ldexpf(1.f, pair_bal_exp(p.seed_kmax[c])));
       }
 #pragma unroll
-    for (int q = 32; q; q >>= 1) m = fmaxf(m, __shfl_xor(m, q));
-    if (lane == 0) red[wave] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])) * f.grow[i];
-    run = (f.chain[i] ? run : 1.f) * m;
-    if (threadIdx.x == 0) f.fac[i] = run;
-    __syncthreads();
+      for (int q = 32; q; q >>= 1) {
+        a = fmaxf(a, __shfl_xor(a, q));
+        b = fmaxf(b, __shfl_xor(b, q));
+      }
+      if (lane == 0) {
+        p.seed[(long long)bx * p.O + o] = a;
+        if (p.seed_kmax) p.seed_bal[(long long)bx * p.O + o] = b;
+      }
+    }
+    return;
   }
+  bx -= nseed;
+  const int nz = gridDim.x - nrow_blocks - p.count - nseed;
+  for (long long i = bx * 256LL + threadIdx.x; i < p.nzero; i += (long long)nz * 256) p.zero[i] = 0.f;
 }
 
-hipError_t launch_conv_prep(hipStream_t s, const ConvPrep& p, const ConvFactors& f) {
+hipError_t launch_conv_prep(hipStream_t s, const ConvPrep& p) {
   long long rows = 0;
   for (int z = 0; z < p.count; ++z) rows += p.N[z];
   const int nr = cdiv(rows, 4), nz = (int)std::min<long long>((p.nzero + 1023) / 1024, 256);
-  k_conv_prep<<<dim3(nr + nz + p.O + (f.count ? 1 : 0)), dim3(256), 0, s>>>(p, f, nr, nz);
+  const long long blocks = (long long)nr + p.count + (p.seed ? p.M : 0) + nz;
+  if (blocks <= 0) return hipSuccess;
+  k_conv_prep<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p, nr);
   return hipGetLastError();
 }
 
-// Largest magnitude of each image of several layer inputs: workgroup (image, input), eight loads in
-// flight per thread.
+// Workgroup (row, item), eight loads in flight per thread; behind the items, one image of cx each, by
+// channel: threads as groups of V channels (CL groups at a time, a power of two) by pixels.
+template <int V>
+__device__ __forceinline__ void chan_max_image(const float* __restrict__ x, int D, int C, int CL, float* __restrict__ out,
+                                               float (*red)[4]) {
+  const int CG = C / V, c = threadIdx.x & (CL - 1), pg = threadIdx.x / CL, np = 256 / CL;
+  for (int c0 = 0; c0 < CG; c0 += CL) {
+    const int cc = min(c0 + c, CG - 1);
+    float m[V] = {};
+    for (int p = pg; p < D; p += 8 * np) {
+      float v[8][V];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float* a = x + ((long long)min(p + u * np, D - 1) * CG + cc) * V;
+        if constexpr (V == 4) {
+          const f32x4 t = *reinterpret_cast<const f32x4*>(a);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[u][q] = t[q];
+        } else {
+          v[u][0] = *a;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int q = 0; q < V; ++q) m[q] = fmaxf(m[q], fabsf(v[u][q]));
+    }
+#pragma unroll
+    for (int q = 0; q < V; ++q) red[threadIdx.x][q] = m[q];
+    __syncthreads();
+    if (pg == 0 && c0 + c < CG)
+#pragma unroll
+      for (int q = 0; q < V; ++q) {
+        for (int u = 1; u < np; ++u) m[q] = fmaxf(m[q], red[u * CL + c][q]);
+        out[(c0 + c) * V + q] = m[q];
+      }
+    __syncthreads();
+  }
+}
 __global__ void __launch_bounds__(256) k_conv_max(ConvMax b) {
-  __shared__ float red[4];
+  __shared__ float cred[256][4];
+  float* red = &cred[0][0];
   const int z = blockIdx.y;
+  if (z == b.count) {
+    if ((int)blockIdx.x >= b.M) return;
+    const float* x = b.cx + (long long)blockIdx.x * b.D * b.C;
+    float* out = b.cout + (long long)blockIdx.x * b.C;
+    const bool vec = b.C % 4 == 0 && (reinterpret_cast<uintptr_t>(b.cx) & 15) == 0;
+    int CL = 4;
+    while (CL < (vec ? b.C / 4 : b.C) && CL < 64) CL *= 2;
+    if (vec) chan_max_image<4>(x, b.D, b.C, CL, out, cred);
+    else chan_max_image<1>(x, b.D, b.C, CL, out, cred);
+    return;
+  }
   const int n = b.plane[z];
+  if ((int)blockIdx.x >= b.rows[z]) return;
   const float* __restrict__ x = b.x[z] + (long long)blockIdx.x * n;
   float m = 0.f;
   if (n % 4 == 0 && (reinterpret_cast<uintptr_t>(b.x[z]) & 15) == 0) {
@@ -1013,8 +1075,10 @@ __global__ void __launch_bounds__(256) k_conv_max(ConvMax b) {
 }
 
 hipError_t launch_conv_max(hipStream_t s, const ConvMax& m) {
-  if (m.count <= 0 || m.M <= 0) return hipSuccess;
-  k_conv_max<<<dim3(m.M, m.count), dim3(256), 0, s>>>(m);
+  int rows = m.cx ? m.M : 0;
+  for (int z = 0; z < m.count; ++z) rows = std::max(rows, m.rows[z]);
+  if (rows <= 0) return hipSuccess;
+  k_conv_max<<<dim3(rows, m.count + (m.cx ? 1 : 0)), dim3(256), 0, s>>>(m);
   return hipGetLastError();
 }
 
@@ -1075,14 +1139,14 @@ __device__ __forceinline__ void conv_wgrad_store(f32x16 (&acc)[Cfg::FM][Cfg::FN]
 template <class Cfg, bool VEC>
 __global__ void __launch_bounds__(Cfg::THREADS)
 k_conv_bwd(LoadPatchesKInnerT<VEC> la, LoadKInnerT<VEC> lb, const float* __restrict__ dphi, int R,
-           int N, FastDiv fOD, FastDiv fD, float* __restrict__ out, int tiles_n, float* __restrict__ gmax) {
+           int N, FastDiv fOD, FastDiv fD, float* __restrict__ out, int tiles_n, ImageMax mx) {
   extern __shared__ float smem[];
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
   f32x16 acc[Cfg::FM][Cfg::FN];
   zero_acc<Cfg>(acc);
   gemm_mainloop<Cfg>(la, lb, m0, n0, 0, la.K, smem, acc);
-  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, gmax);
+  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, mx);
 }
 
 // direct-to-LDS form (Cg % 32 == 0): the cotangent patches gathered by the DMA, NS LDS stages
@@ -1090,14 +1154,14 @@ template <class Cfg, int NS>
 __global__ void __launch_bounds__(Cfg::THREADS)
 k_conv_bwd_dma(DmaPatches<Cfg::BM, Cfg::WAVES> pa, DmaRowMajor<Cfg::BN, Cfg::WAVES> pb, int K,
                const float* __restrict__ dphi, int R, int N, FastDiv fOD, FastDiv fD, float* __restrict__ out,
-               int tiles_n, float* __restrict__ gmax) {
+               int tiles_n, ImageMax mx) {
   extern __shared__ float smem[];
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
   f32x16 acc[Cfg::FM][Cfg::FN];
   zero_acc<Cfg>(acc);
   gemm_mainloop_dma_ops<Cfg, NS>(pa, pb, m0, n0, 0, K, smem, acc);
-  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, gmax);
+  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, mx);
 }
 
 // The same on pairs.  A tile's rows are a run of BM pixels of the stacked cotangent images, and the
@@ -1107,7 +1171,8 @@ k_conv_bwd_dma(DmaPatches<Cfg::BM, Cfg::WAVES> pa, DmaRowMajor<Cfg::BN, Cfg::WAV
 // are row shifts of the LDS reads, and a tap outside the image reads a row of zeros.  The kernel
 // (pair rows) streams through two LDS stages, 32 k at a time.  1280 images of 32 x 32 x 64:
 // 788 us with the fp32 MFMA, 408 us with the cotangents gathered and split per tap (VALU beside
-// the MFMAs), this form 327 us.  Any number of channels: they are padded with zeros to a multiple
+// the MFMAs), this form 327 us; 346 with the channels' balancing factors and the maxima of the images
+// it writes.  Any number of channels: they are padded with zeros to a multiple
 // of 32 on the way into LDS (and in the kernel's pair rows); VEC: Cg % 4 == 0, 16-byte loads.
 constexpr int kHaloMaxW = 63;
 template <class Cfg>
@@ -1127,7 +1192,7 @@ template <class Cfg, bool VEC>
 __global__ void __launch_bounds__(Cfg::THREADS, 2 * Cfg::THREADS / 256)
 k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, DmaRowMajor<Cfg::BN, Cfg::WAVES> pb,
                 ConvPairBwd pr, const float* __restrict__ dphi, int R, int N, FastDiv fOD, FastDiv fD,
-                float* __restrict__ out, int tiles_n, float* __restrict__ gmax) {
+                float* __restrict__ out, int tiles_n, ImageMax mx) {
   extern __shared__ f32x4 halo_lds[];   // 16-byte aligned
   float* smem = reinterpret_cast<float*>(halo_lds);
   const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
@@ -1135,7 +1200,6 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm0 = (wave / Cfg::WAVES_N) * Cfg::WM, wn0 = (wave % Cfg::WAVES_N) * Cfg::WN;
   const int lr = lane & 31, lc = (lane >> 5) * 2;
-  const float fac = pr.fac ? *pr.fac : 1.f;
   const int HR = halo_rows<Cfg>(W);
   float* Bs = smem + (HR + 1) * 32;
   constexpr int NT = halo_tasks<Cfg>();
@@ -1149,10 +1213,13 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
     const int t = threadIdx.x + i * Cfg::THREADS;
     const int q = min(max(m0 - (W + 1) + min(t >> 2, HR - 1), 0), R - 1);
     src[i] = G + (long long)q * Cg;
-    sf[i] = pair_factor(pair_row_exp(pr.gmax[fD.div(q)] * fac));
+    sf[i] = pair_factor(pair_row_exp(pr.gbal[fD.div(q)]));
   }
-  f32x4 st[NT][2];
+  f32x4 st[NT][2], kf[2];   // kf: the balancing factors of the thread's channels (padded to whole blocks)
   auto fetch = [&](int cb) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      kf[u] = *reinterpret_cast<const f32x4*>(pr.kfac + cb * 32 + 8 * (threadIdx.x & 3) + 4 * u);
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
       const int c0 = cb * 32 + 8 * (threadIdx.x & 3);
@@ -1178,7 +1245,7 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
       const int t = threadIdx.x + i * Cfg::THREADS, row = t >> 2, c = 2 * (t & 3);
       if (row < HR) {
         f16x8 hi, lo;
-        pair_split8(st[i][0], st[i][1], sf[i], hi, lo);
+        pair_split8(st[i][0] * kf[0], st[i][1] * kf[1], sf[i], hi, lo);
         *reinterpret_cast<f16x8*>(&smem[row * 32 + (DmaTile<32>::swz(row, c) << 2)]) = hi;
         *reinterpret_cast<f16x8*>(&smem[row * 32 + (DmaTile<32>::swz(row, c + 1) << 2)]) = lo;
       }
@@ -1296,21 +1363,21 @@ k_conv_bwd_pair(const float* __restrict__ G, int H, int W, int Cg, FastDiv fW, D
   for (int i = 0; i < Cfg::FM; ++i) {
     const int r0 = min(m0 + wm0 + i * 32, R - 1), t0 = (int)fD.div(r0);
     const bool one = (int)fD.div(min(r0 + 31, R - 1)) == t0;
-    const int e0 = pair_row_exp(pr.gmax[t0] * fac);
+    const int e0 = pair_row_exp(pr.gbal[t0]);
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int e = one ? e0 : pair_row_exp(pr.gmax[fD.div(min(r0 + frag_row(v, lane), R - 1))] * fac);
+      const int e = one ? e0 : pair_row_exp(pr.gbal[fD.div(min(r0 + frag_row(v, lane), R - 1))]);
 #pragma unroll
       for (int j = 0; j < Cfg::FN; ++j)
         acc[i][j][v] = ldexpf(acc[i][j][v], e + pr.kexps[min(n0 + wn0 + j * 32 + lr, N - 1)]);
     }
   }
-  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, gmax);
+  store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, mx);
 }
 
 template <bool VEC>
 static hipError_t conv_bwd_vec(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
-                               const float* Kt, int Cin, const float* dphi, float* out, float* gmax) {
+                               const float* Kt, int Cin, const float* dphi, float* out, const ImageMax& mx) {
   using Cfg = CfgConv;
   using LA = LoadPatchesKInnerT<VEC>;
   using LB = LoadKInnerT<VEC>;
@@ -1323,13 +1390,13 @@ static hipError_t conv_bwd_vec(hipStream_t s, const float* G, int images, int O,
   hipError_t e = set_smem<Cfg, LA, LB>((const void*)k_conv_bwd<Cfg, VEC>);
   if (e != hipSuccess) return e;
   k_conv_bwd<Cfg, VEC><<<dim3(tm * tn), dim3(Cfg::THREADS), gemm_smem_bytes<Cfg, LA, LB>(), s>>>(
-      la, lb, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn, gmax);
+      la, lb, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn, mx);
   return hipGetLastError();
 }
 
 template <class Cfg>
 static hipError_t conv_bwd_dma_cfg(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
-                                   const float* Kt, int Cin, const float* dphi, float* out, float* gmax) {
+                                   const float* Kt, int Cin, const float* dphi, float* out, const ImageMax& mx) {
   constexpr int NS = kConvBwdStages;
   const int D = H * W, Kd = 9 * Cg;
   int R;
@@ -1342,13 +1409,13 @@ static hipError_t conv_bwd_dma_cfg(hipStream_t s, const float* G, int images, in
                                      hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess) return e;
   k_conv_bwd_dma<Cfg, NS><<<dim3(tm * tn), dim3(Cfg::THREADS), bytes, s>>>(
-      pa, pb, Kd, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn, gmax);
+      pa, pb, Kd, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn, mx);
   return hipGetLastError();
 }
 
 template <class Cfg, bool VEC>
 static hipError_t conv_bwd_pair_cfg(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
-                                    const ConvPairBwd& pr, int Cin, const float* dphi, float* out, float* gmax) {
+                                    const ConvPairBwd& pr, int Cin, const float* dphi, float* out, const ImageMax& mx) {
   const int D = H * W, Kd = 9 * (int)pair_stride(Cg);
   int R;
   if (!to_int((long long)images * O * D, R)) return hipErrorInvalidValue;
@@ -1359,7 +1426,7 @@ static hipError_t conv_bwd_pair_cfg(hipStream_t s, const float* G, int images, i
   if (e != hipSuccess) return e;
   k_conv_bwd_pair<Cfg, VEC><<<dim3(tm * tn), dim3(Cfg::THREADS), halo_smem_bytes<Cfg>(W), s>>>(
       G, H, W, Cg, FastDiv((uint32_t)W), pb, pr, dphi, R, Cin, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), out, tn,
-      gmax);
+      mx);
   return hipGetLastError();
 }
 
@@ -1370,12 +1437,12 @@ bool conv_bwd_pair_ok(int W, int Cg) {
 }
 
 static hipError_t conv_bwd_pair(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
-                                const ConvPairBwd& pr, int Cin, const float* dphi, float* out, float* gmax) {
+                                const ConvPairBwd& pr, int Cin, const float* dphi, float* out, const ImageMax& mx) {
   const bool vec = Cg % 4 == 0 && aligned16(G);
   auto go = [&](auto cfg_tag) {
     using Cfg = decltype(cfg_tag);
-    return vec ? conv_bwd_pair_cfg<Cfg, true>(s, G, images, O, H, W, Cg, pr, Cin, dphi, out, gmax)
-               : conv_bwd_pair_cfg<Cfg, false>(s, G, images, O, H, W, Cg, pr, Cin, dphi, out, gmax);
+    return vec ? conv_bwd_pair_cfg<Cfg, true>(s, G, images, O, H, W, Cg, pr, Cin, dphi, out, mx)
+               : conv_bwd_pair_cfg<Cfg, false>(s, G, images, O, H, W, Cg, pr, Cin, dphi, out, mx);
   };
   // few rows: 128-row tiles, for more workgroups; few channels: 32 columns
   const bool few = (long long)cdiv((long long)images * O * H * W, 256) * cdiv(Cin, 64) < kConvFewTiles;
@@ -1385,16 +1452,16 @@ static hipError_t conv_bwd_pair(hipStream_t s, const float* G, int images, int O
 
 hipError_t launch_conv_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
                            const float* Kt, int Cin, const float* dphi, float* out, const ConvPairBwd* pair,
-                           float* gmax) {
-  if (pair) return conv_bwd_pair(s, G, images, O, H, W, Cg, *pair, Cin, dphi, out, gmax);
+                           const ImageMax& mx) {
+  if (pair) return conv_bwd_pair(s, G, images, O, H, W, Cg, *pair, Cin, dphi, out, mx);
   if (conv_dma_ok(G, (long long)images * O * H * W * Cg, W, Cg, Kt)) {
     const long long tiles = (long long)cdiv((long long)images * O * H * W, CfgConvBwd::BM) * cdiv(Cin, CfgConvBwd::BN);
-    if (tiles < kConvFewTiles) return conv_bwd_dma_cfg<CfgConv>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, gmax);
-    return conv_bwd_dma_cfg<CfgConvBwd>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, gmax);
+    if (tiles < kConvFewTiles) return conv_bwd_dma_cfg<CfgConv>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, mx);
+    return conv_bwd_dma_cfg<CfgConvBwd>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, mx);
   }
   if (Cg % 4 == 0 && aligned16(G) && vec_ok(Kt, 9 * Cg, 9 * Cg))
-    return conv_bwd_vec<true>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, gmax);
-  return conv_bwd_vec<false>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, gmax);
+    return conv_bwd_vec<true>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, mx);
+  return conv_bwd_vec<false>(s, G, images, O, H, W, Cg, Kt, Cin, dphi, out, mx);
 }
 
 // ------------------------------------------------------------------------------ weight-space cotangent
@@ -1538,11 +1605,7 @@ k_conv_wgrad_pair(const float* __restrict__ G, const float* __restrict__ h, Conv
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm0 = (wave / Cfg::WAVES_N) * Cfg::WM, wn0 = (wave % Cfg::WAVES_N) * Cfg::WN;
   const int lr = lane & 31, lc = (lane >> 5) * 2;
-  const float fac = pr.fac ? *pr.fac : 1.f;
-  auto row_exp = [&](int r) {
-    const int o = (int)fC.div(min(r, O * C - 1));
-    return pair_row_exp(pr.gmax ? pr.gmax[s * O + o] * fac : pr.gconst);
-  };
+  auto row_exp = [&](int r) { return pair_row_exp(pr.gmax[s * O + (int)fC.div(min(r, O * C - 1))]); };
   const int eh = pair_row_exp(pr.hmax[s]);
   // staging task of this thread: 4 rows (quad q) x 8 pixels (group g) of operand A (the first BM
   // threads) or B.  Byte offsets through a buffer resource that starts W + 1 pixels before the

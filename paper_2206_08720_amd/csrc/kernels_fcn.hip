@@ -406,10 +406,10 @@ struct EpiBwdPix {
   float* out;
   int R, N;
   FastDiv fOD, fD;
-  float* gmax;   // per cotangent image: the largest magnitude, or null
+  ImageMax mx;
   template <class Cfg>
   __device__ __forceinline__ void tile(f32x16 (&acc)[Cfg::FM][Cfg::FN], int m0, int n0) const {
-    store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, gmax);
+    store_pixel_rows<Cfg>(acc, m0, n0, dphi, out, R, N, fOD, fD, mx);
   }
 };
 
@@ -537,11 +537,11 @@ static hipError_t dense_bwd_ko_cfg(hipStream_t s, const float* G, const float* W
 
 template <class Cfg, bool VEC, bool DMA = false>
 static hipError_t pw_bwd_cfg(hipStream_t s, const float* G, const float* Wt, const float* dphi, int R, int N,
-                             int K, int O, int D, float* out, float* gmax) {
+                             int K, int O, int D, float* out, const ImageMax& mx) {
   using L = LoadKInnerT<VEC>;
   L la{G, R, K, K};
   L lb{Wt, N, K, K};
-  EpiBwdPix epi{dphi, out, R, N, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), gmax};
+  EpiBwdPix epi{dphi, out, R, N, FastDiv((uint32_t)(O * D)), FastDiv((uint32_t)D), mx};
   const int tn = cdiv(N, Cfg::BN), tm = cdiv(R, Cfg::BM);
   constexpr int bytes = DMA ? gemm_dma_smem_bytes<Cfg, 2>() : gemm_smem_bytes<Cfg, L, L>();
   hipError_t e = hipFuncSetAttribute((const void*)k_dense_bwd<Cfg, VEC, DMA, EpiBwdPix>,
@@ -552,7 +552,7 @@ static hipError_t pw_bwd_cfg(hipStream_t s, const float* G, const float* Wt, con
 }
 
 hipError_t launch_pw_bwd(hipStream_t s, const float* G, const float* Wt, const float* dphi, int R, int N,
-                         int K, int O, int D, float* out, float* gmax) {
+                         int K, int O, int D, float* out, const ImageMax& mx) {
   if ((long long)O * D >= (1LL << 31) || R <= 0) return R <= 0 ? hipSuccess : hipErrorInvalidValue;
   const long long big_tiles = (long long)cdiv(R, 128) * cdiv(N, 128);
   const bool v = vec_ok(G, K, K) && vec_ok(Wt, K, K);
@@ -560,14 +560,14 @@ hipError_t launch_pw_bwd(hipStream_t s, const float* G, const float* Wt, const f
   // memory-bound product (K = input channels), so the tile is sized for three workgroups per CU
   // (48 KB of LDS): 150 vs 160 us for 256x64 tiles at 1280 x 32x32 cotangent images of 64 channels
   if (N <= 64 && (long long)cdiv(R, 256) >= 512 && v && K % 32 == 0 && dma_span_ok(K, K, 256))
-    return pw_bwd_cfg<CfgPw, true, true>(s, G, Wt, dphi, R, N, K, O, D, out, gmax);
+    return pw_bwd_cfg<CfgPw, true, true>(s, G, Wt, dphi, R, N, K, O, D, out, mx);
   if (big_tiles >= 512) {
-    if (v && K % 32 == 0 && dma_span_ok(K, K, 256)) return pw_bwd_cfg<CfgBig8, true, true>(s, G, Wt, dphi, R, N, K, O, D, out, gmax);
-    return v ? pw_bwd_cfg<CfgBig8, true>(s, G, Wt, dphi, R, N, K, O, D, out, gmax)
-             : pw_bwd_cfg<CfgBig8, false>(s, G, Wt, dphi, R, N, K, O, D, out, gmax);
+    if (v && K % 32 == 0 && dma_span_ok(K, K, 256)) return pw_bwd_cfg<CfgBig8, true, true>(s, G, Wt, dphi, R, N, K, O, D, out, mx);
+    return v ? pw_bwd_cfg<CfgBig8, true>(s, G, Wt, dphi, R, N, K, O, D, out, mx)
+             : pw_bwd_cfg<CfgBig8, false>(s, G, Wt, dphi, R, N, K, O, D, out, mx);
   }
-  return v ? pw_bwd_cfg<CfgSmall, true>(s, G, Wt, dphi, R, N, K, O, D, out, gmax)
-           : pw_bwd_cfg<CfgSmall, false>(s, G, Wt, dphi, R, N, K, O, D, out, gmax);
+  return v ? pw_bwd_cfg<CfgSmall, true>(s, G, Wt, dphi, R, N, K, O, D, out, mx)
+           : pw_bwd_cfg<CfgSmall, false>(s, G, Wt, dphi, R, N, K, O, D, out, mx);
 }
 
 // Two 8-wave workgroups share a compute unit (4 waves per SIMD).  At the depth-8 width-2048

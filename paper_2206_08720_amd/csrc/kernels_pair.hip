@@ -69,8 +69,7 @@ __global__ void __launch_bounds__(1024) k_pair_wstats(PairWeights b) {
 #pragma unroll
     for (int q = 32; q; q >>= 1) m[i] = fmaxf(m[i], __shfl_xor(m[i], q));
     const int r = 2 * wave + i;
-    // 2^e at most the largest element: a cotangent times 2^e overflows no earlier than its product
-    const int e = r < rows && m[i] > 0.f ? pair_e(m[i]) - 1 : 0;
+    const int e = r < rows ? pair_bal_exp(m[i]) : 0;
     if (lane == 0) {
       kd[r] = e;
       b.kexps[z][k0 + r] = e;

@@ -74,9 +74,9 @@ __device__ __forceinline__ void act_pair(int act, double z, float& h, float& d) 
 }
 
 // Launch shape of the plane kernels: blockIdx.y strides over the rows (images or cotangent
-// images), the x-blocks over the row's plane of V-channel groups.
-dim3 plane_grid(long long rows, long long plane) {
-  const int bx = std::max(1, std::min(cdiv_i(plane, 256), 512));
+// images), the x-blocks over the row's plane of V-channel groups, per_lane groups per lane.
+dim3 plane_grid(long long rows, long long plane, int per_lane = 1) {
+  const int bx = std::max(1, std::min(cdiv_i(plane, 256 * per_lane), 512));
   const int by = (int)std::max(1LL, std::min<long long>(rows, 65535));
   return dim3(bx, by);
 }
@@ -97,6 +97,28 @@ __device__ __forceinline__ void for_plane_items(int rows, int per, int plane, in
     const int q = (t - k * chunks) * 256 + (int)threadIdx.x;
     if (q < plane) f(g * per + k, q);
   }
+}
+
+// The same with the maxima of the planes written: f(r, q, lane maxima).
+template <class F>
+__device__ __forceinline__ void for_plane_items_max(int rows, int per, int plane, int ids, const ImageMax& mx, F&& f) {
+  const int chunks = (plane + 255) / 256, tiles = per * chunks;
+  for (int id = blockIdx.x; id < ids; id += gridDim.x) {
+    int g, t;
+    if (!xcd_sample_tile(id, tiles, rows / per, g, t)) continue;
+    const int k = t / chunks, r = g * per + k;
+    const int q = (t - k * chunks) * 256 + (int)threadIdx.x;
+    ImageMaxLane m;
+    if (q < plane) f(r, q, m);
+    if (mx.raw) m.flush_block(mx, r);
+  }
+}
+
+// V channel factors of the balanced maxima (0: none are asked for)
+template <int V>
+__device__ __forceinline__ Vf<V> max_factors(const ImageMax& mx, int c0) {
+  if (mx.bal) return ldv<V>(mx.f + c0);
+  return Vf<V>{};
 }
 
 // Launch shape of for_plane_items; ids = 0 (nothing launched: an invalid-value error) when the
@@ -300,11 +322,11 @@ k_pool_fwd(const float* __restrict__ x, int images, int Ho, int Wo, FastDiv fCG,
 template <int V, int XS, int RS>
 __global__ void __launch_bounds__(256)
 k_dw_bwd(const float* __restrict__ G, int rows, int O, int H, int W, FastDiv fCG, FastDiv fXB,
-         const float* __restrict__ w, const float* __restrict__ dphi, float* __restrict__ out, int ids) {
+         const float* __restrict__ w, const float* __restrict__ dphi, float* __restrict__ out, int ids, ImageMax mx) {
   const int CG = (int)fCG.d, C = CG * V, XB = (int)fXB.d;
   const int plane = ((H + RS - 1) / RS) * XB * CG;
   const long long img_elems = (long long)H * W * C;
-  for_plane_items(rows, O, plane, ids, [&](int r, int q) {
+  for_plane_items_max(rows, O, plane, ids, mx, [&](int r, int q, ImageMaxLane& m) {
     const float* Gr = G + (long long)r * img_elems;
     const float* dimg = dphi ? dphi + (long long)(r / O) * img_elems : nullptr;
     const int rest = (int)fCG.div(q), cg = q - rest * CG;
@@ -313,6 +335,7 @@ k_dw_bwd(const float* __restrict__ G, int rows, int O, int H, int W, FastDiv fCG
     Vf<V> tap[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) tap[t] = ldv<V>(w + (8 - t) * C + c0);
+    const Vf<V> f = max_factors<V>(mx, c0);
     dw_rows<V, XS, RS, float>(Gr, H, W, C, c0, yb * RS, x0, tap, [&](int y, const float (&acc)[XS][V]) {
       // act' of the output pixels (clamped column, unused past W)
       Vf<V> d[XS];
@@ -325,7 +348,10 @@ k_dw_bwd(const float* __restrict__ G, int rows, int O, int H, int W, FastDiv fCG
         if (x0 + j < W) {
           Vf<V> res;
 #pragma unroll
-          for (int v = 0; v < V; ++v) res.v[v] = dimg ? acc[j][v] * d[j].v[v] : acc[j][v];
+          for (int v = 0; v < V; ++v) {
+            res.v[v] = dimg ? acc[j][v] * d[j].v[v] : acc[j][v];
+            m.add(res.v[v], f.v[v]);
+          }
           stv<V>(out + (long long)r * img_elems + ((long long)y * W + x0 + j) * C + c0, res);
         }
       }
@@ -336,12 +362,13 @@ k_dw_bwd(const float* __restrict__ G, int rows, int O, int H, int W, FastDiv fCG
 template <int V>
 __global__ void __launch_bounds__(256)
 k_scale_bwd(const float* __restrict__ G, int rows, int O, int D, FastDiv fCG, const float* __restrict__ w,
-            const float* __restrict__ dphi, float* __restrict__ out) {
+            const float* __restrict__ dphi, float* __restrict__ out, ImageMax mx) {
   const int CG = (int)fCG.d, C = CG * V;
   const int plane = D * CG;
   const long long img_elems = (long long)D * C;
   for (int r = blockIdx.y; r < rows; r += gridDim.y) {
     const long long dbase = (long long)(r / O) * img_elems;
+    ImageMaxLane m;
     for (int q = blockIdx.x * 256 + threadIdx.x; q < plane; q += gridDim.x * 256) {
       const int p = (int)fCG.div(q), c0 = (q - p * CG) * V;
       const long long o = (long long)p * C + c0;
@@ -356,7 +383,11 @@ k_scale_bwd(const float* __restrict__ G, int rows, int O, int D, FastDiv fCG, co
         for (int v = 0; v < V; ++v) res.v[v] *= d.v[v];
       }
       stv<V>(out + (long long)r * img_elems + o, res);
+      const Vf<V> f = max_factors<V>(mx, c0);
+#pragma unroll
+      for (int v = 0; v < V; ++v) m.add(res.v[v], f.v[v]);
     }
+    if (mx.raw) m.flush_block(mx, r);
   }
 }
 
@@ -365,7 +396,7 @@ k_scale_bwd(const float* __restrict__ G, int rows, int O, int D, FastDiv fCG, co
 template <int V>
 __global__ void __launch_bounds__(256)
 k_pool_bwd(const float* __restrict__ G, int rows, int O, int H, int W, FastDiv fCG, FastDiv fWo,
-           const float* __restrict__ dphi, float* __restrict__ out) {
+           const float* __restrict__ dphi, float* __restrict__ out, ImageMax mx) {
   const int CG = (int)fCG.d, C = CG * V;
   const int Wo = W / 2;
   const int plane = (H / 2) * Wo * CG;
@@ -373,6 +404,7 @@ k_pool_bwd(const float* __restrict__ G, int rows, int O, int H, int W, FastDiv f
   const long long gimg_elems = img_elems / 4;
   for (int r = blockIdx.y; r < rows; r += gridDim.y) {
     const long long dbase = (long long)(r / O) * img_elems;
+    ImageMaxLane m;
     for (int q = blockIdx.x * 256 + threadIdx.x; q < plane; q += gridDim.x * 256) {
       const int pq = (int)fCG.div(q), c0 = (q - pq * CG) * V;
       const int yo = (int)fWo.div(pq), xo = pq - yo * Wo;
@@ -396,7 +428,13 @@ k_pool_bwd(const float* __restrict__ G, int rows, int O, int H, int W, FastDiv f
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) stv<V>(out + (long long)r * img_elems + o[i], res[i]);
+      const Vf<V> f = max_factors<V>(mx, c0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < V; ++v) m.add(res[i].v[v], f.v[v]);
     }
+    if (mx.raw) m.flush_block(mx, r);
   }
 }
 
@@ -655,7 +693,7 @@ hipError_t launch_pool_fwd(hipStream_t s, const float* x, int images, int H, int
 }
 
 hipError_t launch_dw_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int C,
-                         const float* w, const float* dphi, float* out) {
+                         const float* w, const float* dphi, float* out, const ImageMax& mx) {
   const long long rows = (long long)images * O;
   if (rows >= (1LL << 31) || !plane_fits(rows, (long long)H * W * C)) return hipErrorInvalidValue;
   if (rows == 0 || H * W * C == 0) return hipSuccess;
@@ -664,42 +702,42 @@ hipError_t launch_dw_bwd(hipStream_t s, const float* G, int images, int O, int H
     const PlaneLaunch L = plane_launch(rows, O, (long long)YB * XB * C / 4);
     if (L.ids == 0) return hipErrorInvalidValue;
     k_dw_bwd<4, kDwBwdXS, kDwBwdRS><<<L.grid, dim3(256), 0, s>>>(
-        G, (int)rows, O, H, W, FastDiv((uint32_t)(C / 4)), FastDiv((uint32_t)XB), w, dphi, out, L.ids);
+        G, (int)rows, O, H, W, FastDiv((uint32_t)(C / 4)), FastDiv((uint32_t)XB), w, dphi, out, L.ids, mx);
   } else {
     const PlaneLaunch L = plane_launch(rows, O, (long long)YB * XB * C);
     if (L.ids == 0) return hipErrorInvalidValue;
     k_dw_bwd<1, kDwBwdXS, kDwBwdRS><<<L.grid, dim3(256), 0, s>>>(
-        G, (int)rows, O, H, W, FastDiv((uint32_t)C), FastDiv((uint32_t)XB), w, dphi, out, L.ids);
+        G, (int)rows, O, H, W, FastDiv((uint32_t)C), FastDiv((uint32_t)XB), w, dphi, out, L.ids, mx);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_scale_bwd(hipStream_t s, const float* G, int images, int O, int D, int C, const float* w,
-                            const float* dphi, float* out) {
+                            const float* dphi, float* out, const ImageMax& mx) {
   const long long rows = (long long)images * O;
   if (rows >= (1LL << 31) || !plane_fits(rows, (long long)D * C)) return hipErrorInvalidValue;
   if (use_vec4(C, {G, w, dphi, out})) {
-    k_scale_bwd<4><<<plane_grid(rows, (long long)D * C / 4), dim3(256), 0, s>>>(
-        G, (int)rows, O, D, FastDiv((uint32_t)(C / 4)), w, dphi, out);
+    k_scale_bwd<4><<<plane_grid(rows, (long long)D * C / 4, mx.raw ? 4 : 1), dim3(256), 0, s>>>(
+        G, (int)rows, O, D, FastDiv((uint32_t)(C / 4)), w, dphi, out, mx);
   } else {
-    k_scale_bwd<1><<<plane_grid(rows, (long long)D * C), dim3(256), 0, s>>>(
-        G, (int)rows, O, D, FastDiv((uint32_t)C), w, dphi, out);
+    k_scale_bwd<1><<<plane_grid(rows, (long long)D * C, mx.raw ? 4 : 1), dim3(256), 0, s>>>(
+        G, (int)rows, O, D, FastDiv((uint32_t)C), w, dphi, out, mx);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_pool_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int C,
-                           const float* dphi, float* out) {
+                           const float* dphi, float* out, const ImageMax& mx) {
   const long long rows = (long long)images * O;
   if (H % 2 || W % 2 || rows >= (1LL << 31) || !plane_fits(rows, (long long)H * W * C))
     return hipErrorInvalidValue;
   const long long pooled = (long long)(H / 2) * (W / 2) * C;
   if (use_vec4(C, {G, dphi, out})) {
-    k_pool_bwd<4><<<plane_grid(rows, pooled / 4), dim3(256), 0, s>>>(
-        G, (int)rows, O, H, W, FastDiv((uint32_t)(C / 4)), FastDiv((uint32_t)(W / 2)), dphi, out);
+    k_pool_bwd<4><<<plane_grid(rows, pooled / 4, mx.raw ? 4 : 1), dim3(256), 0, s>>>(
+        G, (int)rows, O, H, W, FastDiv((uint32_t)(C / 4)), FastDiv((uint32_t)(W / 2)), dphi, out, mx);
   } else {
-    k_pool_bwd<1><<<plane_grid(rows, pooled), dim3(256), 0, s>>>(
-        G, (int)rows, O, H, W, FastDiv((uint32_t)C), FastDiv((uint32_t)(W / 2)), dphi, out);
+    k_pool_bwd<1><<<plane_grid(rows, pooled, mx.raw ? 4 : 1), dim3(256), 0, s>>>(
+        G, (int)rows, O, H, W, FastDiv((uint32_t)C), FastDiv((uint32_t)(W / 2)), dphi, out, mx);
   }
   return hipGetLastError();
 }

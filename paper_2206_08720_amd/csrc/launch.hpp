@@ -77,11 +77,19 @@ hipError_t launch_dense_bwd(hipStream_t s, const float* G, const float* Wt, cons
 bool dense_bwd_w_ok(const float* G, const float* W, long long R, long long N, long long K);
 hipError_t launch_dense_bwd_w(hipStream_t s, const float* G, const float* W, const float* dphi, int R, int N,
                               int K, int O, float* out);
+// Where a kernel that writes cotangent images [.., C] leaves their largest magnitudes (pair_core.hpp
+// needs them beforehand): raw[image], and bal[image] of the values times f[c].  Both are zero before.
+// Null raw: nothing; null bal: raw alone.
+struct ImageMax {
+  float* raw;
+  float* bal;
+  const float* f;
+};
 // Pointwise (1x1) convolution backward: rows r = (img*O + o)*D + p of R cotangent pixels,
-// out[r, c] = (sum_k G[r, k] Wt[c, k]) * dphi[img*D + p, c]  (dphi null: the identity).  With gmax,
-// gmax[r / D] (zero before) receives the largest magnitude of each cotangent image of out.
+// out[r, c] = (sum_k G[r, k] Wt[c, k]) * dphi[img*D + p, c]  (dphi null: the identity); mx: the
+// maxima of the cotangent images r / D of out.
 hipError_t launch_pw_bwd(hipStream_t s, const float* G, const float* Wt, const float* dphi, int R, int N,
-                         int K, int O, int D, float* out, float* gmax = nullptr);
+                         int K, int O, int D, float* out, const ImageMax& mx = {});
 // Wt [C, R] = W^T for W [R, C].
 hipError_t launch_transpose(hipStream_t s, const float* W, int R, int C, float* Wt);
 // Wt[z] = W[z]^T for z < count (each W[z] R[z] x C[z], row-major), in one launch.

@@ -26,29 +26,24 @@ struct FlipBatch {
   int count;
 };
 hipError_t launch_conv_flip_batch(hipStream_t s, const FlipBatch& b);
-// What the products on f16 pairs (pair_core.hpp) need beside the fp32 operands: a bound of the
-// magnitudes of each cotangent image, gmax[img*O + o] * *fac (fac null: 1; gmax null: gconst), of
-// each image of the other operand, hmax[img], and the kernel's pair rows.  Null pointers to these
+// What the products on f16 pairs (pair_core.hpp) need beside the fp32 operands.  Null pointers to these
 // structs: the fp32 matrix cores.
 struct ConvPairBwd {
-  const float* gmax;
-  const float* fac;
-  const float* Kp;    // Kt as pair rows [Cin, 9 pair_stride(Cg)], the channels of a tap padded
+  const float* gbal;  // [images*O] largest |G[.., c]| kfac[c]
+  const float* kfac;  // [pair_stride(Cg)] balancing factors of the channels
+  const float* Kp;    // Kt divided by kfac, as pair rows [Cin, 9 pair_stride(Cg)], the channels of a tap padded
   const int* kexps;   // [Cin]
 };
 struct ConvPairWgrad {
-  const float* gmax;
-  const float* fac;
-  float gconst;
-  const float* hmax;  // [images]
+  const float* gmax;  // [images*O] largest |G|
+  const float* hmax;  // [images] largest |h|
   long long bias;     // column of J of the layer's bias cotangents, sum_p G[s, o, p, c]; -1: none
 };
 // out [images*O, D, Cin] = conv3x3(G [images*O, H, W, Cg], Kt [Cin, 3, 3, Cg]) * dphi [images, D, Cin]
-// (dphi null: the identity).  With gmax_out, gmax_out[img*O + o] (zero before) receives the largest
-// magnitude of each cotangent image of out.
+// (dphi null: the identity); mx: the maxima of the images of out.
 hipError_t launch_conv_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int Cg,
                            const float* Kt, int Cin, const float* dphi, float* out,
-                           const ConvPairBwd* pair = nullptr, float* gmax_out = nullptr);
+                           const ConvPairBwd* pair = nullptr, const ImageMax& mx = {});
 bool conv_bwd_pair_ok(int W, int Cg);
 // J[(s*O + o), off + c*9*Cin + k] = sum_p G[s, o, p, c] patch(h)[s, p, k] for every sample s.  The
 // pair form sums the bias cotangents too (pair->bias); bias_done is then set.
@@ -61,41 +56,43 @@ hipError_t launch_pw_wgrad(hipStream_t s, const float* G, const float* h, int im
                            const ConvPairWgrad* pair = nullptr, bool* bias_done = nullptr);
 // Whether a weight-space product given `pair` takes its pair form (Cin: the padded count in the padded form).
 bool conv_wgrad_takes_pairs(int images, int O, int H, int W, int C, int Cin, bool pw);
-// Everything the pair products of one CNN evaluation need that does not depend on the backward, in
-// one launch: the pair rows of the flipped kernels (N[z] rows of 9 taps of C[z] channels), the
-// largest magnitude of each image of the layer inputs x[j] ([M, plane[j]] -> hmax[j]), the bound
-// of the seed's cotangents (max_c |Wd[o, c]| scale -> gseed[img*O + o]), zeroed maxima
-// [zero, zero + nzero), and per depthwise or scale layer the factor by which its backward can grow
-// a magnitude (largest column sum of taps[i] x ch[i] weights, times grow[i]) multiplied over runs
-// of such layers: fac[i] = (chain[i] ? fac[i - 1] : 1) * factor_i.
+// out[z][i] = the largest magnitude of row i < rows[z] of x[z] [rows, plane]: images of the layer
+// inputs, channels of the kernels.
+constexpr int kConvMaxItems = 2 * kMaxLayers + 1;
+struct ConvMax {
+  const float* x[kConvMaxItems];
+  float* out[kConvMaxItems];
+  int plane[kConvMaxItems], rows[kConvMaxItems];
+  int count;
+  const float* cx;
+  float* cout;
+  int M, D, C;
+};
+// Per layer z the balancing factors kfac[c] of its C output channels, the power of two below kmax[c], the
+// largest |K[c, ..]| (1 for 0 and for the padding), and the pair rows of the flipped kernel divided by
+// them (N rows of 9 taps of C channels); the maxima seed[img*O + o] (null: none) of the seed's cotangent
+// images Wd[o, c] inv_d dphi from dmax[img, c], the largest |dphi| of the channel (null: 1), and, with
+// seed_kmax, seed_bal of the values times the factors for seed_kmax; and the zeroed maxima
+// [zero, zero + nzero).
 struct ConvPrep {
   const float* Kt[kMaxLayers];
+  const float* kmax[kMaxLayers];
+  float* kfac[kMaxLayers];
   float* Kp[kMaxLayers];
   int* kexps[kMaxLayers];
   int C[kMaxLayers], N[kMaxLayers];
   int count;
   const float* Wd;   // [O, Cl]
-  int O, Cl, M;
-  float seed_scale;
-  float* gseed;
+  const float* dmax;
+  const float* seed_kmax;
+  float* seed;
+  float* seed_bal;
+  int M, O, Cl;
+  float inv_d;
   float* zero;
   long long nzero;
 };
-struct ConvFactors {
-  const float* w[kMaxLayers];   // null: a pool (factor grow)
-  int taps[kMaxLayers], ch[kMaxLayers];
-  float grow[kMaxLayers];
-  unsigned char chain[kMaxLayers];
-  int count;
-  float* fac;
-};
-struct ConvMax {
-  const float* x[kMaxLayers];
-  float* out[kMaxLayers];
-  int plane[kMaxLayers];
-  int count, M;
-};
-hipError_t launch_conv_prep(hipStream_t s, const ConvPrep& p, const ConvFactors& f);
+hipError_t launch_conv_prep(hipStream_t s, const ConvPrep& p);
 hipError_t launch_conv_max(hipStream_t s, const ConvMax& m);
 // The same products for Cin % 4 != 0 on the direct-to-LDS path: h [images, H, W, Cin] is first
 // copied into xp [images, H, W, Cp] (Cp = Cin rounded up to 4, zero channels past Cin; caller's

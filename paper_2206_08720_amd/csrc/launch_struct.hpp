@@ -6,6 +6,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "launch.hpp"
+
 namespace ntk {
 
 // hn/dphi [images, H, W, C] = act / act' of z = depthwise SAME 3x3 cross-correlation of
@@ -18,16 +20,16 @@ hipError_t launch_scale_fwd(hipStream_t s, const float* x, int images, int D, in
 // out [images, H/2, W/2, C] = mean of each 2x2 window of x [images, H, W, C] (H, W even).
 hipError_t launch_pool_fwd(hipStream_t s, const float* x, int images, int H, int W, int C, float* out);
 
-// Cotangent of the layer input, times act' of the layer before:
+// Cotangent of the layer input, times act' of the layer before (mx: the maxima of its images):
 // out [images*O, H, W, C] = (depthwise transposed conv of G [images*O, H, W, C] with w) * dphi[img]
 hipError_t launch_dw_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int C,
-                         const float* w, const float* dphi, float* out);
+                         const float* w, const float* dphi, float* out, const ImageMax& mx = {});
 // out [images*O, D, C] = G * w[c] * dphi[img]
 hipError_t launch_scale_bwd(hipStream_t s, const float* G, int images, int O, int D, int C, const float* w,
-                            const float* dphi, float* out);
+                            const float* dphi, float* out, const ImageMax& mx = {});
 // out [images*O, H, W, C] = G [images*O, H/2, W/2, C] at (y/2, x/2) / 4 * dphi[img]  (H, W: pool input)
 hipError_t launch_pool_bwd(hipStream_t s, const float* G, int images, int O, int H, int W, int C,
-                           const float* dphi, float* out);
+                           const float* dphi, float* out, const ImageMax& mx = {});
 
 // Weight-space cotangents that are sums over pixels, per row r = img*O + o of G [rows, H, W, C]
 // and the layer input x [images, H, W, C]:

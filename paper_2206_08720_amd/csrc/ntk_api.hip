@@ -174,12 +174,13 @@ struct ntk_handle {
   size_t off_mc = 0;              // per-channel Grams of the last convolution [C, N1, N2] (0: none)
   size_t off_xpad = 0;            // a convolution input padded to a multiple of 4 channels (0: none)
   long long part_capacity = 0;    // floats of the split-K partial buffer
-  // products on f16 pairs (pair_core.hpp): pair rows of the flipped kernels and their exponents,
-  // bounds of the cotangent images [nc, Mmax*O] and the layer inputs' images [nc, Mmax], growth
-  // factors of the block-diagonal layers [nc]; not in the lean plan
+  // products on f16 pairs (pair_core.hpp): pair rows of the flipped kernels and their exponents, their
+  // channels' maxima and balancing factors, and the largest magnitudes of the cotangent images (as they
+  // are and balanced [2, nc, Mmax*O]), the layer inputs' images [nc, Mmax] and the last layer's act' by
+  // channel [Mmax, C] and image [Mmax]; not in the lean plan
   bool cpair = false;
-  std::vector<size_t> off_Kp, off_ke;
-  size_t off_gmax = 0, off_hmax = 0, off_fac = 0;
+  std::vector<size_t> off_Kp, off_ke, off_km, off_kf;
+  size_t off_gmax = 0, off_hmax = 0, off_dcmax = 0, off_dmax = 0;
 };
 
 static thread_local std::string g_init_error;
@@ -510,14 +511,19 @@ static void plan_cnn(ntk_handle* h) {
   if (h->cpair) {
     h->off_Kp.assign(nc, 0);
     h->off_ke.assign(nc, 0);
+    h->off_km.assign(nc, 0);
+    h->off_kf.assign(nc, 0);
     for (int l = 1; l < nc; ++l)
       if (h->layers[l].kind == NTK_CONV3X3_SAME && conv_bwd_pair_ok(h->bw[l], h->ch[l + 1])) {
         h->off_Kp[l] = take((size_t)9 * h->ch[l] * pair_stride(h->ch[l + 1]));
         h->off_ke[l] = take(h->ch[l]);
+        h->off_km[l] = take(h->ch[l + 1]);
+        h->off_kf[l] = take(pair_stride(h->ch[l + 1]));
       }
-    h->off_gmax = take(Mmax * O * nc);
+    h->off_gmax = take(2 * Mmax * O * nc);
     h->off_hmax = take(Mmax * nc);
-    h->off_fac = take(nc);
+    h->off_dcmax = take(Mmax * h->ch[nc]);
+    h->off_dmax = take(Mmax);
   }
   h->off_g = take(Mmax * h->ch[nc]);
   h->off_Gping = take(Mmax * O * gmax);
@@ -1282,14 +1288,15 @@ static double inside_out_cost(double pairs, int D, int Cin, int C, int Oe, bool 
          (gram_blocks * Dp * Dp * Ci + out_blocks * (16.0 * Dp * Dp * C + 256.0 * Dp * C));
 }
 
-// Whether a CNN's backward and weight-space products run on f16 pairs: two more launches (the pair
-// rows and the images' maxima, 12 us) against the time of the products that have a pair form (the
-// folded last layer's `fold` has no cotangents in it, an inside-out layer no weight-space product).
-// 4x4 images, 5 GFLOP: 348 us with pairs, 316 us with the fp32 MFMA (the few workgroups wait on
-// loads either way); ten outputs of 32 16x16 images, 19 GFLOP: 302 against 348 us.
+// Whether a CNN's backward and weight-space products run on f16 pairs: two more launches (the images'
+// maxima and the kernels' pair rows, 15 to 35 us) against the time of the products that have a pair form
+// (the folded last layer's `fold` has no cotangents in it, an inside-out layer no weight-space product).
+// 4x4 images, 5 GFLOP: 348 us with pairs, 316 us with the fp32 MFMA (the few workgroups wait on loads
+// either way).  Ten outputs, 32x32 images: 6.9 GFLOP 216 against 211 us, 10.4 229 against 235, 13.9 243
+// against 280; 16x16 images, 14 GFLOP: 228 against 256; one output, 15 GFLOP: 411 against 407.
 // Channel counts that the direct-to-LDS fp32 kernels do not take (not a multiple of 32 behind a
-// backward, of 4 in a weight-space product) repay pairs earlier: 3.5 GFLOP 255 against 241 us,
-// 4.2 GFLOP 272 against 340 us.
+// backward, of 4 in a weight-space product) repay pairs earlier: 15x15 images of four layers 3.4 GFLOP
+// 343 against 311 us, 4.6 356 against 365; 30x26 images 2.7 GFLOP 329 against 341, 5.4 386 against 435.
 constexpr double kConvPairMinFlops = 1.2e10, kConvPairMinFlopsRagged = 4e9;
 static bool cnn_pair_pays(const ntk_handle* h, int M, int Oe, const std::vector<char>& inside, bool fold) {
   double flops = 0;
@@ -1458,74 +1465,75 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
   float* Gcur = F(h->off_Gping);
   float* Gnext = F(h->off_Gpong);
   const float* Wd = params[h->rslot] + (logit ? (size_t)h->opt_logit * C : 0);
-  // Products on f16 pairs: bounds of every cotangent image (the seed's from the readout weights,
-  // exact ones from the convolutions' epilogues, grown by a factor through the block-diagonal
-  // layers and pools) and of every layer input.
-  auto act_bound = [&](int l) { return h->wslot[l] >= 0 && h->layers[l].act == NTK_ACT_ERF ? 1.1284f : 1.f; };
-  struct Bound {
-    const float *gmax, *fac;
-  };
-  std::vector<Bound> bound(nc, Bound{nullptr, nullptr});
+  // Products on f16 pairs: the largest magnitudes of every operand's images (of the cotangents from the
+  // epilogues of the kernels that write them) and the kernels' pair rows.
   const size_t gm_ld = ((size_t)h->max_n1 + h->max_n2) * O, hm_ld = (size_t)h->max_n1 + h->max_n2;
-  auto gmax = [&](int l) { return F(h->off_gmax) + l * gm_ld; };
-  bool cpair = h->cpair && h->opt_method != NTK_METHOD_JACOBIAN && cnn_pair_pays(h, M, Oe, inside, fold);
+  // (the maxima that kernels add to, and have to be zero before, in front; the seed's behind)
+  auto gmax = [&](int l) { return F(h->off_gmax) + (l < nc - 1 ? l : 2 * nc - 2) * gm_ld; };
+  auto gbal = [&](int l) { return F(h->off_gmax) + (l < nc - 1 ? nc - 1 + l : 2 * nc - 1) * gm_ld; };
+  const bool cpair = h->cpair && h->opt_method != NTK_METHOD_JACOBIAN && cnn_pair_pays(h, M, Oe, inside, fold);
+  // the maxima of G_l that a convolution's pair products ask for
+  auto image_max = [&](int l) -> ImageMax {
+    const int kind = h->layers[l].kind;
+    if (!cpair || (kind != NTK_CONV3X3_SAME && kind != NTK_CONV1X1)) return {};
+    const bool bal = l > 0 && h->off_Kp[l];
+    return {gmax(l), bal ? gbal(l) : nullptr, bal ? F(h->off_kf[l]) : nullptr};
+  };
   if (cpair) {
-    ConvFactors cf{};
-    int run = 0;
-    bound[nc - 1] = {gmax(nc - 1), nullptr};
-    for (int l = nc - 1; l >= 1; --l) {
-      const ntk_layer_desc& L = h->layers[l];
-      if (L.kind == NTK_CONV3X3_SAME || L.kind == NTK_CONV1X1) {
-        bound[l - 1] = {gmax(l - 1), nullptr};
-        run = 0;
-        continue;
-      }
-      const int i = cf.count++;
-      cf.w[i] = h->wslot[l] >= 0 ? params[h->wslot[l]] : nullptr;
-      cf.taps[i] = L.kind == NTK_DWCONV3X3_SAME ? 9 : 1;
-      cf.ch[i] = h->ch[l + 1];
-      cf.grow[i] = (L.kind == NTK_AVGPOOL2 ? 0.25f : 1.f) * act_bound(l - 1);
-      cf.chain[i] = bound[l].fac != nullptr;
-      bound[l - 1] = {bound[l].gmax, F(h->off_fac) + i};
-      // each such layer loosens the bound (about 2 bits); the pairs hold about 10 to spare
-      if (++run > 4) cpair = false;
+    ConvPrep cp{};
+    ConvMax cm{};
+    auto add_max = [&](const float* x, float* out, int rows, int plane) {
+      cm.x[cm.count] = x;
+      cm.out[cm.count] = out;
+      cm.rows[cm.count] = rows;
+      cm.plane[cm.count] = plane;
+      ++cm.count;
+    };
+    for (int l = 0; l < nc; ++l) {
+      const int kind = h->layers[l].kind;
+      if ((kind == NTK_CONV3X3_SAME || kind == NTK_CONV1X1) && !inside[l])
+        add_max(hptr(l), F(h->off_hmax) + l * hm_ld, M, h->bh[l] * h->bw[l] * h->ch[l]);
+      if (l == 0 || !h->off_Kp[l]) continue;
+      add_max(params[h->wslot[l]], F(h->off_km[l]), h->ch[l + 1], 9 * h->ch[l]);
+      cp.Kt[cp.count] = F(h->off_Kt[l]);
+      cp.kmax[cp.count] = F(h->off_km[l]);
+      cp.kfac[cp.count] = F(h->off_kf[l]);
+      cp.Kp[cp.count] = F(h->off_Kp[l]);
+      cp.kexps[cp.count] = I(h->off_ke[l]);
+      cp.C[cp.count] = h->ch[l + 1];
+      cp.N[cp.count] = h->ch[l];
+      ++cp.count;
     }
-    cf.fac = F(h->off_fac);
-    if (cpair) {
-      ConvPrep cp{};
-      for (int l = 1; l < nc; ++l) {
-        if (!h->off_Kp[l]) continue;
-        cp.Kt[cp.count] = F(h->off_Kt[l]);
-        cp.Kp[cp.count] = F(h->off_Kp[l]);
-        cp.kexps[cp.count] = I(h->off_ke[l]);
-        cp.C[cp.count] = h->ch[l + 1];
-        cp.N[cp.count] = h->ch[l];
-        ++cp.count;
-      }
+    // the folded layer's "cotangent" is act' itself
+    if (fold) add_max(F(h->off_cdphi[ll]), F(h->off_dmax), M, h->bh[ll] * h->bw[ll] * h->ch[ll + 1]);
+    const float* dz = h->wslot[nc - 1] >= 0 ? F(h->off_cdphi[nc - 1]) : nullptr;
+    const ImageMax sm = image_max(nc - 1);
+    const int D = h->bh[nc] * h->bw[nc];
+    if (sm.raw) {
       cp.Wd = Wd;
+      cp.dmax = dz ? F(h->off_dcmax) : nullptr;
+      cp.seed_kmax = sm.bal ? F(h->off_km[nc - 1]) : nullptr;
+      cp.seed = sm.raw;
+      cp.seed_bal = sm.bal;
+      cp.M = M;
       cp.O = Oe;
       cp.Cl = C;
-      cp.M = M;
-      cp.seed_scale = act_bound(nc - 1) / (float)(h->bh[nc] * h->bw[nc]);
-      cp.gseed = gmax(nc - 1);
-      cp.zero = gmax(0);
-      cp.nzero = (long long)(nc - 1) * gm_ld;
-      ConvMax cm{};
-      cm.M = M;
-      for (int l = 0; l < nc; ++l) {
-        const int kind = h->layers[l].kind;
-        if ((kind != NTK_CONV3X3_SAME && kind != NTK_CONV1X1) || inside[l]) continue;
-        cm.x[cm.count] = hptr(l);
-        cm.out[cm.count] = F(h->off_hmax) + l * hm_ld;
-        cm.plane[cm.count] = h->bh[l] * h->bw[l] * h->ch[l];
-        ++cm.count;
-      }
-      prof_begin(P, s, KC_PAIR_ROWS);
-      e = launch_conv_prep(s, cp, cf);
-      if (e == hipSuccess) e = launch_conv_max(s, cm);
-      prof_end(P, s, KC_PAIR_ROWS);
-      if (e != hipSuccess) return hip_fail(h, e, "pair preparation");
+      cp.inv_d = 1.f / (float)D;
     }
+    if (cp.dmax) {
+      cm.cx = dz;
+      cm.cout = F(h->off_dcmax);
+      cm.M = M;
+      cm.D = D;
+      cm.C = C;
+    }
+    cp.zero = gmax(0);
+    cp.nzero = 2LL * (nc - 1) * gm_ld;
+    prof_begin(P, s, KC_PAIR_ROWS);
+    e = launch_conv_max(s, cm);
+    if (e == hipSuccess) e = launch_conv_prep(s, cp);
+    prof_end(P, s, KC_PAIR_ROWS);
+    if (e != hipSuccess) return hip_fail(h, e, "pair preparation");
   }
   prof_begin(P, s, KC_CONV_SEED);
   const float* dlast = h->wslot[nc - 1] >= 0 ? F(h->off_cdphi[nc - 1]) : nullptr;
@@ -1538,9 +1546,7 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
                    long long bias, bool* bias_done) -> hipError_t {
     const int Hl = h->bh[l], Wl = h->bw[l], cin = h->ch[l], cout = h->ch[l + 1];
     float* xp = h->off_xpad ? F(h->off_xpad) : nullptr;
-    // the folded layer's "cotangent" is act' itself
-    const ConvPairWgrad pg{fold && l == ll ? nullptr : bound[l].gmax, bound[l].fac, act_bound(l),
-                           F(h->off_hmax) + l * hm_ld, bias};
+    const ConvPairWgrad pg{fold && l == ll ? F(h->off_dmax) : gmax(l), F(h->off_hmax) + l * hm_ld, bias};
     const bool padded = xp && conv_wgrad_pad_ok(M, Orows, Hl, Wl, cout, cin, G, xp);
     const ConvPairWgrad* pr =
         cpair && conv_wgrad_takes_pairs(M, Orows, Hl, Wl, cout, padded ? (cin + 3) & ~3 : cin, pw) ? &pg : nullptr;
@@ -1623,29 +1629,29 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
       // to the cotangent of layer l-1's pre-activation (its output, when it has no activation)
       const float* dprev = h->wslot[l - 1] >= 0 ? F(h->off_cdphi[l - 1]) : nullptr;
       if (L.kind == NTK_CONV3X3_SAME) {
-        const ConvPairBwd pb{bound[l].gmax, bound[l].fac, cpair && h->off_Kp[l] ? F(h->off_Kp[l]) : nullptr,
-                             cpair && h->off_Kp[l] ? I(h->off_ke[l]) : nullptr};
-        const int cls = pb.Kp ? KC_CONV_BWD_PAIR : KC_CONV_BWD;
+        const bool pr = cpair && h->off_Kp[l];
+        const ConvPairBwd pb = pr ? ConvPairBwd{gbal(l), F(h->off_kf[l]), F(h->off_Kp[l]), I(h->off_ke[l])} : ConvPairBwd{};
+        const int cls = pr ? KC_CONV_BWD_PAIR : KC_CONV_BWD;
         prof_begin(P, s, cls);
-        e = launch_conv_bwd(s, Gcur, M, Oe, Hl, Wl, cout, F(h->off_Kt[l]), cin, dprev, Gnext, pb.Kp ? &pb : nullptr,
-                            cpair ? gmax(l - 1) : nullptr);
+        e = launch_conv_bwd(s, Gcur, M, Oe, Hl, Wl, cout, F(h->off_Kt[l]), cin, dprev, Gnext, pr ? &pb : nullptr,
+                            image_max(l - 1));
         prof_end(P, s, cls);
       } else if (L.kind == NTK_CONV1X1) {
         prof_begin(P, s, KC_CONV_BWD);
         int rows;
         e = to_int((long long)M * Oe * Hl * Wl, rows)
                 ? launch_pw_bwd(s, Gcur, F(h->off_Kt[l]), dprev, rows, cin, cout, Oe, Hl * Wl, Gnext,
-                                cpair ? gmax(l - 1) : nullptr)
+                                image_max(l - 1))
                 : hipErrorInvalidValue;
         prof_end(P, s, KC_CONV_BWD);
       } else {
         prof_begin(P, s, KC_STRUCT_BWD);
         if (L.kind == NTK_DWCONV3X3_SAME)
-          e = launch_dw_bwd(s, Gcur, M, Oe, Hl, Wl, cout, w, dprev, Gnext);
+          e = launch_dw_bwd(s, Gcur, M, Oe, Hl, Wl, cout, w, dprev, Gnext, image_max(l - 1));
         else if (L.kind == NTK_SCALE)
-          e = launch_scale_bwd(s, Gcur, M, Oe, Hl * Wl, cout, w, dprev, Gnext);
+          e = launch_scale_bwd(s, Gcur, M, Oe, Hl * Wl, cout, w, dprev, Gnext, image_max(l - 1));
         else
-          e = launch_pool_bwd(s, Gcur, M, Oe, Hl, Wl, cin, dprev, Gnext);
+          e = launch_pool_bwd(s, Gcur, M, Oe, Hl, Wl, cin, dprev, Gnext, image_max(l - 1));
         prof_end(P, s, KC_STRUCT_BWD);
       }
       if (e != hipSuccess) return hip_fail(h, e, "backward pass");

@@ -51,6 +51,9 @@ __device__ __forceinline__ float pair_max(float m, float x) {
   const float a = fabsf(x);
   return a < __builtin_inff() ? fmaxf(m, a) : m;
 }
+// exponent of the balancing factor of a column whose counterpart's largest magnitude is m: a value times the
+// factor overflows no earlier than its product with that element
+__device__ __forceinline__ int pair_bal_exp(float m) { return m > 0.f && m < __builtin_inff() ? pair_e(m) - 1 : 0; }
 // the row's exponent from its elements' largest one
 __device__ __forceinline__ int pair_row_e(int e) { return (e <= kPairNone / 2 ? 0 : e) - kPairTop; }
 

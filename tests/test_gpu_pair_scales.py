@@ -87,3 +87,96 @@ def test_pair_rows_unit_scales(kind):
 def test_pair_rows_of_wide_layers(widths):
     """Rows of more than 2048 values (a workgroup each) and of more than its registers hold."""
     _check("normal 4", widths, 9, 8, False, (FULL,))
+
+
+# ---- convolutions ---------------------------------------------------------------------------------
+C3, DW, PW, POOL, SC = "conv3x3", "dwconv3x3", "conv1x1", "avgpool2", "scale"
+# as derived for the convolutions' pair tests: three backward products, a weight-space product, J1 J2^T
+CONV_TOL = 3 * 6.8e-6 + 5.8e-6 + 1e-5
+PLAIN = ((20, 20), [(C3, 64, "relu", True)] * 3, 13, 10)
+STRUCT = ((24, 20), [(C3, 64, "relu", True), (DW, "relu", True), (PW, 64, "relu", True), (POOL,), (SC, "relu", True),
+                     (C3, 64, "relu", True), (DW, "relu", False), (SC, "relu", False), (C3, 64, "relu", False)], 40, 21)
+# padded channels, scalar loads
+ODD = ((15, 15), [(C3, 20, "relu", False), (C3, 45, "relu", True), (SC, "relu", True), (C3, 37, "relu", False),
+                  (C3, 17, "relu", False)], 24, 17)
+
+
+def param_slots(spec):
+    """(layer, index of its weight in params) of the layers with parameters."""
+    out, i = [], 0
+    for L in spec["layers"]:
+        if L["kind"] in wl.PARAM_KINDS:
+            out.append((L, i))
+            i += 2 if L["bias"] else 1
+    return out
+
+
+def rescale_cnn(spec, params, kind, seed):
+    rng = np.random.default_rng(seed)
+    params = [p.copy() for p in params]
+    slots = param_slots(spec)
+    for (L, i), (_, j) in zip(slots, slots[1:]):
+        s = np.exp2(scales(kind, L["out"], rng)).astype(np.float32)
+        # outputs lead in a convolution's weights, channels come last in depthwise and scale weights
+        if L["kind"] in (C3, PW):
+            params[i] *= s.reshape((-1,) + (1,) * (params[i].ndim - 1))
+        else:
+            params[i] *= s
+        if L["bias"]:
+            params[i + 1] *= s
+        params[j] /= s   # the inputs' axis is the last one of every kind
+    return params
+
+
+def _conv_check(name, net, change, hooks=("conv_bwd_pair", "conv_wgrad_pair"), act=None):
+    hw, blocks, n1, n2 = net
+    if act:
+        blocks = [tuple(act if x == "relu" else x for x in b) for b in blocks]
+    spec = wl.cnn_layers_spec("pairu", hw, 3, blocks, 10)
+    params = change(spec, wl.make_params(spec, 95, "2/fan_in", bias_var=0.05))
+    X1, X2 = wl.make_inputs(spec, n1, 96), wl.make_inputs(spec, n2, 97)
+    print(f"[pair] {name} {hw}", flush=True)
+    prof = {}
+    got = gpu_ntk(spec, params, X1, X2, profile=prof)
+    assert set(hooks) <= set(prof)
+    ref, d1, d2 = oracle.ntk_jc_with_norms(spec, params, X1, X2, layer_storage=S)
+    cs, nw = scaled_errors(got, ref, sample_scale(d1, d2))
+    report(f"{name} {hw}", cs, nw)
+    assert np.isfinite(got).all() and cs <= CONV_TOL and nw <= CONV_TOL
+
+
+@pytest.mark.parametrize("net", [PLAIN, STRUCT, ODD], ids=["plain", "struct", "odd"])
+@pytest.mark.parametrize("kind", KINDS)
+def test_pair_conv_channel_scales(kind, net):
+    _conv_check(f"channel scales {kind}", net, lambda spec, params: rescale_cnn(spec, params, kind, 98))
+
+
+def test_pair_conv_outlier_channels():
+    """Depthwise and scale layers each with one large channel, not the same one."""
+    def change(spec, params):
+        for n, (L, i) in enumerate(l for l in param_slots(spec) if l[0]["kind"] in (DW, SC)):
+            params[i][..., 7 + 11 * n] *= np.float32(2.0 ** 24)
+        return params
+    _conv_check("outlier channels", STRUCT, change)
+
+
+def test_pair_conv_saturated_act():
+    """act' of the last layer near 2^-36 for every unit, readout weights that make up for it."""
+    def change(spec, params):
+        (_, i), (_, j) = param_slots(spec)[-2:]
+        params[i] *= np.float32(0.02)
+        params[i + 1][:] = 5.0
+        params[j] *= np.float32(2.0 ** 44)
+        return params
+    # (enough images for the last layer's weight-space product to take pairs)
+    _conv_check("saturated", PLAIN[:2] + (24, 16), change, act="erf")
+
+
+def test_pair_conv_dead_channel():
+    """A channel that no image activates has the largest readout weights by 2^32."""
+    def change(spec, params):
+        (_, i), (_, j) = param_slots(spec)[-2:]
+        params[i + 1][5] = -100.0
+        params[j][:, 5] *= np.float32(2.0 ** 32)
+        return params
+    _conv_check("dead channel", PLAIN, change)
