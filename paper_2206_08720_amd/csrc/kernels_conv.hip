@@ -2289,8 +2289,8 @@ constexpr double kSplitKPairMinFlops = 3e8;
 constexpr long long kSplitKPairMinK = 4096;
 hipError_t launch_ntk_splitk(hipStream_t s, const float* J1, const float* J2, int R1, int R2,
                              long long K, long long ld, int symmetric, int chunk, int splits,
-                             float* part) {
-  if (K >= kSplitKPairMinK && 2.0 * R1 * R2 * K >= kSplitKPairMinFlops && dma_span_ok(ld, K, 128)) {
+                             float* part, bool pairs) {
+  if (pairs && K >= kSplitKPairMinK && 2.0 * R1 * R2 * K >= kSplitKPairMinFlops && dma_span_ok(ld, K, 128)) {
     using Cfg = CfgSplitK;
     const int tm = cdiv(R1, Cfg::BM), tn = cdiv(R2, Cfg::BN);
     const int tiles = symmetric ? tn * (tn + 1) / 2 : tm * tn;

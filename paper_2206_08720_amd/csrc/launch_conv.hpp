@@ -116,9 +116,10 @@ hipError_t launch_fold_rowdot(hipStream_t s, const float* A1, const float* A2, i
 int splitk_tile();
 // splits * R1 * R2 <= part_capacity (floats) always holds for the returned plan.
 int splitk_plan(int R1, int R2, long long K, int symmetric, long long part_capacity, int* chunk_out);
+// pairs: large products may run on f16 pairs (pair_core.hpp).
 hipError_t launch_ntk_splitk(hipStream_t s, const float* J1, const float* J2, int R1, int R2,
                              long long K, long long ld, int symmetric, int chunk, int splits,
-                             float* part);
+                             float* part, bool pairs);
 // accumulate = 0: theta = w (.) partial sum + rscale * readout summand; 1: theta += w (.) partial
 // sum.  w [N1, N2] may be null (= 1); gram [N1, N2] may be null (no readout summand).
 hipError_t launch_ntk_reduce(hipStream_t s, const float* part, int splits, int N1, int N2, int O,

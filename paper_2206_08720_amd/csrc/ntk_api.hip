@@ -684,7 +684,8 @@ static hipError_t contract_rows(ntk_handle* h, const float* A, const float* B, i
   int chunk = 0;
   const int splits = splitk_plan(R1, R2, Kc, sym ? 1 : 0, part_capacity, &chunk);
   prof_begin(P, s, KC_NTK_SPLITK);
-  e = launch_ntk_splitk(s, A, B, R1, R2, Kc, Kc, sym ? 1 : 0, chunk, splits, part);
+  // (the explicit Jacobians are contracted in fp32: a cross-check of the structured method's products)
+  e = launch_ntk_splitk(s, A, B, R1, R2, Kc, Kc, sym ? 1 : 0, chunk, splits, part, false);
   prof_end(P, s, KC_NTK_SPLITK);
   if (e != hipSuccess) return e;
   prof_begin(P, s, KC_NTK_REDUCE);
@@ -1179,7 +1180,7 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
       int chunk = 0;
       const int splits = splitk_plan(n1, n2, K, sym ? 1 : 0, h->vpart_capacity, &chunk);
       prof_begin(P, s, KC_NTK_SPLITK);
-      e = launch_ntk_splitk(s, G1(l), G2(l), n1, n2, K, K, sym ? 1 : 0, chunk, splits, F(h->off_vpart));
+      e = launch_ntk_splitk(s, G1(l), G2(l), n1, n2, K, K, sym ? 1 : 0, chunk, splits, F(h->off_vpart), !h->lean);
       prof_end(P, s, KC_NTK_SPLITK);
       if (e != hipSuccess) return hip_fail(h, e, "split-K contraction");
       prof_begin(P, s, KC_NTK_REDUCE);
@@ -1702,7 +1703,7 @@ static int compute_cnn(ntk_handle* h, const float* const* params, const float* X
       int chunk = 0;
       const int splits = splitk_plan(R1, R2, Kc, sym ? 1 : 0, h->part_capacity, &chunk);
       prof_begin(P, s, KC_NTK_SPLITK);
-      e = launch_ntk_splitk(s, J, J2, R1, R2, Kc, Kc, sym ? 1 : 0, chunk, splits, F(h->off_part));
+      e = launch_ntk_splitk(s, J, J2, R1, R2, Kc, Kc, sym ? 1 : 0, chunk, splits, F(h->off_part), !h->lean);
       prof_end(P, s, KC_NTK_SPLITK);
       if (e != hipSuccess) return hip_fail(h, e, "split-K contraction");
       prof_begin(P, s, KC_NTK_REDUCE);

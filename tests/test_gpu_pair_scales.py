@@ -180,3 +180,51 @@ def test_pair_conv_dead_channel():
         params[j][:, 5] *= np.float32(2.0 ** 32)
         return params
     _conv_check("dead channel", PLAIN, change)
+
+
+# ---- what stays in fp32 -----------------------------------------------------------------------------
+def _disjoint(params, X1, X2):
+    """Every other unit answers to X1 alone and carries readout weights of 2^30: entries (x1, x2) come
+    from the units between, below the precision of a pair row whose exponent is that of the first."""
+    W, b, Wr = params[:3]
+    b[::2] = -1e3
+    W[::2] = 0.0
+    W[(slice(None, None, 2),) + (1,) * (W.ndim - 2) + (0,)] = 1e3   # (the middle tap of a convolution)
+    Wr[:, ::2] *= np.float32(2.0 ** 30)
+    X1[..., 0], X2[..., 0] = 2.0, 0.0
+
+
+def _entry_errors(got, ref):
+    """Largest error relative to the entry itself, over entries that do not cancel."""
+    m = np.abs(ref) > 1e-2 * np.abs(ref).max()
+    assert m.mean() > 0.05
+    return float(np.max(np.abs(got.astype(np.float64) - ref)[m] / np.abs(ref)[m]))
+
+
+@pytest.mark.parametrize("call", ["jacobian", "static"])
+def test_jacobian_baseline_and_static_calls_stay_in_fp32(call):
+    import torch
+    from paper_2206_08720_amd import _lib
+    from paper_2206_08720_amd.ntk import compute_static
+    from tests.gpu_helpers import to_dev
+    if call == "jacobian":
+        spec = wl.fcn_spec("disj", 96, [256], 10, bias=True)
+        n1, n2 = 24, 16
+    else:
+        spec = wl.cnn_layers_spec("disj", (8, 8), 8, [(C3, 64, "relu", True), (POOL,)], 10)
+        n1, n2 = 40, 24
+    params = wl.make_params(spec, 81, "2/fan_in")
+    X1, X2 = np.abs(wl.make_inputs(spec, n1, 82)), np.abs(wl.make_inputs(spec, n2, 83))
+    _disjoint(params, X1, X2)
+    ref = oracle.ntk_jc(spec, params, X1, X2, layer_storage=S)
+    print(f"[pair] fp32 {call}", flush=True)
+    if call == "jacobian":
+        got = gpu_ntk(spec, params, X1, X2, options={_lib.NTK_OPT_METHOD: _lib.NTK_METHOD_JACOBIAN})
+    else:
+        got = compute_static(spec, to_dev(params), *to_dev([X1, X2]))
+        torch.cuda.synchronize()
+        got = got.cpu().numpy()
+    err = _entry_errors(got, ref)
+    print(f"[parity] fp32 {call}: entries {err:.3e}", flush=True)
+    # fp32 partial sums of about 1000 columns: 1000 2^-24 at most
+    assert err <= 6e-5
