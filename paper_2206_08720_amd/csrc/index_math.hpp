@@ -74,6 +74,15 @@ __host__ __device__ inline void tri2_index(int t, int tiles_n, int& tm, int& tn)
   tn = 2 * r + (t - base);
 }
 
+// What a kernel that forms element (r, s) of a symmetric product writes: an element on or above the
+// diagonal itself and, off it, its mirror.  Elements below the diagonal are formed as well in the tiles
+// it runs through; they are not used, because a product of pairs of f16 values adds its cross terms in
+// an order that the exchange of the operands reverses: the mirror alone keeps theta symmetric to the last bit.
+__host__ __device__ inline void sym_writes(int symmetric, int r, int s, bool& direct, bool& mirror) {
+  direct = !symmetric || r <= s;
+  mirror = symmetric && r < s;
+}
+
 // Start of stream-K range `lam` when U units are cut into P equal contiguous ranges.
 __host__ __device__ inline long long sk_start(int lam, long long U, int P) {
   return (long long)lam * U / P;

@@ -2197,7 +2197,7 @@ k_ntk_splitk_pair(const float* __restrict__ J1, const float* __restrict__ J2, in
 template <int ZG>
 __global__ void __launch_bounds__(256)
 k_ntk_reduce(const float* __restrict__ part, int splits, int N1, int N2, int O,
-             int symmetric, int tile, const float* __restrict__ w,
+             int symmetric, const float* __restrict__ w,
              const float* __restrict__ gram, float rscale, int accumulate,
              float* __restrict__ theta) {
   constexpr int EB = 256 / ZG;   // entries per workgroup and pass
@@ -2215,7 +2215,7 @@ k_ntk_reduce(const float* __restrict__ part, int splits, int N1, int N2, int O,
     float v = 0.f;
     if (in) {
       long long src = i;
-      if (symmetric && (r1 / tile) > (r2 / tile)) src = (long long)r2 * R2 + r1;
+      if (symmetric && r1 > r2) src = (long long)r2 * R2 + r1;   // exactly symmetric: see sym_writes
       float a[4] = {0.f, 0.f, 0.f, 0.f};   // four independent chains keep several loads in flight
       int z = z0;
       for (; z + 4 <= z1; z += 4) {
@@ -2335,7 +2335,7 @@ hipError_t launch_ntk_reduce(hipStream_t s, const float* part, int splits, int N
   auto go = [&](auto zg_tag) {
     constexpr int ZG = decltype(zg_tag)::value, EB = 256 / ZG;
     k_ntk_reduce<ZG><<<dim3((unsigned)std::min<long long>((total + EB - 1) / EB, 256 * 64)), dim3(256), 0, s>>>(
-        part, splits, N1, N2, O, symmetric, CfgSplitK::BM, w, gram, rscale, accumulate, theta);
+        part, splits, N1, N2, O, symmetric, w, gram, rscale, accumulate, theta);
   };
   // one thread per entry from two workgroups a compute unit on, or for a few partials
   if (total < 512 * 256 && splits >= 16)

@@ -1107,17 +1107,19 @@ __device__ __forceinline__ void fcn_tile_reduce(const float* __restrict__ gram_r
     }
   }
   __syncthreads();
-  // direct block: consecutive threads take consecutive columns s = (n2, o2)
+  // direct block: consecutive threads take consecutive columns s = (n2, o2); below the diagonal of a
+  // symmetric theta the entry above it
+  const bool diagonal = symmetric && tm == tn;
   for (int e = threadIdx.x; e < 4096; e += 256) {
     const int rl = e >> 6, sl = e & 63;
     const int r = m0 + rl, s = n0 + sl;
     if (r < R1 && s < R2) {
       const int n1 = (int)fO.div(r), o1 = r - n1 * O;
       const int n2 = (int)fO.div(s), o2 = s - n2 * O;
-      theta[(((long long)n1 * N2 + n2) * O + o1) * O + o2] = tile[rl][sl];
+      theta[(((long long)n1 * N2 + n2) * O + o1) * O + o2] = diagonal && rl > sl ? tile[sl][rl] : tile[rl][sl];
     }
   }
-  if (!(symmetric && tm != tn)) return;
+  if (!symmetric || diagonal) return;
   // mirrored block theta[n2][n1][o2][o1]: consecutive threads take consecutive rows r = (n1, o1)
   for (int e = threadIdx.x; e < 4096; e += 256) {
     const int sl = e >> 6, rl = e & 63;
@@ -1192,18 +1194,11 @@ __device__ __forceinline__ void sk_tile_coords(int t, int symmetric, int tiles_m
   if (symmetric && Cfg::BM == 2 * Cfg::BN) tri2_index(t, tiles_n, tm, tn);
   else tile_coords(t, symmetric, tiles_m, tiles_n, tm, tn);
 }
-// The symmetric schedule's writes of element (r, s) of the tile at (m0, n0): itself and, off the
-// diagonal, its mirror.  A two-high tile is two blocks of BN x BN: itself from the diagonal of blocks
-// up, the mirror from above it.
-template <class Cfg>
-__device__ __forceinline__ void fcn_write(float* __restrict__ theta, int N1, int N2, int O, int symmetric, int m0, int n0,
-                                          int r, int s, int n1, int o1, int n2, int o2, float v) {
-  bool direct = true, mirror = symmetric && m0 != n0;
-  if constexpr (Cfg::BM != Cfg::BN) {
-    const int br = r / Cfg::BN, bs = s / Cfg::BN;   // powers of two
-    direct = !symmetric || br <= bs;
-    mirror = symmetric && br < bs;
-  }
+// Element (r, s) of theta and, in the symmetric schedule, its mirror (sym_writes).
+__device__ __forceinline__ void fcn_write(float* __restrict__ theta, int N1, int N2, int O, int symmetric, int r, int s,
+                                          int n1, int o1, int n2, int o2, float v) {
+  bool direct, mirror;
+  sym_writes(symmetric, r, s, direct, mirror);
   if (direct) theta[(((long long)n1 * N2 + n2) * O + o1) * O + o2] = v;
   if (mirror) theta[(((long long)n2 * N1 + n1) * O + o2) * O + o1] = v;
 }
@@ -1221,7 +1216,7 @@ __device__ __forceinline__ void fcn_tile_out(f32x16 (&tot)[Cfg::FM][Cfg::FN], co
       const int n1 = (int)fO.div(r), o1 = r - n1 * O;
       const int n2 = (int)fO.div(s), o2 = s - n2 * O;
       if (o1 == o2) v += rscale * smem[(n1 - n1lo) * S2 + (n2 - n2lo)];
-      fcn_write<Cfg>(theta, N1, N2, O, symmetric, m0, n0, r, s, n1, o1, n2, o2, v);
+      fcn_write(theta, N1, N2, O, symmetric, r, s, n1, o1, n2, o2, v);
     }
   });
   __syncthreads();
@@ -1378,7 +1373,7 @@ k_ntk_fcn_fixup(int L, const float* __restrict__ gram_readout, float rscale, int
       const int n2 = (int)fO.div(s), o2 = s - n2 * O;
       float w = vals[k];
       if (o1 == o2) w += rscale * gram_readout[(long long)n1 * N2 + n2];
-      fcn_write<Cfg>(theta, N1, N2, O, symmetric, tm * Cfg::BM, tn * Cfg::BN, r, s, n1, o1, n2, o2, w);
+      fcn_write(theta, N1, N2, O, symmetric, r, s, n1, o1, n2, o2, w);
     }
   }
 }

@@ -1,7 +1,6 @@
 // Host check of the upper-triangle order of two-high tiles (index_math.hpp): every tile that holds an
 // element on or above the block diagonal once, and every element of a square written exactly once
-// by the rule of the symmetric schedule (itself from the diagonal of blocks up, its mirror from
-// above it).
+// by the rule of the symmetric schedule (sym_writes).
 #include <cstdio>
 #include <set>
 #include <utility>
@@ -15,7 +14,9 @@ int main() {
     const int tm_n = (nb + 1) / 2, tn_n = nb;
     const int T = tri2_tiles(tm_n, tn_n);
     std::set<std::pair<int, int>> seen;
-    std::vector<int> writes(nb * nb, 0);
+    constexpr int B = 3;   // elements of a block's edge
+    const int R = nb * B - (nb > 1 ? 1 : 0);   // a ragged last block
+    std::vector<int> writes(R * R, 0);
     for (int t = 0; t < T; ++t) {
       int tm, tn;
       tri2_index(t, tn_n, tm, tn);
@@ -23,14 +24,17 @@ int main() {
         std::printf("bad tile %d of %d (nb %d): %d %d\n", t, T, nb, tm, tn);
         return 1;
       }
-      for (int br = 2 * tm; br < 2 * tm + 2 && br < nb; ++br) {
-        if (br <= tn) ++writes[br * nb + tn];
-        if (br < tn) ++writes[tn * nb + br];
-      }
+      for (int r = 2 * tm * B; r < (2 * tm + 2) * B && r < R; ++r)
+        for (int s = tn * B; s < (tn + 1) * B && s < R; ++s) {
+          bool direct, mirror;
+          sym_writes(1, r, s, direct, mirror);
+          writes[r * R + s] += direct;
+          writes[s * R + r] += mirror;
+        }
     }
-    for (int i = 0; i < nb * nb; ++i)
+    for (int i = 0; i < R * R; ++i)
       if (writes[i] != 1) {
-        std::printf("block %d of nb %d written %d times\n", i, nb, writes[i]);
+        std::printf("element %d of nb %d written %d times\n", i, nb, writes[i]);
         return 1;
       }
   }

@@ -173,3 +173,21 @@ def test_pair_splitk_row_exponents(scaling, n1, n2):
     X1 = wl.make_inputs(spec, n1, 72)
     X2 = X1 if n1 == n2 else wl.make_inputs(spec, n2, 73)
     _conv_check("split-K " + scaling, spec, params, X1, X2, classes=())   # small: the other products in fp32
+
+
+@pytest.mark.parametrize("case", ["layer groups", "stream-K", "trace", "convolutions"])
+def test_pair_theta_of_one_batch_is_exactly_symmetric(case):
+    """Theta(X, X) equals its transpose bit for bit, inside the diagonal's tiles too (the pair products
+    of (r, s) and (s, r) round differently)."""
+    variant = ("trace", "full", 0) if case == "trace" else ("full", "full", 0)
+    if case == "convolutions":
+        spec, n = wl.cnn_layers_spec("sym", (20, 20), 3, [(C3, 64, "relu", True)] * 2 + [("scale", "relu", False)], 10), 23
+    else:
+        spec, n = wl.fcn_spec("sym", 64, [389, 260, 515], 10, bias=True), {"layer groups": 90, "stream-K": 330, "trace": 400}[case]
+    params = wl.make_params(spec, 51, "2/fan_in")
+    X = wl.make_inputs(spec, n, 52)
+    print(f"[pair] symmetric {case}", flush=True)
+    prof = {}
+    got = gpu_ntk(spec, params, X, X, variant=variant, profile=prof)
+    assert any(k.endswith("_pair") for k in prof)
+    assert np.array_equal(got, got.T if case == "trace" else got.transpose(1, 0, 3, 2))
