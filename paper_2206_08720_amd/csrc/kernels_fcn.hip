@@ -920,12 +920,23 @@ constexpr int pair_gram_offset() {
 }
 // a tile of BM rows (n, o) touches at most (BM - 1) / O + 2 samples
 template <class Cfg>
-__host__ __device__ inline int gram_block_floats(int O) {
+__host__ __device__ constexpr int gram_block_floats(int O) {
   return (((Cfg::BM - 1) / O + 2) * ((Cfg::BN - 1) / O + 2) + 3) / 4 * 4;
 }
 template <class Cfg, int NSTAGE>
-__host__ inline int pair_smem_bytes(int O) {
+__host__ constexpr int pair_smem_bytes(int O) {
   return (pair_gram_offset<Cfg, NSTAGE>() + gram_block_floats<Cfg>(O) + Cfg::BM) * 4;
+}
+// what a kernel's limit of dynamic LDS is set to: the same on every call, since the limit is the
+// process's and another thread may be between setting it and its launch
+template <class Cfg, int NSTAGE>
+__host__ constexpr int pair_smem_limit() {
+  constexpr int one = pair_smem_bytes<Cfg, NSTAGE>(1);
+  // fewer outputs only mean more samples in a tile
+  static_assert(pair_smem_bytes<Cfg, NSTAGE>(2) <= one && pair_smem_bytes<Cfg, NSTAGE>(3) <= pair_smem_bytes<Cfg, NSTAGE>(2) &&
+                    pair_smem_bytes<Cfg, NSTAGE>(512) <= pair_smem_bytes<Cfg, NSTAGE>(3),
+                "one output takes the most");
+  return one < 160 * 1024 ? one : 160 * 1024;
 }
 // The sum over a layer's k is flushed into the tile's total every FLUSH k: shorter chains of
 // roundings than one over all of K (the fp32 accumulator is rounded three times per 16 k).
@@ -1458,7 +1469,8 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
     static_assert(PAIR || kSkPerCu * max_bytes <= 160 * 1024, "the workgroups of one CU must fit its LDS");
     const int bytes = PAIR ? pair_smem_bytes<Cfg, sk_pair_stages<Cfg>()>(O) : max_bytes;
     hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_sk<Cfg, VEC, DMA, PAIR>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       PAIR ? pair_smem_limit<Cfg, sk_pair_stages<Cfg>()>() : max_bytes);
     if (e != hipSuccess) return e;
     const FastDiv fO((uint32_t)O);
     k_ntk_fcn_sk<Cfg, VEC, DMA, PAIR><<<dim3(P), dim3(Cfg::THREADS), bytes, s>>>(
@@ -1493,7 +1505,8 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
     const int T = symmetric ? tn * (tn + 1) / 2 : tm * tn;
     const FastDiv fO((uint32_t)O);
     hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_lpart<Cfg, VEC, DMA, PAIR>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       PAIR ? pair_smem_limit<Cfg, kSplitStages>() : max_bytes);
     if (e != hipSuccess) return e;
     k_ntk_fcn_lpart<Cfg, VEC, DMA, PAIR><<<dim3(8 * cdiv((long long)T * NG, 8)), dim3(Cfg::THREADS), bytes, s>>>(
         c, N1, N2, fO, symmetric, tn, T, NG, part);

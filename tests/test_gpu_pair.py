@@ -191,3 +191,43 @@ def test_pair_theta_of_one_batch_is_exactly_symmetric(case):
     got = gpu_ntk(spec, params, X, X, variant=variant, profile=prof)
     assert any(k.endswith("_pair") for k in prof)
     assert np.array_equal(got, got.T if case == "trace" else got.transpose(1, 0, 3, 2))
+
+
+def test_pair_calls_of_two_threads_with_different_outputs():
+    """Two host threads, a handle and a stream each, whose contractions ask for different amounts of LDS
+    (few outputs more than many): every call succeeds and repeats the result of a call alone."""
+    import threading
+    import torch
+    from paper_2206_08720_amd.ntk import NTK
+    from tests.gpu_helpers import to_dev
+    jobs = []
+    for O, n in ((3, 400), (3, 100), (10, 220), (10, 60)):
+        spec = wl.fcn_spec("thr", 64, [389, 260], O)
+        ps = to_dev(wl.make_params(spec, 53, "2/fan_in"))
+        xs = to_dev([wl.make_inputs(spec, n, 54), wl.make_inputs(spec, n, 55)])
+        jobs.append((spec, ps, xs, gpu_ntk(spec, [p.cpu().numpy() for p in ps], *[x.cpu().numpy() for x in xs])))
+    errors = []
+
+    def run(part):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                handles = [(NTK(spec, x1.shape[0], x2.shape[0]), ps, x1, x2, ref) for spec, ps, (x1, x2), ref in part]
+                for _ in range(40):
+                    for h, ps, x1, x2, ref in handles:
+                        out = h.compute(ps, x1, x2)
+                for h, ps, x1, x2, ref in handles:
+                    out = h.compute(ps, x1, x2)
+                    torch.cuda.current_stream().synchronize()
+                    if not np.array_equal(out.cpu().numpy(), ref):
+                        errors.append("results differ")
+                    h.close()
+        except Exception as e:   # reported by the test's own thread
+            errors.append(repr(e))
+
+    print("[pair] two threads", flush=True)
+    threads = [threading.Thread(target=run, args=(part,)) for part in (jobs[:2], jobs[2:])]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not errors, errors
