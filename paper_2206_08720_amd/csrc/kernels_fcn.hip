@@ -25,20 +25,20 @@ using CfgSK = CfgBig8;                          // stream-K contraction
 // The same on pair rows: 8 waves of 64x64, one workgroup per CU.  Against 4 waves of 64x64 on 128x128
 // tiles, two workgroups per CU, a K tile's loads into LDS are shared by twice the products (LDS
 // bandwidth bounds both): 13.3 -> 11.2 ms at 12800 x 12800 x (3 x 4096), 2.45 -> 2.21 ms at
-// 5120 x 5120 x (8 x 2048).  With one or two outputs the tile's Gram block leaves no room for three
-// stages, and the 128x128 tiles stay.
+// 5120 x 5120 x (8 x 2048).
 using CfgSKPair = TileCfg<256, 128, 32, 64, 64>;
-using CfgSKPairSmall = TileCfg<128, 128, 32, 64, 64>;
+constexpr int kSkPairStages = 3;
 // The stream-K contraction keeps two workgroups per compute unit (two LDS stages each, so
 // both fit the 160 KB of LDS): one workgroup's barrier waits are covered by the other's MFMAs.
 constexpr int kSkPerCu = 2, kSkStages = 2;
-template <class Cfg, bool PAIR>
+// Pair rows: the Gram block of a tile lies in LDS beside the stages, or, where it does not fit (one or two
+// outputs, whose tiles touch a sample or half of one per row), it is read from memory.  One output,
+// 2900 x 2900 x (3 x 1024): 583 us in fp32, 546 on 128x128 tiles with the block in LDS (no room for a
+// second workgroup on the CU), 217 from memory.
+enum { kRowsFp32 = 0, kRowsPair = 1, kRowsPairGramInMemory = 2 };
+template <int ROWS>
 constexpr int sk_per_cu() {
-  return PAIR && Cfg::BM == 256 ? 1 : kSkPerCu;
-}
-template <class Cfg>
-constexpr int sk_pair_stages() {
-  return Cfg::BM == 256 ? 3 : 2;
+  return ROWS != kRowsFp32 ? 1 : kSkPerCu;
 }
 // LDS stages of the direct-to-LDS loop of the layer-split contraction (64 x 64 tiles): two
 // stages (32 KB) let four workgroups share a compute unit
@@ -923,18 +923,19 @@ template <class Cfg>
 __host__ __device__ constexpr int gram_block_floats(int O) {
   return (((Cfg::BM - 1) / O + 2) * ((Cfg::BN - 1) / O + 2) + 3) / 4 * 4;
 }
-template <class Cfg, int NSTAGE>
+template <class Cfg, int NSTAGE, int ROWS>
 __host__ constexpr int pair_smem_bytes(int O) {
-  return (pair_gram_offset<Cfg, NSTAGE>() + gram_block_floats<Cfg>(O) + Cfg::BM) * 4;
+  return (pair_gram_offset<Cfg, NSTAGE>() + (ROWS == kRowsPair ? gram_block_floats<Cfg>(O) : 0) + Cfg::BM) * 4;
 }
 // what a kernel's limit of dynamic LDS is set to: the same on every call, since the limit is the
 // process's and another thread may be between setting it and its launch
-template <class Cfg, int NSTAGE>
+template <class Cfg, int NSTAGE, int ROWS>
 __host__ constexpr int pair_smem_limit() {
-  constexpr int one = pair_smem_bytes<Cfg, NSTAGE>(1);
+  constexpr int one = pair_smem_bytes<Cfg, NSTAGE, ROWS>(1);
   // fewer outputs only mean more samples in a tile
-  static_assert(pair_smem_bytes<Cfg, NSTAGE>(2) <= one && pair_smem_bytes<Cfg, NSTAGE>(3) <= pair_smem_bytes<Cfg, NSTAGE>(2) &&
-                    pair_smem_bytes<Cfg, NSTAGE>(512) <= pair_smem_bytes<Cfg, NSTAGE>(3),
+  static_assert(pair_smem_bytes<Cfg, NSTAGE, ROWS>(2) <= one &&
+                    pair_smem_bytes<Cfg, NSTAGE, ROWS>(3) <= pair_smem_bytes<Cfg, NSTAGE, ROWS>(2) &&
+                    pair_smem_bytes<Cfg, NSTAGE, ROWS>(512) <= pair_smem_bytes<Cfg, NSTAGE, ROWS>(3),
                 "one output takes the most");
   return one < 160 * 1024 ? one : 160 * 1024;
 }
@@ -944,16 +945,17 @@ __host__ constexpr int pair_smem_limit() {
 // 1.0e-7 (512) on widths 1001, 750, 301; 2.6e-7 / 1.9e-7 / 1.4e-7 (512) at depth 8, width 2048,
 // where each flush of the large tiles costs 2 % of the contraction.
 constexpr int kPairFlushSmall = 256, kPairFlushBig = 1024;
-template <class Cfg, int NSTAGE, int FLUSH>
+template <class Cfg, int NSTAGE, int FLUSH, int ROWS>
 __device__ __forceinline__ void fcn_pair_layer(const FcnContraction& c, int l, int N2, int R1, int R2, FastDiv fO,
                                                int m0, int n0, float* smem, f32x16 (&tot)[Cfg::FM][Cfg::FN]) {
   const int lane_id = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm0 = (wave / Cfg::WAVES_N) * Cfg::WM, wn0 = (wave % Cfg::WAVES_N) * Cfg::WN;
   float* sg = smem + pair_gram_offset<Cfg, NSTAGE>();
-  int* se = reinterpret_cast<int*>(sg + gram_block_floats<Cfg>((int)fO.d));
+  int* se = reinterpret_cast<int*>(sg + (ROWS == kRowsPair ? gram_block_floats<Cfg>((int)fO.d) : 0));
   for (int i = threadIdx.x; i < Cfg::BM; i += Cfg::THREADS) se[i] = c.exps[l * c.exps_ld + min(m0 + i, R1 - 1)];
-  int n1lo, n2lo, S2;
-  stage_gram<Cfg>(c.gram[l], N2, R1, R2, fO, m0, n0, sg, n1lo, n2lo, S2);
+  int n1lo = 0, n2lo = 0, S2 = N2;
+  if (ROWS == kRowsPair) stage_gram<Cfg>(c.gram[l], N2, R1, R2, fO, m0, n0, sg, n1lo, n2lo, S2);
+  else __syncthreads();
   for (int k0 = 0; k0 < c.K[l]; k0 += FLUSH) {
     f32x16 acc[Cfg::FM][Cfg::FN];
     zero_acc<Cfg>(acc);
@@ -962,7 +964,11 @@ __device__ __forceinline__ void fcn_pair_layer(const FcnContraction& c, int l, i
     // an opaque copy of the lane index keeps the addresses below out of the main loop's registers
     int lane = lane_id;
     asm volatile("" : "+v"(lane));
-    pair_weighted_add<Cfg>(sg, se, c.exps + l * c.exps_ld + c.exps_off, R1, R2, fO, n1lo, n2lo, S2, m0, n0, wm0, wn0, lane, acc, tot);
+    const int* e2 = c.exps + l * c.exps_ld + c.exps_off;
+    if constexpr (ROWS == kRowsPair)
+      pair_weighted_add<Cfg>(sg, se, e2, R1, R2, fO, n1lo, n2lo, S2, m0, n0, wm0, wn0, lane, acc, tot);
+    else
+      pair_weighted_add<Cfg>(c.gram[l], se, e2, R1, R2, fO, 0, 0, S2, m0, n0, wm0, wn0, lane, acc, tot);
   }
   __syncthreads();
 }
@@ -1143,7 +1149,7 @@ __device__ __forceinline__ void fcn_tile_reduce(const float* __restrict__ gram_r
   }
 }
 
-template <class Cfg, bool VEC, bool DMA, bool PAIR = false>
+template <class Cfg, bool VEC, bool DMA, int ROWS = kRowsFp32>
 __global__ void __launch_bounds__(Cfg::THREADS)
 k_ntk_fcn_lpart(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, int tiles_n, int T, int NG,
                 float* __restrict__ part) {
@@ -1162,8 +1168,8 @@ k_ntk_fcn_lpart(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, int
   f32x16 tot[Cfg::FM][Cfg::FN];
   zero_acc<Cfg>(tot);
   for (int l = l0; l < l1; ++l) {
-    if constexpr (PAIR)
-      fcn_pair_layer<Cfg, kSplitStages, kPairFlushSmall>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
+    if constexpr (ROWS != kRowsFp32)
+      fcn_pair_layer<Cfg, kSplitStages, kPairFlushSmall, ROWS>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
     else
       fcn_layer_term<Cfg, VEC, DMA>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
   }
@@ -1280,8 +1286,8 @@ __device__ __forceinline__ void fcn_tile_layers(const FcnContraction& c, int l0,
 
 // kSkPerCu workgroups per compute unit must be resident together: the register budget is that
 // of kSkPerCu * THREADS / 256 waves per SIMD
-template <class Cfg, bool VEC, bool DMA, bool PAIR = false>
-__global__ void __launch_bounds__(Cfg::THREADS, (sk_per_cu<Cfg, PAIR>() * Cfg::THREADS / 256))
+template <class Cfg, bool VEC, bool DMA, int ROWS = kRowsFp32>
+__global__ void __launch_bounds__(Cfg::THREADS, (sk_per_cu<ROWS>() * Cfg::THREADS / 256))
 k_ntk_fcn_sk(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, float* __restrict__ theta,
              int tiles_m, int tiles_n, int T, int P, float* __restrict__ part) {
   extern __shared__ float smem[];
@@ -1314,8 +1320,8 @@ k_ntk_fcn_sk(FcnContraction c, int N1, int N2, FastDiv fO, int symmetric, float*
     const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
     f32x16 tot[Cfg::FM][Cfg::FN];
     zero_acc<Cfg>(tot);
-    if constexpr (PAIR) {
-      for (int l = l0; l < l1; ++l) fcn_pair_layer<Cfg, sk_pair_stages<Cfg>(), kPairFlushBig>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
+    if constexpr (ROWS != kRowsFp32) {
+      for (int l = l0; l < l1; ++l) fcn_pair_layer<Cfg, kSkPairStages, kPairFlushBig, ROWS>(c, l, N2, R1, R2, fO, m0, n0, smem, tot);
     } else {
       fcn_tile_layers<Cfg, VEC, DMA>(c, l0, l1, N2, fO, R1, R2, m0, n0, smem, tot);
     }
@@ -1429,6 +1435,8 @@ bool ntk_fcn_pair_ok(long long R1, long long R2, int L, int symmetric, int num_c
                     fcn_split_groups(R1, R2, L, symmetric, num_cu, part, true) >= 1);
 }
 
+template <int ROWS>
+using RowsT = std::integral_constant<int, ROWS>;
 hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2, int O,
                           int symmetric, float* theta, int num_cu, float* part) {
   int R1, R2;
@@ -1453,27 +1461,29 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
   for (int l = 0; l < c.L; ++l) dma = dma && c.K[l] % 32 == 0 && dma_span_ok(c.K[l], c.K[l], 256);
   const bool pair = c.L > 0 && c.exps;
   if (pair && !dma) return hipErrorInvalidValue;   // pair rows are aligned and padded to 32 k
-  auto go_sk = [&](auto cfg_tag, auto vec_tag, auto dma_tag, auto pair_tag) -> hipError_t {
+  auto go_sk = [&](auto cfg_tag, auto vec_tag, auto dma_tag, auto rows_tag) -> hipError_t {
     using Cfg = decltype(cfg_tag);
     constexpr bool VEC = decltype(vec_tag)::value;
     constexpr bool DMA = decltype(dma_tag)::value;
-    constexpr bool PAIR = decltype(pair_tag)::value;
+    constexpr int ROWS = decltype(rows_tag)::value;
     using L = LoadKInnerT<VEC>;
     const int tm = cdiv(R1, Cfg::BM), tn = cdiv(R2, Cfg::BN);
     const int T = !symmetric ? tm * tn : (Cfg::BM == Cfg::BN ? tn * (tn + 1) / 2 : tri2_tiles(tm, tn));
-    const int P = sk_per_cu<Cfg, PAIR>() * num_cu;
+    const int P = sk_per_cu<ROWS>() * num_cu;
     // LDS: the main loop's stages, or the Gram block of a tile if larger
     constexpr int loop_bytes = DMA ? gemm_dma_smem_bytes<Cfg, kSkStages>() : gemm_smem_bytes<Cfg, L, L>();
     constexpr int gram_bytes = (Cfg::BM + 1) * (Cfg::BN + 1) * 4;
     constexpr int max_bytes = loop_bytes > gram_bytes ? loop_bytes : gram_bytes;
-    static_assert(PAIR || kSkPerCu * max_bytes <= 160 * 1024, "the workgroups of one CU must fit its LDS");
-    const int bytes = PAIR ? pair_smem_bytes<Cfg, sk_pair_stages<Cfg>()>(O) : max_bytes;
-    hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_sk<Cfg, VEC, DMA, PAIR>,
+    static_assert(ROWS != kRowsFp32 || kSkPerCu * max_bytes <= 160 * 1024, "the workgroups of one CU must fit its LDS");
+    const int bytes = ROWS != kRowsFp32 ? pair_smem_bytes<Cfg, kSkPairStages, ROWS>(O) : max_bytes;
+    // (a tile's readout Gram block takes the place of the stages)
+    static_assert(ROWS == kRowsFp32 || pair_gram_offset<Cfg, kSkPairStages>() >= Cfg::BM * Cfg::BN, "Gram block in LDS");
+    hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_sk<Cfg, VEC, DMA, ROWS>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       PAIR ? pair_smem_limit<Cfg, sk_pair_stages<Cfg>()>() : max_bytes);
+                                       ROWS != kRowsFp32 ? pair_smem_limit<Cfg, kSkPairStages, ROWS>() : max_bytes);
     if (e != hipSuccess) return e;
     const FastDiv fO((uint32_t)O);
-    k_ntk_fcn_sk<Cfg, VEC, DMA, PAIR><<<dim3(P), dim3(Cfg::THREADS), bytes, s>>>(
+    k_ntk_fcn_sk<Cfg, VEC, DMA, ROWS><<<dim3(P), dim3(Cfg::THREADS), bytes, s>>>(
         c, N1, N2, fO, symmetric, theta, tm, tn, T, P, part);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1484,31 +1494,32 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
   const long long big_tiles = (long long)cdiv(R1, 128) * cdiv(R2, 128);
   if (fcn_uses_stream_k(c.L, big_tiles, num_cu, part != nullptr)) {
     if (pair)
-      return pair_smem_bytes<CfgSKPair, sk_pair_stages<CfgSKPair>()>(O) <= 160 * 1024
-                 ? go_sk(CfgSKPair{}, TrueT{}, TrueT{}, TrueT{})
-                 : go_sk(CfgSKPairSmall{}, TrueT{}, TrueT{}, TrueT{});
-    return dma ? go_sk(CfgSK{}, TrueT{}, TrueT{}, FalseT{})
-               : (v ? go_sk(CfgSK{}, TrueT{}, FalseT{}, FalseT{}) : go_sk(CfgSK{}, FalseT{}, FalseT{}, FalseT{}));
+      return pair_smem_bytes<CfgSKPair, kSkPairStages, kRowsPair>(O) <= 160 * 1024
+                 ? go_sk(CfgSKPair{}, TrueT{}, TrueT{}, RowsT<kRowsPair>{})
+                 : go_sk(CfgSKPair{}, TrueT{}, TrueT{}, RowsT<kRowsPairGramInMemory>{});
+    return dma ? go_sk(CfgSK{}, TrueT{}, TrueT{}, RowsT<kRowsFp32>{})
+               : (v ? go_sk(CfgSK{}, TrueT{}, FalseT{}, RowsT<kRowsFp32>{})
+                    : go_sk(CfgSK{}, FalseT{}, FalseT{}, RowsT<kRowsFp32>{}));
   }
   if (!pair && big_tiles >= 512) return v ? go(CfgBig8{}, TrueT{}) : go(CfgBig8{}, FalseT{});
   const int NG = fcn_split_groups(R1, R2, c.L, symmetric, num_cu, part != nullptr, pair);
-  auto go_split = [&](auto vec_tag, auto dma_tag, auto pair_tag) -> hipError_t {
+  auto go_split = [&](auto vec_tag, auto dma_tag, auto rows_tag) -> hipError_t {
     using Cfg = CfgSmall;
     constexpr bool VEC = decltype(vec_tag)::value;
     constexpr bool DMA = decltype(dma_tag)::value;
-    constexpr bool PAIR = decltype(pair_tag)::value;
+    constexpr int ROWS = decltype(rows_tag)::value;
     using L = LoadKInnerT<VEC>;
     constexpr int max_bytes = DMA ? gemm_dma_smem_bytes<Cfg, kSplitStages>() : gemm_smem_bytes<Cfg, L, L>();
     static_assert(64 * 64 <= max_bytes / 4, "Gram block must fit the LDS tile area");
-    const int bytes = PAIR ? pair_smem_bytes<Cfg, kSplitStages>(O) : max_bytes;
+    const int bytes = ROWS != kRowsFp32 ? pair_smem_bytes<Cfg, kSplitStages, ROWS>(O) : max_bytes;
     const int tm = cdiv(R1, 64), tn = cdiv(R2, 64);
     const int T = symmetric ? tn * (tn + 1) / 2 : tm * tn;
     const FastDiv fO((uint32_t)O);
-    hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_lpart<Cfg, VEC, DMA, PAIR>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_ntk_fcn_lpart<Cfg, VEC, DMA, ROWS>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       PAIR ? pair_smem_limit<Cfg, kSplitStages>() : max_bytes);
+                                       ROWS != kRowsFp32 ? pair_smem_limit<Cfg, kSplitStages, ROWS>() : max_bytes);
     if (e != hipSuccess) return e;
-    k_ntk_fcn_lpart<Cfg, VEC, DMA, PAIR><<<dim3(8 * cdiv((long long)T * NG, 8)), dim3(Cfg::THREADS), bytes, s>>>(
+    k_ntk_fcn_lpart<Cfg, VEC, DMA, ROWS><<<dim3(8 * cdiv((long long)T * NG, 8)), dim3(Cfg::THREADS), bytes, s>>>(
         c, N1, N2, fO, symmetric, tn, T, NG, part);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1516,11 +1527,11 @@ hipError_t launch_ntk_fcn(hipStream_t s, const FcnContraction& c, int N1, int N2
                                                     NG, part, theta);
     return hipGetLastError();
   };
-  if (NG >= 1 && pair) return go_split(TrueT{}, TrueT{}, TrueT{});
+  if (NG >= 1 && pair) return go_split(TrueT{}, TrueT{}, RowsT<kRowsPair>{});
   if (pair) return hipErrorInvalidValue;
   if (NG >= 2)
-    return dma ? go_split(TrueT{}, TrueT{}, FalseT{})
-               : (v ? go_split(TrueT{}, FalseT{}, FalseT{}) : go_split(FalseT{}, FalseT{}, FalseT{}));
+    return dma ? go_split(TrueT{}, TrueT{}, RowsT<kRowsFp32>{})
+               : (v ? go_split(TrueT{}, FalseT{}, RowsT<kRowsFp32>{}) : go_split(FalseT{}, FalseT{}, RowsT<kRowsFp32>{}));
   return v ? go(CfgSmall{}, TrueT{}) : go(CfgSmall{}, FalseT{});
 }
 

@@ -46,6 +46,10 @@ CASES = [
     ("one hidden layer", [131], 10, 300, 127, "relu", False),
     ("100 outputs, few samples", [200, 140], 100, 17, 13, "erf", False),
     ("stream-K tiles", [133, 160], 10, 300, 301, "relu", False),
+    # from 512 tiles of 128 x 128 on; the Gram block of a tile does not fit in LDS beside the stages
+    ("stream-K tiles, one output", [133, 160], 1, 2905, 2950, "relu", True),
+    ("stream-K tiles, two outputs", [160, 130], 2, 1460, 1461, "erf", False),
+    ("stream-K tiles, three outputs", [160, 130], 3, 970, 981, "relu", False),
 ]
 
 
