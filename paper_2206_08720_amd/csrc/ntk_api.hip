@@ -458,7 +458,34 @@ static long long weight_cols(const ntk_layer_desc& L, int cin) {
   }
 }
 
-static void plan_cnn(ntk_handle* h) {
+// Whether a CNN's backward and weight-space products run on f16 pairs: two more launches (the images'
+// maxima and the kernels' pair rows, 15 to 35 us) against the time of the products that have a pair form
+// (the folded last layer's `fold` has no cotangents in it, an inside-out layer no weight-space product).
+// 4x4 images, 5 GFLOP: 348 us with pairs, 316 us with the fp32 MFMA (the few workgroups wait on loads
+// either way).  Ten outputs, 32x32 images: 6.9 GFLOP 216 against 211 us, 10.4 229 against 235, 13.9 243
+// against 280; 16x16 images, 14 GFLOP: 228 against 256; one output, 15 GFLOP: 411 against 407.
+// Channel counts that the direct-to-LDS fp32 kernels do not take (not a multiple of 32 behind a
+// backward, of 4 in a weight-space product) repay pairs earlier: 15x15 images of four layers 3.4 GFLOP
+// 343 against 311 us, 4.6 356 against 365; 30x26 images 2.7 GFLOP 329 against 341, 5.4 386 against 435.
+constexpr double kConvPairMinFlops = 1.2e10, kConvPairMinFlopsRagged = 4e9;
+static bool cnn_pair_bwd(const ntk_handle* h, int l) {
+  return l > 0 && h->layers[l].kind == NTK_CONV3X3_SAME && conv_bwd_pair_ok(h->bw[l], h->ch[l + 1]);
+}
+static bool cnn_pair_pays(const ntk_handle* h, double M, int Oe, const std::vector<char>& inside, bool fold) {
+  double flops = 0;
+  bool ragged = false;
+  for (int l = 0; l < h->nc; ++l) {
+    const int kind = h->layers[l].kind, cin = h->ch[l], cout = h->ch[l + 1];
+    if (kind != NTK_CONV3X3_SAME && kind != NTK_CONV1X1) continue;
+    const double f = 2.0 * M * h->bh[l] * h->bw[l] * weight_cols(h->layers[l], cin);
+    if (!inside[l]) flops += f * (fold && l == h->nc - 1 ? 1 : Oe);
+    if (cnn_pair_bwd(h, l)) flops += f * Oe;
+    ragged = ragged || cout % 4 != 0 || (l && kind == NTK_CONV3X3_SAME && cout % 32 != 0);
+  }
+  return flops >= (ragged ? kConvPairMinFlopsRagged : kConvPairMinFlops);
+}
+
+static void plan_cnn(ntk_handle* h, bool pairs = true) {
   const int n = (int)h->layers.size();
   h->nc = n - 2;
   h->H = h->in_h;
@@ -507,14 +534,15 @@ static void plan_cnn(ntk_handle* h) {
   for (int l = 1; l < nc; ++l)   // flipped 3x3 kernels, transposed pointwise weights
     if (h->layers[l].kind == NTK_CONV3X3_SAME || h->layers[l].kind == NTK_CONV1X1)
       h->off_Kt[l] = take((size_t)(h->layers[l].kind == NTK_CONV1X1 ? 1 : 9) * h->ch[l] * h->ch[l + 1]);
-  h->cpair = !h->lean;
+  // (if any call of these sizes can take pairs)
+  h->cpair = pairs && !h->lean && cnn_pair_pays(h, (double)Mmax, (int)O, std::vector<char>(nc, 0), false);
   if (h->cpair) {
     h->off_Kp.assign(nc, 0);
     h->off_ke.assign(nc, 0);
     h->off_km.assign(nc, 0);
     h->off_kf.assign(nc, 0);
     for (int l = 1; l < nc; ++l)
-      if (h->layers[l].kind == NTK_CONV3X3_SAME && conv_bwd_pair_ok(h->bw[l], h->ch[l + 1])) {
+      if (cnn_pair_bwd(h, l)) {
         h->off_Kp[l] = take((size_t)9 * h->ch[l] * pair_stride(h->ch[l + 1]));
         h->off_ke[l] = take(h->ch[l]);
         h->off_km[l] = take(h->ch[l + 1]);
@@ -571,6 +599,28 @@ static void plan_cnn(ntk_handle* h) {
   h->ws_bytes = off;
 }
 
+// Whether the backward (and the contraction of `pairs` input pairs) of a fully-connected net runs
+// on pair rows.  It costs launches (the weights' statistics and pair rows, a pass over the rows per
+// layer), so small problems keep the fp32 kernels.  Widths that take the direct-to-LDS fp32 kernels
+// are even at 7.8 GFLOP (width 512, depth 4: 103 us in fp32, 106 on pairs at 5.4 GFLOP; 130.5, 130.4 at
+// 7.8; 196, 169 at 10.7; width 128: 129, 133 at 7.2; width 1024: 186, 168 at 11.4; the batch diagonal of
+// width 512: 153.4, 152.5 at 8.1); those that do not, below 0.5 GFLOP (widths 500, 401, 333: 112, 92 at
+// 0.7; width 250: 113, 107 at 0.4).  Layers narrower than 128 keep fp32: sums that short are no more
+// exact on pairs.
+constexpr double kPairMinFlops = 8e9, kPairMinFlopsRagged = 5e8;
+static bool fcn_pair_pays(const ntk_handle* h, double M, int Oe, double pairs) {
+  double flops = 0;
+  bool ragged = false;
+  for (int l = 0; l < h->L; ++l) {
+    const double d = h->dims[l + 1];
+    if (d < 128) return false;
+    ragged = ragged || h->dims[l + 1] % 32 != 0;
+    if (l >= 1) flops += 2.0 * M * Oe * d * h->dims[l];
+    flops += 2.0 * pairs * Oe * Oe * d;
+  }
+  return flops >= (ragged ? kPairMinFlopsRagged : kPairMinFlops);
+}
+
 static void destroy_sync_objects(ntk_handle* h) {
   if (h->aux) (void)hipStreamSynchronize(h->aux);
   for (hipEvent_t* ev : {&h->ev_fork, &h->ev_tr, &h->ev_fwd, &h->ev_gram, &h->ev_seed, &h->ev_bwd}) {
@@ -621,14 +671,17 @@ extern "C" int ntk_init(const ntk_model_desc* model, int max_n1, int max_n2, voi
   if (h->cnn) {
     plan_cnn(h);
   } else {
-    h->pair = pair_in_range(*h);
     plan_fcn(h);
+    // buffers of pair rows, if any call of these sizes can take them
+    h->pair = pair_in_range(*h) && fcn_pair_pays(h, (double)max_n1 + max_n2, h->out_dim, (double)max_n1 * max_n2);
+    if (h->pair) plan_fcn(h);
   }
   e = hipMalloc((void**)&h->ws, h->ws_bytes);
-  if (e != hipSuccess && h->pair) {   // without the pair rows' buffers
+  if (e != hipSuccess && (h->pair || h->cpair)) {   // without the pair products' buffers: all in fp32
     (void)hipGetLastError();
     h->pair = false;
-    plan_fcn(h);
+    if (h->cnn) plan_cnn(h, false);
+    else plan_fcn(h);
     e = hipMalloc((void**)&h->ws, h->ws_bytes);
   }
   if (e != hipSuccess) {
@@ -805,28 +858,6 @@ static int fcn_forward(ntk_handle* h, const float* const* params, const float* X
   int rc = fcn_stack(h, params, X1, n1, X2, n2, sym, h0);
   if (rc != NTK_OK) return rc;
   return fcn_forward_rows(h, params, *h0, 0, sym ? n1 : n1 + n2, h->stream, true, seedW, seedO, seedG);
-}
-
-// Whether the backward (and the contraction of `pairs` input pairs) of a fully-connected net runs
-// on pair rows.  It costs launches (the weights' statistics and pair rows, a pass over the rows per
-// layer), so small problems keep the fp32 kernels.  Widths that take the direct-to-LDS fp32 kernels
-// are even at 7.8 GFLOP (width 512, depth 4: 103 us in fp32, 106 on pairs at 5.4 GFLOP; 130.5, 130.4 at
-// 7.8; 196, 169 at 10.7; width 128: 129, 133 at 7.2; width 1024: 186, 168 at 11.4; the batch diagonal of
-// width 512: 153.4, 152.5 at 8.1); those that do not, below 0.5 GFLOP (widths 500, 401, 333: 112, 92 at
-// 0.7; width 250: 113, 107 at 0.4).  Layers narrower than 128 keep fp32: sums that short are no more
-// exact on pairs.
-constexpr double kPairMinFlops = 8e9, kPairMinFlopsRagged = 5e8;
-static bool fcn_pair_pays(const ntk_handle* h, int M, int Oe, double pairs) {
-  double flops = 0;
-  bool ragged = false;
-  for (int l = 0; l < h->L; ++l) {
-    const double d = h->dims[l + 1];
-    if (d < 128) return false;
-    ragged = ragged || h->dims[l + 1] % 32 != 0;
-    if (l >= 1) flops += 2.0 * M * Oe * d * h->dims[l];
-    flops += 2.0 * pairs * Oe * Oe * d;
-  }
-  return flops >= (ragged ? kPairMinFlopsRagged : kPairMinFlops);
 }
 
 // forward FLOPs from which the FCN path puts independent steps on the second stream
@@ -1287,30 +1318,6 @@ static double inside_out_cost(double pairs, int D, int Cin, int C, int Oe, bool 
   const double gram_blocks = trace ? 1 : nob * nob, out_blocks = trace ? nob : nob * nob;
   return kInsideOutTimeWeight * pairs *
          (gram_blocks * Dp * Dp * Ci + out_blocks * (16.0 * Dp * Dp * C + 256.0 * Dp * C));
-}
-
-// Whether a CNN's backward and weight-space products run on f16 pairs: two more launches (the images'
-// maxima and the kernels' pair rows, 15 to 35 us) against the time of the products that have a pair form
-// (the folded last layer's `fold` has no cotangents in it, an inside-out layer no weight-space product).
-// 4x4 images, 5 GFLOP: 348 us with pairs, 316 us with the fp32 MFMA (the few workgroups wait on loads
-// either way).  Ten outputs, 32x32 images: 6.9 GFLOP 216 against 211 us, 10.4 229 against 235, 13.9 243
-// against 280; 16x16 images, 14 GFLOP: 228 against 256; one output, 15 GFLOP: 411 against 407.
-// Channel counts that the direct-to-LDS fp32 kernels do not take (not a multiple of 32 behind a
-// backward, of 4 in a weight-space product) repay pairs earlier: 15x15 images of four layers 3.4 GFLOP
-// 343 against 311 us, 4.6 356 against 365; 30x26 images 2.7 GFLOP 329 against 341, 5.4 386 against 435.
-constexpr double kConvPairMinFlops = 1.2e10, kConvPairMinFlopsRagged = 4e9;
-static bool cnn_pair_pays(const ntk_handle* h, int M, int Oe, const std::vector<char>& inside, bool fold) {
-  double flops = 0;
-  bool ragged = false;
-  for (int l = 0; l < h->nc; ++l) {
-    const int kind = h->layers[l].kind, cin = h->ch[l], cout = h->ch[l + 1];
-    if (kind != NTK_CONV3X3_SAME && kind != NTK_CONV1X1) continue;
-    const double f = 2.0 * M * h->bh[l] * h->bw[l] * weight_cols(h->layers[l], cin);
-    if (!inside[l]) flops += f * (fold && l == h->nc - 1 ? 1 : Oe);
-    if (l && h->off_Kp[l]) flops += f * Oe;
-    ragged = ragged || cout % 4 != 0 || (l && kind == NTK_CONV3X3_SAME && cout % 32 != 0);
-  }
-  return flops >= (ragged ? kConvPairMinFlopsRagged : kConvPairMinFlops);
 }
 
 static int compute_cnn(ntk_handle* h, const float* const* params, const float* X1, int n1,

@@ -235,3 +235,32 @@ def test_pair_calls_of_two_threads_with_different_outputs():
     for th in threads:
         th.join()
     assert not errors, errors
+
+
+def test_pair_buffers_are_planned_once_and_only_where_pairs_can_run():
+    """Options allocate nothing, and a network that never takes the pair kernels (a layer below 128, or too
+    small at the handle's largest batches) has no buffers for them: its workspace grows with the outputs by
+    the fp32 cotangent rows alone."""
+    import torch
+    from paper_2206_08720_amd.ntk import NTK
+
+    def handle(widths, O, n):
+        return NTK(wl.fcn_spec("mem", 64, widths, O), n, n)
+
+    h = handle([512, 512, 512], 100, 300)
+    try:
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        for variant in (("trace", "full", 0), ("logit", "diagonal", 1), ("full", "diagonal", 0)):
+            h.set_variant(*variant)
+            assert torch.cuda.mem_get_info()[0] == free
+    finally:
+        h.close()
+    for widths, n in (([256, 64, 256], 100), ([256, 128, 256], 2)):
+        sizes = []
+        for O in (100, 200):
+            h = handle(widths, O, n)
+            sizes.append(h.workspace_bytes())
+            h.close()
+        rows = 2 * n * 100 * sum(widths) * 4
+        assert abs(sizes[1] - sizes[0] - rows) <= 4096, (widths, sizes, rows)   # (rounded to 256 bytes an array)
