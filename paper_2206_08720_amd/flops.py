@@ -275,8 +275,9 @@ def vp_flops(spec, n1, n2, symmetric=False):
     """Operation count of one NTK-vector product Theta(X1, X2) v (ntk_vector_product), by the
     kernel groups that run it: the forward pass of both batches, the VJP of batch 2 (one
     cotangent row per sample), the weight-space cotangent (sum over batch 2) and the JVP of
-    batch 1.  FCN: `gram_products` is the weight-space cotangent plus the JVP (both run on the
-    Gram kernel).  CNN: `forward_and_jvp` is the forward pass plus the JVP convolutions."""
+    batch 1.  FCN: `gram_products` is the JVP's products on the Gram kernel: the tangents through the
+    weights, and the layers' own summands either through the weight-space cotangent, (n1 + n2) in out
+    multiply-adds, or through the layer-input Grams, n1 n2 (in + out), whichever is less in all.  CNN: `forward_and_jvp` is the forward pass plus the JVP convolutions."""
     M = n1 if symmetric else n1 + n2
     layers = spec["layers"]
     if any(Lr["kind"] != "dense" for Lr in layers):
@@ -300,8 +301,8 @@ def vp_flops(spec, n1, n2, symmetric=False):
         st = {
             "forward": sum(2.0 * M * d[l] * d[l + 1] for l in range(L)),
             "vjp_backward": sum(2.0 * n2 * d[l + 1] * d[l] for l in range(1, L + 1)),
-            "gram_products": sum(2.0 * n2 * d[l + 1] * d[l] for l in range(L + 1))
-            + sum(2.0 * n1 * d[l] * d[l + 1] for l in range(L + 1))
+            "gram_products": min(sum(2.0 * (n1 + n2) * d[l + 1] * d[l] for l in range(L + 1)),
+                                 sum(2.0 * n1 * n2 * (d[l] + d[l + 1]) for l in range(L + 1)))
             + sum(2.0 * n1 * d[l] * d[l + 1] for l in range(1, L + 1)),
         }
     st["total"] = sum(st.values())

@@ -8,7 +8,7 @@ terms those of the appendix "CNN NTK Complexity" / table "complexities_cnn".
 import pytest
 
 import workloads as wl
-from paper_2206_08720_amd.flops import cnn_flops, fcn_flops, ntk_entries
+from paper_2206_08720_amd.flops import cnn_flops, fcn_flops, ntk_entries, vp_flops
 
 
 def test_fcn_terms_match_section_4_1():
@@ -171,3 +171,11 @@ def test_pointwise_counts():
     assert g["contraction"] == 2 * N * N * O * O * (3 * 6 + 6 + 9 * 6)
     assert g["gram"] == 2 * N * N * 5 + 2 * N * N * 5 * 6 + 3 * N * N * O * O * 5
     assert param_total(spec) == oracle.param_count(spec)
+
+
+def test_vector_product_counts_the_cheaper_form():
+    """One hidden layer of 8 -> 6 -> 2: through the Grams for 2 + 3 samples, through the weights for 50 + 60."""
+    spec = wl.fcn_spec("vp", 8, [6], 2)
+    tangents = {n1: 2.0 * n1 * 6 * 2 for n1 in (2, 50)}
+    assert vp_flops(spec, 2, 3)["gram_products"] == 2.0 * 2 * 3 * (8 + 6 + 6 + 2) + tangents[2]
+    assert vp_flops(spec, 50, 60)["gram_products"] == 2.0 * 110 * (8 * 6 + 6 * 2) + tangents[50]
