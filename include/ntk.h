@@ -15,7 +15,13 @@
  * Section 4.1 for the FCN and the appendix "CNN NTK Complexity" for the CNN).
  *
  * The contractions run on the GPU in fp32 with fp32 accumulation (the paper's
- * experiments use 32-bit precision, appendix "Experimental Details").  The forward
+ * experiments use 32-bit precision, appendix "Experimental Details").  Large products run on
+ * the f16 matrix cores: each fp32 factor is split into two f16 values under one exponent per
+ * row (23 bits of what lies within 2^18 of the row's largest element, 2^-40 of that element
+ * below), three f16 products per product, sums in fp32.  Their errors, relative to the norms of
+ * the rows multiplied, are those of fp32 products or smaller; an entry of Theta far below the
+ * norms of its two Jacobian rows (samples that share none of their large units) keeps fewer
+ * bits of its own.  ntk_compute_static and NTK_METHOD_JACOBIAN multiply in fp32 throughout.  The forward
  * pre-activations are accumulated in fp64 from the fp32 layer inputs and weights, so that
  * the activation's decisions (the ReLU sign) are those of the exact pre-activation; every
  * stored array (layer inputs, derivatives, cotangents, Theta) is fp32.
@@ -182,6 +188,9 @@ typedef struct ntk_handle ntk_handle;
  * that break this are refused with NTK_E_UNSUPPORTED, naming the array, before any HIP call
  * and before anything is allocated; larger problems are computed in blocks of samples
  * (Theta(X1[R1], X2[R2]) is the block [R1, R2] of Theta(X1, X2)).
+ * Where calls of these sizes can take the f16 pair products, the workspace holds their buffers;
+ * if it does not fit the memory that is free, it is planned again without them and the handle
+ * computes in fp32 throughout (NTK_E_OOM if that does not fit either).
  * The device is the one current on the calling thread; later calls must keep it current.
  */
 int ntk_init(const ntk_model_desc* model, int max_n1, int max_n2, void* hip_stream,
@@ -203,19 +212,22 @@ int ntk_init(const ntk_model_desc* model, int max_n1, int max_n2, void* hip_stre
  *           Every entry is written.  theta must not overlap the inputs.
  * NTK_E_ARG also when NTK_OPT_LOGIT is not below O, or NTK_BATCH_DIAGONAL with n1 != n2.
  * Stream-ordered and asynchronous.  Deterministic: two calls with the same inputs
- * give bit-identical theta (no atomics).
+ * give bit-identical theta (the only atomics are maxima, which no order changes).
  */
 int ntk_compute(ntk_handle* h, const float* const* params, const float* X1, int n1,
                 const float* X2, int n2, float* theta);
 
 /*
  * ntk_vector_product -- enqueue out = Theta(X1, X2) v without forming Theta (the NTK-vector
- * product of Section 3.3, Eq. ntk_vp_main): the VJP of batch 2 at v gives the weight-space
- * vector theta_c = J(X2)^T v, and the JVP of batch 1 along theta_c gives J(X1) theta_c.
+ * product of Section 3.3, Eq. ntk_vp_main): the VJP of batch 2 at v gives the cotangents
+ * delta_l of every layer and with them the weight-space vector theta_c = J(X2)^T v, and the JVP of
+ * batch 1 along theta_c gives J(X1) theta_c.  An FCN whose layer-input Grams cost less than its
+ * weight-space vector (n1 n2 (in + out) against (n1 + n2) in out multiply-adds, summed over the
+ * layers) takes layer l's summand h1_l (theta_c^l)^T as (h1_l h2_l^T) delta_l without forming theta_c.
  *   params, X1, n1, X2, n2  as for ntk_compute.
  *   v    device [n2, O] fp32: v[n2*O + o2].
  *   out  device [n1, O] fp32: out[n1*O + o1] = sum_{n2, o2} Theta(x1_{n1}, x2_{n2})[o1, o2] v[n2, o2].
- * Time about 3 forward passes of the batches (no N1 N2 O^2 term).  The output and batch
+ * Time about 3 forward passes of the batches or less (no N1 N2 O^2 term).  The output and batch
  * variants and NTK_OPT_METHOD do not apply.  Every layer kind is supported.  The first call on a handle allocates the
  * weight-space vector (one float per parameter) and the tangent buffers.  Stream-ordered,
  * asynchronous, deterministic; NTK_E_ARG for null pointers or sizes out of range.
@@ -255,13 +267,15 @@ int ntk_free(ntk_handle* h);
  * h == NULL, the message of the last failed ntk_init on this thread. */
 const char* ntk_last_error(const ntk_handle* h);
 
-/* ntk_set_option -- set NTK_OPT_* (see above).  NTK_E_ARG for an unknown option/value. */
+/* ntk_set_option -- set NTK_OPT_* (see above): host work only, nothing is allocated.  NTK_E_ARG
+ * for an unknown option/value. */
 int ntk_set_option(ntk_handle* h, int option, int value);
 
 /* ntk_set_stream -- change the stream later work is enqueued on (NULL = default). */
 int ntk_set_stream(ntk_handle* h, void* hip_stream);
 
-/* ntk_workspace_bytes -- bytes of device workspace the handle holds. */
+/* ntk_workspace_bytes -- bytes of the workspace that ntk_init allocated (the buffers of the
+ * Jacobian baseline and of ntk_vector_product, allocated by their first calls, come on top). */
 long long ntk_workspace_bytes(const ntk_handle* h);
 
 /* ---- per-kernel timing ------------------------------------------------------------

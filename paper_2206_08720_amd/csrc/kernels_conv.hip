@@ -2209,13 +2209,14 @@ k_ntk_reduce(const float* __restrict__ part, int splits, int N1, int N2, int O,
   const int z1 = ZG > 1 ? (int)((long long)splits * (zg + 1) / ZG) : splits;
   for (long long i0 = blockIdx.x * (long long)EB; i0 < total; i0 += (long long)gridDim.x * EB) {
     const long long i = i0 + te;
-    const bool in = i < total;
-    if (ZG == 1 && !in) return;   // later passes of this thread lie further on
-    const int r1 = in ? (int)(i / R2) : 0, r2 = in ? (int)(i - (long long)r1 * R2) : 0;
+    if (ZG == 1 && i >= total) return;   // later passes of this thread lie further on
+    const int r1 = (int)(min(i, total - 1) / R2), r2 = (int)(min(i, total - 1) - (long long)r1 * R2);
+    bool direct, mirror;
+    sym_writes(symmetric, r1, r2, direct, mirror);
+    const bool in = i < total && direct;
     float v = 0.f;
     if (in) {
-      long long src = i;
-      if (symmetric && r1 > r2) src = (long long)r2 * R2 + r1;   // exactly symmetric: see sym_writes
+      const long long src = i;
       float a[4] = {0.f, 0.f, 0.f, 0.f};   // four independent chains keep several loads in flight
       int z = z0;
       for (; z + 4 <= z1; z += 4) {
@@ -2238,12 +2239,13 @@ k_ntk_reduce(const float* __restrict__ part, int splits, int N1, int N2, int O,
     if (!in || zg) continue;
     const int n1 = r1 / O, o1 = r1 - n1 * O, n2 = r2 / O, o2 = r2 - n2 * O;
     if (w) v *= w[(long long)n1 * N2 + n2];
+    if (!accumulate && o1 == o2 && gram) v += rscale * gram[(long long)n1 * N2 + n2];
     float* dst = theta + (((long long)n1 * N2 + n2) * O + o1) * O + o2;
-    if (accumulate)
-      v += *dst;
-    else if (o1 == o2 && gram)
-      v += rscale * gram[(long long)n1 * N2 + n2];
-    *dst = v;
+    *dst = accumulate ? *dst + v : v;
+    if (mirror) {
+      float* dst2 = theta + (((long long)n2 * N1 + n1) * O + o2) * O + o1;
+      *dst2 = accumulate ? *dst2 + v : v;
+    }
   }
 }
 

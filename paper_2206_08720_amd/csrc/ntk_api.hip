@@ -891,8 +891,8 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
   // that no transposed copies are made; with one stream, the Grams in the launch of the first
   // backward layer
   bool bwd_w = false, gram_in_bwd = false;
-  // The backward and the full contraction on pair rows; the variants' contractions read fp32 rows,
-  // which the backward then writes beside them.
+  // The backward and the full contraction on pair rows; the variants' contractions read the fp32 rows
+  // that the backward writes.
   const bool full = !logit && !trace && !diag;
   const bool pair = h->pair && !jc && L >= 1 && fcn_pair_pays(h, M, Oe, full ? (sym ? 0.5 : 1.0) * n1 * n2 : 0.0) &&
                     (full ? ntk_fcn_pair_ok((long long)n1 * O, (long long)n2 * O, L, sym ? 1 : 0, h->num_cu, true)

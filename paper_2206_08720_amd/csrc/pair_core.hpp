@@ -12,8 +12,14 @@
 // library product reaches on the card).
 //
 // One exponent e per row of an operand (a row is what a sum runs along), so that a row of any
-// magnitude uses the f16 range: |x| 2^-e < 2^16, and values down to 2^-18 of the largest keep all
-// 23 bits (below that the absolute error is 2^-25 2^e, 2^-40 of the row's largest).
+// magnitude uses the f16 range: |x| 2^-e < 2^15, and values down to 2^-18 of the largest keep all
+// 23 bits (below that the absolute error is 2^-25 2^e, 2^-40 of the row's largest).  Two rules follow
+// for whoever makes pairs.  The exponent is that of the row's true largest element: a bound that multiplies
+// maxima of different elements can lie any number of bits above it.  And where the sum's terms count alike
+// although one factor is small where the other is large, the factors are balanced by powers of two first
+// (kernels_pair.hip).  The error of a sum is then relative to the product of its rows' norms, like the
+// rounding of the sum itself; what is lost is the relative precision of a sum whose rows have their large
+// elements at different k.
 //
 // Pair rows in memory: groups of 8 consecutive k, 16 bytes of hi then 16 bytes of lo, so a row of
 // K floats takes the same 4 K bytes, is loaded into LDS by the same 16-byte chunks as fp32 rows

@@ -74,8 +74,8 @@ def test_pair_rows_variants(variant):
 
 
 def test_pair_rows_magnitudes():
-    """Units, outputs and layers whose weights differ by powers of two up to 2^40, and dead units
-    (rows of zeros): every row has an exponent of its own."""
+    """Outputs and whole layers whose weights differ by powers of two up to 2^40, and dead units (rows of
+    zeros): every row has an exponent of its own.  (Units of different scales: test_gpu_pair_scales.py.)"""
     spec = wl.fcn_spec("pairm", 64, [200, 170, 150], 10)
     params = wl.make_params(spec, 47, "2/fan_in")
     rng = np.random.default_rng(48)
@@ -151,7 +151,8 @@ def test_pair_conv_shapes(case):
 
 
 def test_pair_conv_magnitudes():
-    """Images, outputs and layers that differ by powers of two, an image of zeros."""
+    """Images, outputs and whole layers that differ by powers of two, an image of zeros.  (Channels of
+    different scales: test_gpu_pair_scales.py.)"""
     spec = wl.cnn_layers_spec("paircm", (20, 20), 3, [(C3, 64, "relu", False)] * 3, 10)
     params = wl.make_params(spec, 64, "2/fan_in")
     rng = np.random.default_rng(65)
