@@ -228,3 +228,12 @@ def test_jacobian_baseline_and_static_calls_stay_in_fp32(call):
     print(f"[parity] fp32 {call}: entries {err:.3e}", flush=True)
     # fp32 partial sums of about 1000 columns: 1000 2^-24 at most
     assert err <= 6e-5
+
+
+@pytest.mark.parametrize("kind", ["normal 0", "normal 4"])
+def test_pair_conv_long_runs_of_block_diagonal_layers(kind):
+    """Seven depthwise, scale and pool layers between two convolutions: the maxima are the images' own, however
+    many layers lie between."""
+    blocks = [(C3, 64, "relu", True), (DW, "relu", False), (SC, "relu", True), (DW, "relu", True), (SC, "relu", False),
+              (POOL,), (DW, "relu", False), (SC, "relu", True), (C3, 64, "relu", False), (C3, 64, "relu", False)]
+    _conv_check(f"long run {kind}", ((24, 20), blocks, 44, 30), lambda spec, params: rescale_cnn(spec, params, kind, 99))
