@@ -1136,8 +1136,9 @@ static int compute_fcn(ntk_handle* h, const float* const* params, const float* X
         prof_begin(P, s, cls);
         if (prep)
           e = launch_pair_prep(s, pair_weights(), pair_rows(L - 1, 0, M, true), gram_batch(), n1, n2, h->num_cu);
-        else
-          e = seed_pairs(s, 0, M);
+        else   // (a half's rows have a place of their own in the balanced rows' buffer)
+          e = seed_pairs(s, 0, MA);
+        if (e == hipSuccess && split) e = seed_pairs(s, MA, M);
         prof_end(P, s, cls);
         if (e != hipSuccess) return hip_fail(h, e, "readout cotangents");
       }

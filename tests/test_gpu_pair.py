@@ -265,3 +265,25 @@ def test_pair_buffers_are_planned_once_and_only_where_pairs_can_run():
             h.close()
         rows = 2 * n * 100 * sum(widths) * 4
         assert abs(sizes[1] - sizes[0] - rows) <= 4096, (widths, sizes, rows)   # (rounded to 256 bytes an array)
+
+
+@pytest.mark.parametrize("variant", [("full", "full", 0), ("trace", "diagonal", 0)])
+def test_pair_halves_on_two_streams_with_layers_of_different_widths(variant):
+    """The two halves of the samples may be at different layers; with rows of different lengths they must not
+    reach into each other's.  With per-kernel timing the forward runs on one stream: the same bits."""
+    spec = wl.fcn_spec("halves", 64, [2304, 2048, 2560, 2112], 10)
+    params = wl.make_params(spec, 56, "2/fan_in")
+    X1, X2 = wl.make_inputs(spec, 500, 57), wl.make_inputs(spec, 500, 58)
+    print(f"[pair] halves {variant}", flush=True)
+    prof = {}
+    ref = gpu_ntk(spec, params, X1, X2, variant=variant, profile=prof)
+    assert "dense_bwd_pair" in prof
+    for _ in range(3):
+        assert np.array_equal(gpu_ntk(spec, params, X1, X2, variant=variant), ref)
+    sub = [0, 249, 250, 499]
+    full = oracle.ntk_structured_fp64(spec, params, X1[sub], X2[sub], layer_storage=S)
+    d1, d2 = (oracle.ntk_structured_diag_fp64(spec, params, X[sub], layer_storage=S) for X in (X1, X2))
+    got = ref[sub] if variant[1] == "diagonal" else ref[np.ix_(sub, sub)]
+    cs, nw = scaled_errors(got, variant_of(full, *variant), variant_scale(d1, d2, *variant))
+    report(f"halves {variant}", cs, nw)
+    assert cs <= PAIR_TOL and nw <= PAIR_TOL
